@@ -1,0 +1,274 @@
+"""The work this framework is used for, as cases that can be timed and compared.
+
+A case names one call of the public entry points together with the data it is made on: a proximity graph over
+an item table, a relevance metric, a batch of users.  `prepare` builds what a serving program holds before a
+request arrives (graph and metric handles, workspace, result arrays, the users of the batch), `run` is one call.
+
+    latency_1        one user at a time on a million-item table: a request that is not batched with others
+    tiny_f32         the smallest table, reference precision, a short list: everything is latency
+    deep_f32         the same table and metric searched to high recall (lists of 4,096 entries)
+    batch_1m         the ordinary batch: a thousand users, a million items, two hidden layers, bf16
+    batch_10m_wide   the headline batch: 4,096 users, 10^7 items of 128 dimensions, the wide metric, L = 1,024
+    deep_10m_wide    the same batch where its recall flattens: L = 8,192, 64 nodes expanded per round
+    shallow_20m      a very large batch on a large table with the one-hidden-layer metric: bound by gathering
+    ragged_10m       requests with their own list lengths, widths and round limits, skewed cluster sizes
+    two_stage_f8     8-bit traversal, its best 1,024 candidates ranked again by the 16-bit metric
+    stream_f16       a long queue of users served through fewer slots, fp16 tables, an odd number of both
+    exhaustive_f16   every item scored for every user: what recall is measured against
+    pairs_own_widths scores of given (user, item) pairs under a metric with layer widths of the caller's own
+
+Items are a Gaussian mixture; half of an item's edges go to its neighbours inside its cluster (next in the order
+of one coordinate of the deviation from the cluster's mean), half are uniform random; ids are a random
+permutation.  Weights are He-initialised with small biases.
+"""
+import math
+
+import torch
+
+import paper_2502_11490_amd as ann
+
+HEAD_WEIGHTS = {1: (1.0,), 2: (0.6, 0.4), 3: (0.5, 0.3, 0.2), 4: (0.4, 0.3, 0.2, 0.1)}
+TORCH_TYPE = {"f32": torch.float32, "bf16": torch.bfloat16, "f16": torch.float16, "f8": torch.bfloat16}
+ANN_TYPE = {"f32": ann.ANN_F32, "bf16": ann.ANN_BF16, "f16": ann.ANN_F16, "f8": ann.ANN_F8}
+ITEM_BYTES = {"f32": 4, "bf16": 2, "f16": 2, "f8": 1}
+# widths of the metrics that the repository's configurations use: item (= user) width, hidden layers, heads
+METRICS = {"small": (32, "64", 3), "two": (64, "256,128", 3), "wide": (128, "512,256", 4), "one": (64, "256", 3)}
+
+
+def _search(name, metric, dtype, N, clusters, R, Q, E, W, L, k, **more):
+    d, hidden, heads = METRICS[metric]
+    return dict(name=name, kind="search", dtype=dtype, N=N, d=d, d_user=d, hidden=hidden, heads=heads,
+                clusters=clusters, R=R, Q=Q, E=E, W=W, L=L, k=k, **more)
+
+
+def listed():
+    cases = [
+        _search("latency_1", "two", "bf16", 1_000_000, 1024, 32, 1, 4, 4, 64, 100),
+        _search("tiny_f32", "small", "f32", 10_000, 16, 16, 64, 1, 2, 32, 10),
+        _search("deep_f32", "small", "f32", 10_000, 16, 16, 64, 1, 16, 4096, 100),
+        _search("batch_1m", "two", "bf16", 1_000_000, 1024, 32, 1024, 4, 4, 512, 100),
+        _search("batch_10m_wide", "wide", "bf16", 10_000_000, 16384, 32, 4096, 8, 8, 1024, 200, locality=True),
+        _search("deep_10m_wide", "wide", "bf16", 10_000_000, 16384, 32, 4096, 8, 64, 8192, 200, locality=True),
+        _search("shallow_20m", "one", "bf16", 20_000_000, 16384, 32, 16384, 4, 4, 64, 100),
+        _search("ragged_10m", "two", "bf16", 10_000_000, 8192, 32, 8192, 4, 16, 256, 100, cap=64, ragged=True,
+                zipf=True),
+        _search("two_stage_f8", "wide", "f8", 4_000_000, 6553, 32, 2048, 8, 16, 2048, 200, locality=True,
+                candidates=1024),
+        _search("stream_f16", "wide", "f16", 3_000_001, 4915, 32, 6001, 8, 8, 256, 100, slots=2047),
+    ]
+    exhaustive = _search("exhaustive_f16", "wide", "f16", 1_000_003, 1638, 32, 65, 1, 1, 1, 100)
+    exhaustive["kind"] = "exhaustive"
+    pairs = dict(name="pairs_own_widths", kind="pairs", dtype="bf16", N=500_000, d=96, d_user=80, hidden="192,96",
+                 heads=2, clusters=512, R=16, Q=333, M=100_003)
+    return cases + [exhaustive, pairs]
+
+
+def _log_uniform(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def draw(rng):
+    kind = rng.choice(["search", "search", "search", "search", "f32", "ragged", "two_stage", "stream", "exhaustive",
+                       "pairs"])
+    if kind == "f32":  # reference precision: small tables, short and long lists
+        N = _log_uniform(rng, 4_000, 60_000)
+        L = _log_uniform(rng, 16, 4096)
+        c = _search(None, "small", "f32", N, max(4, N // 625), 16, _log_uniform(rng, 1, 256), rng.randint(1, 8),
+                    rng.choice([1, 2, 4, 8, 16]), L, rng.randint(5, 100))
+    elif kind == "pairs":
+        hidden = ",".join(str(8 * rng.randint(4, 40)) for _ in range(rng.randint(1, 3)))
+        return dict(kind="pairs", dtype=rng.choice(["bf16", "f16", "f32"]), N=_log_uniform(rng, 20_000, 1_000_000),
+                    d=8 * rng.randint(3, 20), d_user=8 * rng.randint(3, 20), hidden=hidden, heads=rng.randint(1, 4),
+                    clusters=256, R=16, Q=_log_uniform(rng, 1, 2000), M=_log_uniform(rng, 500, 300_000))
+    elif kind == "exhaustive":
+        metric = rng.choice(["two", "wide", "one"])
+        c = _search(None, metric, rng.choice(["bf16", "f16"]), _log_uniform(rng, 50_000, 1_500_000), 512, 16,
+                    rng.randint(1, 100), 1, 1, 1, rng.randint(10, 300))
+        c["kind"] = "exhaustive"
+    else:
+        metric = rng.choice(["two", "wide", "one"])
+        if kind == "two_stage":
+            metric = rng.choice(["two", "wide"])
+        N = _log_uniform(rng, 200_000, 6_000_000)
+        L = _log_uniform(rng, 32, 4096 if metric == "wide" else 2048)
+        # the wide batch at L = 8,192 bounds the work of a drawn call
+        Q = _log_uniform(rng, 1, min(8192, 4096 * 4096 // L))
+        W = rng.choice([1, 2, 4, 8, 16, 32]) if L >= 64 else rng.choice([1, 2, 4])
+        c = _search(None, metric, rng.choice(["bf16", "f16"]), N, max(16, N // 610), 32, Q, rng.randint(1, 16), W, L,
+                    rng.randint(10, 200), locality=rng.random() < 0.5)
+        if kind == "ragged":
+            c.update(ragged=True, zipf=rng.random() < 0.5, cap=rng.randint(8, 64))
+        elif kind == "two_stage":
+            c.update(dtype="f8", candidates=rng.randint(200, 1024))
+        elif kind == "stream":
+            c.update(slots=max(1, int(c["Q"] * rng.uniform(0.2, 0.9))))
+    del c["name"]
+    return c
+
+
+def _gpu(seed):
+    return torch.Generator(device="cuda").manual_seed(seed)
+
+
+def _items(case, seed, with_graph):
+    """Item table [N][d], and with_graph the adjacency [N][R] and the items' places in cluster order [N]."""
+    N, d, C, R, K = case["N"], case["d"], case["clusters"], case["R"], case["R"] // 2
+    gen, dev, step = _gpu(seed), "cuda", 1 << 20
+    means = torch.randn(C, d, generator=gen, device=dev)
+    if case.get("zipf"):
+        p = torch.arange(1, C + 1, device=dev, dtype=torch.float64).pow(-1.1).cumsum(0)
+        u = torch.rand(N, generator=gen, device=dev, dtype=torch.float64) * p[-1]
+        cluster = torch.searchsorted(p, u).clamp_(max=C - 1)
+    else:
+        cluster = torch.randint(0, C, (N,), generator=gen, device=dev)
+    # positions: by cluster, inside a cluster by the first coordinate of the deviation from its mean
+    first = torch.randn(N, generator=gen, device=dev).clamp_(-8, 8)
+    key, order = torch.sort(cluster.double() * 32 + first)
+    cluster, first = cluster[order], first[order]
+    del key, order
+    perm = torch.randperm(N, generator=gen, device=dev)  # position -> id
+    emb = torch.empty(N, d, dtype=TORCH_TYPE[case["dtype"]], device=dev)
+    for s in range(0, N, step):
+        e = min(N, s + step)
+        x = torch.randn(e - s, d, generator=gen, device=dev)
+        x[:, 0] = first[s:e]
+        emb[perm[s:e]] = (means[cluster[s:e]] + 0.3 * x).to(emb.dtype)
+    if not with_graph:
+        return emb, None, None
+    counts = torch.bincount(cluster, minlength=C)
+    starts = counts.cumsum(0) - counts
+    off = torch.cat([torch.arange(-(K // 2), 0, device=dev), torch.arange(1, K - K // 2 + 1, device=dev)])
+    adj = torch.empty(N, R, dtype=torch.int32, device=dev)
+    for s in range(0, N, step):
+        e = min(N, s + step)
+        cl = cluster[s:e]
+        n, s0 = counts[cl][:, None], starts[cl][:, None]
+        near = s0 + (torch.arange(s, e, device=dev)[:, None] - s0 + off) % n
+        far = torch.randint(0, N, (e - s, R), generator=gen, device=dev)
+        far[:, :K] = torch.where(n > K, near, far[:, :K])
+        adj[perm[s:e]] = perm[far].to(torch.int32)
+    rank = torch.empty(N, dtype=torch.int32, device=dev)
+    rank[perm] = torch.arange(N, device=dev, dtype=torch.int32)
+    return emb, adj, rank
+
+
+def _weights(case, seed):
+    gen = torch.Generator().manual_seed(seed + 1)
+    dims = [case["d_user"] + case["d"]] + [int(h) for h in case["hidden"].split(",")] + [case["heads"]]
+    W = [(torch.randn(o, i, generator=gen) * math.sqrt(2.0 / i)).to(TORCH_TYPE[case["dtype"]])
+         for i, o in zip(dims, dims[1:])]
+    b = [torch.randn(o, generator=gen) * 0.05 for o in dims[1:]]
+    return W, b, torch.tensor(HEAD_WEIGHTS[case["heads"]])
+
+
+def prepare(case, seed):
+    kind, N, Q = case["kind"], case["N"], case["Q"]
+    emb, adj, rank = _items(case, seed, with_graph=kind == "search")
+    if adj is None:  # no call of this kind walks the graph
+        adj = torch.zeros(N, 1, dtype=torch.int32, device="cuda")
+    W, b, head_w = _weights(case, seed)
+    gen = _gpu(seed + 2)
+    st = {"case": case, "users": torch.randn(Q, case["d_user"], generator=gen, device="cuda").to(emb.dtype)}
+    table = ann.ann_quantize_e4m3(emb) if case["dtype"] == "f8" else emb
+    g = st["g"] = ann.ann_graph_load(adj, table)
+    m = st["m"] = ann.ann_mlp_load(W, b, head_w, case["d_user"], ANN_TYPE[case["dtype"]])
+    if case.get("locality"):
+        ann.ann_graph_set_locality(g, rank)
+
+    def buffers(nbytes, rows, cols):
+        return dict(workspace=torch.empty(nbytes, dtype=torch.uint8, device="cuda"),
+                    out_ids=torch.empty(rows, cols, dtype=torch.int32, device="cuda"),
+                    out_scores=torch.empty(rows, cols, dtype=torch.float32, device="cuda"))
+
+    if kind == "pairs":  # every user's own candidates, one group after the other, groups of different sizes
+        M = case["M"]
+        st["q"] = torch.randint(0, Q, (M,), generator=gen, device="cuda").sort().values.to(torch.int32)
+        st["item"] = torch.randint(0, N, (M,), generator=gen, device="cuda").to(torch.int32)
+        st["out"] = torch.empty(M, dtype=torch.float32, device="cuda")
+        return st
+    k = case["k"]
+    if kind == "exhaustive":
+        st["bufs"] = buffers(ann.ann_brute_force_workspace_bytes(g, m, Q, k), Q, k)
+        return st
+    E, wide, L, cap = case["E"], case["W"], case["L"], case.get("cap", 0)
+    st["entries"] = torch.randint(0, N, (Q, E), generator=gen, device="cuda").to(torch.int32)
+    if case.get("ragged"):
+        between = lambda lo, hi: torch.randint(lo, hi + 1, (Q,), generator=gen, device="cuda").to(torch.int32)
+        st["own"] = (between(1, wide), between(min(16, L), L), between(min(8, cap), cap))
+    if case.get("slots"):
+        st["bufs"] = buffers(ann.ann_search_stream_workspace_bytes(g, m, Q, case["slots"], E, wide, L, k), Q, k)
+        return st
+    n = case.get("candidates", k)
+    st["bufs"] = buffers(ann.ann_search_workspace_bytes(g, m, Q, E, wide, L, n, cap), Q, n)
+    if "candidates" in case:
+        st["g16"] = ann.ann_graph_load(adj, emb)
+        st["m16"] = ann.ann_mlp_load(W, b, head_w, case["d_user"], ann.ANN_BF16)
+        kk = min(k, n)
+        st["bufs16"] = buffers(ann.ann_rerank_workspace_bytes(st["g16"], st["m16"], Q, n, kk), Q, kk)
+    return st
+
+
+def run(st):
+    case, g, m, users = st["case"], st["g"], st["m"], st["users"]
+    if case["kind"] == "pairs":
+        return ann.ann_score_pairs(g, m, users, st["q"], st["item"], out=st["out"])
+    if case["kind"] == "exhaustive":
+        return ann.ann_brute_force(g, m, users, case["k"], **st["bufs"])
+    if "own" in st:
+        return ann.ann_search_ragged(g, m, users, st["entries"], *st["own"], case["W"], case["L"], case["k"],
+                                     case["cap"], **st["bufs"])
+    if case.get("slots"):
+        return ann.ann_search_stream(g, m, users, st["entries"], case["slots"], case["W"], case["L"], case["k"],
+                                     **st["bufs"])
+    found = ann.ann_search(g, m, users, st["entries"], case["W"], case["L"], case.get("candidates", case["k"]),
+                           **st["bufs"])
+    if "candidates" in case:
+        return ann.ann_rerank(st["g16"], st["m16"], users, found[0], min(case["k"], case["candidates"]),
+                              **st["bufs16"])
+    return found
+
+
+def _expected_pairs(case):
+    """(nodes expanded, pairs scored) per user.  Measured on these graphs: a converged search expands 1.05 to 1.8
+    times as many nodes as its list has entries (most with short lists), and 0.55 to 0.65 of an expanded node's
+    neighbours are new to the user."""
+    L, W, R, N = case["L"], case["W"], case["R"], case["N"]
+    if case.get("ragged"):  # means over uniform widths, lists and limits
+        L, W = (min(16, L) + L) / 2, (1 + W) / 2
+        expanded = min(L, W * (min(8, case["cap"]) + case["cap"]) / 2)
+    else:
+        expanded = 1.2 * L
+    expanded = min(expanded, N)
+    return expanded, min(case["E"] + 0.58 * expanded * R, N)
+
+
+def work(case):
+    d, N, Q, size = case["d"], case["N"], case["Q"], ITEM_BYTES[case["dtype"]]
+    dims = [int(h) for h in case["hidden"].split(",")] + [case["heads"]]
+    rest = sum(a * b for a, b in zip(dims, dims[1:]))
+    per_pair = 2 * (d * dims[0] + rest)          # the item's half of layer 1 and the layers behind it
+    user_terms = 2 * Q * case["d_user"] * dims[0]
+    user_bytes = Q * case["d_user"] * (4 if case["dtype"] == "f32" else 2)
+    if case["kind"] == "pairs":
+        pairs, nodes, out = case["M"], 0, 4 * case["M"] + 8 * case["M"]
+    elif case["kind"] == "exhaustive":
+        pairs, nodes, out = Q * N, 0, 8 * Q * case["k"]
+    else:
+        nodes, pairs = (Q * x for x in _expected_pairs(case))
+        out = 8 * Q * case["k"] + 4 * Q * case["E"]
+    rows = min(pairs, N) * d * size + min(nodes, N) * case["R"] * 4   # a row that many users meet: once
+    extra = 0
+    if "candidates" in case:                     # the second stage: candidates under the 16-bit metric
+        extra = Q * case["candidates"]
+        rows += min(extra, N) * d * 2
+    return {"bytes": float(rows + out + user_bytes), "flops": float((pairs + extra) * per_pair + user_terms)}
+
+
+def tolerance(case):
+    if case["dtype"] == "f32":
+        # sums in 64 bits, one rounding to 32: 6e-8 relative; ids can differ only between equal scores
+        return {"rel": 1e-6, "max": 1e-5, "differ": 0.005}
+    # 16- and 8-bit operands, 32-bit sums: the order of a sum moves a hidden unit across a rounding boundary now
+    # and then, and neighbours in a list whose scores are that close change places.  Four times what the matrix
+    # kernels and the plain ones differ by on these cases (rel 4.6e-4, max 1.5e-2; ids of a list: 0.3 to 2.8 %)
+    return {"rel": 2e-3, "max": 6e-2, "differ": 0.01}
