@@ -133,7 +133,8 @@ int ann_mlp_load(int32_t n_layers, const int32_t *dims_host, const void *const *
                  int32_t dtype, uint32_t flags, void *stream, ann_mlp **out);
 void ann_mlp_free(ann_mlp *m);
 
-/* 1 if searches with this metric run the MFMA kernels, 0 if the plain ALU kernels. */
+/* 1 if the metric has one of the shapes with MFMA kernels of their own, 0 if its widths are served by the kernels
+ * for any widths (matrix cores as well, or the plain ALUs: ANN_MLP_GENERIC and very wide layers). */
 int ann_mlp_uses_mfma(const ann_mlp *m);
 
 /*

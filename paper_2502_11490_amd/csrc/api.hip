@@ -665,6 +665,9 @@ int ann_mlp_load(int32_t n_layers, const int32_t *dims_host, const void *const *
         rc = build_mfma_fragments(m, W_host, s);
         if (rc != ANN_OK) return fail(rc);
         m->kernel = MLP_MFMA2;
+    } else if (!(flags & ANN_MLP_GENERIC)) {
+        rc = build_any_fragments(m, W_host, s);
+        if (rc != ANN_OK) return fail(rc);
     }
     *out = m;
     return ANN_OK;
@@ -676,6 +679,7 @@ void ann_mlp_free(ann_mlp *m) {
     if (m->b_dev) (void)hipFree(m->b_dev);
     if (m->head_w_dev) (void)hipFree(m->head_w_dev);
     if (m->frag_dev) (void)hipFree(m->frag_dev);
+    if (m->any_dev) (void)hipFree(m->any_dev);
     delete m;
 }
 

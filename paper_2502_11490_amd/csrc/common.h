@@ -51,6 +51,19 @@ __device__ __forceinline__ float sigmoid_hw(float z) {
     return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * z));
 }
 
+// Layers of a metric as mlp_tile.h walks them: fragments of 1 KB, counts in units of the matrix instruction.
+struct TileNet {
+    int32_t n_layers, J, d_user, d_item;
+    int32_t KS[MAX_LAYERS];        // inputs, in 16s
+    int32_t NB[MAX_LAYERS];        // blocks of output units (32; fp32 metrics: 16)
+    int32_t stride_n[MAX_LAYERS];  // fragments from a block to the next one
+    int32_t step2[MAX_LAYERS];     // fragments from a pair of inputs-of-16 to the next pair
+    int32_t b_off[MAX_LAYERS];     // bias
+    int32_t slabs[2];              // most inputs-of-16 of the even layers, of the odd layers
+    int64_t base[MAX_LAYERS];      // first fragment
+    float head_w[MAX_HEADS];
+};
+
 }  // namespace gmpgr
 
 struct ann_graph {
@@ -65,7 +78,7 @@ struct ann_graph {
 };
 
 // Which fused kernel serves the metric.
-enum MlpKernel { MLP_ALU = 0, MLP_MFMA2 = 1 /* the bf16 MFMA kernels: one or two hidden layers */ };
+enum MlpKernel { MLP_ALU = 0 /* any widths: mlp_any.hip, mlp_alu.hip */, MLP_MFMA2 = 1 /* a built-in shape's MFMA kernel */ };
 
 struct ann_mlp {
     int32_t n_layers;
@@ -82,6 +95,9 @@ struct ann_mlp {
     // MFMA path: fragment-ordered bf16 copies (see mlp_mfma.hip)
     void *frag_dev;        // W1 item half, W2, W_last (padded to 32 rows), in fragment order
     int64_t frag_bytes;
+    // widths of the caller's own, fp32 metrics: fragment-ordered copies (see mlp_any.hip), null = vector-ALU kernel
+    void *any_dev;
+    gmpgr::TileNet any;
     int device;
 };
 
@@ -177,6 +193,12 @@ int launch_quantize_e4m3(const void *in, int dtype, int64_t n, float scale, uint
 int launch_mlp_alu(const ann_graph *g, const ann_mlp *m, const void *queries, const int32_t *pair_q,
                    const int32_t *pair_id, const int32_t *M_dev, int64_t M_max, int32_t Q, float *scores,
                    int32_t tile_rows, hipStream_t stream);
+// mlp_any.hip: the same on the matrix cores, where the metric has fragments (any_dev)
+bool any_supported(const ann_mlp *m);
+int build_any_fragments(ann_mlp *m, const void *const *W_host, hipStream_t stream);
+int launch_mlp_any(const ann_graph *g, const ann_mlp *m, const void *queries, const int32_t *pair_q,
+                   const int32_t *pair_id, const int32_t *M_dev, int64_t M_max, int32_t Q, float *scores,
+                   hipStream_t stream);
 int launch_user_pre(const ann_mlp *m, const void *queries, int32_t Q, float *upre, hipStream_t stream);
 int launch_mlp_mfma(const ann_graph *g, const ann_mlp *m, const float *upre, const int32_t *pair_q,
                     const int32_t *pair_id, const int32_t *M_dev, int64_t M_max, int32_t Q, float *scores,

@@ -1,9 +1,9 @@
 // Relevance metric of Sec. 3.1 (1), Eq. 5-8, on the vector ALUs (fp32 FMA).
 //
-// This is the path for fp32 metrics and the fallback for 16-bit metrics whose shape the MFMA
-// kernels do not cover.  A workgroup takes one batch of T pairs from the dense pair list
-// (the fixed-size batch of Algorithm 2), keeps the activations of the whole batch in LDS and
-// walks the layers; a thread owns one pair and a strided set of output units, so a weight is
+// This is the path for metrics loaded with ANN_MLP_GENERIC and for layers too wide for the matrix-core
+// kernels (mlp_any.hip: activations of 32 pairs, fp32 16, in LDS).
+// A workgroup takes one batch of T pairs from the dense pair list (the fixed-size batch of
+// Algorithm 2), keeps the activations of the whole batch in LDS and walks the layers; a thread owns one pair and a strided set of output units, so a weight is
 // read once per wave (all lanes of a wave share the output unit) and the activations are
 // read from LDS with an odd row stride (no bank conflicts).
 //
@@ -140,6 +140,7 @@ int launch_mlp_alu(const ann_graph *g, const ann_mlp *m, const void *queries, co
                    const int32_t *pair_id, const int32_t *M_dev, int64_t M_max, int32_t Q, float *scores,
                    int32_t tile_rows, hipStream_t stream) {
     if (M_max <= 0) return ANN_OK;
+    if (any_supported(m)) return launch_mlp_any(g, m, queries, pair_q, pair_id, M_dev, M_max, Q, scores, stream);
     AluMlpParams P;
     P.n_layers = m->n_layers;
     int maxw = 0;
