@@ -280,16 +280,29 @@ static int score_batch(const SearchArgs &a) {
                           (float *)(a.ws + p.off_scores), 0, a.stream);
 }
 
+static const char NO_PROGRESS[] = "no progress report from the search's kernels within the time limit (ann_set_progress_timeout)";
+static const char RAN_DRY[] = "the stream failed or ran dry without the search's progress report";
+
+// Waits for the search and reports queries that stopped because their visited table was full.
+static int report_overflow(const SearchArgs &a) {
+    const Plan &p = a.plan;
+    int64_t stats[8];
+    ANN_HIP_TRY(hipMemcpyAsync(stats, a.ws + p.off_stats, sizeof(stats), hipMemcpyDeviceToHost, a.stream));
+    ANN_HIP_TRY(hipStreamSynchronize(a.stream));
+    if (stats[3] > 0) {
+        set_error("%lld queries filled their visited table (sized for %d rounds) and stopped early",
+                  (long long)stats[3], p.rounds_assumed);
+        return ANN_EWORKSPACE;
+    }
+    return ANN_OK;
+}
+
 static int run_search(SearchArgs &a) {
     const Plan &p = a.plan;
     int rc;
     if (p.Q == 0) return ANN_OK;
     if (a.m->kernel == MLP_MFMA2)
         if ((rc = launch_user_pre(a.m, a.queries, p.Q, (float *)(a.ws + p.off_upre), a.stream)) != ANN_OK) return rc;
-    {
-        StageTimer timer(ANN_STAGE_ROUND, a.stream);
-        if ((rc = launch_init(a)) != ANN_OK) return rc;
-    }
     const bool capped = p.max_iters_max > 0;
     Mailbox *box = nullptr;
     if (!capped) {
@@ -301,18 +314,32 @@ static int run_search(SearchArgs &a) {
         a.mailbox = box->dev;
         a.mail_tag = box->new_tag();
     }
-    bool overflow_seen = false;
     // a query expands only ids it has scored, so it cannot run more rounds than its visited
     // table holds ids: the loop is bounded even if no query ever reported convergence
     const int64_t round_limit = capped ? (int64_t)p.max_iters_max
                                        : (p.bitmap_words > 0 ? a.g->N : (int64_t)p.hash_cap / 2) + 1;
+    // stage times are those of the separate kernels: a profiled search runs them
+    const bool fused = !g_prof.on && fused_serves(a);
+    if (fused) {
+        if ((rc = launch_fused(a, (int32_t)(round_limit < 0x7ffffffe ? round_limit : 0x7ffffffe))) != ANN_OK) return rc;
+        if (capped) return ANN_OK;
+        const int g = box->gate(a.mail_tag, INT64_MAX, a.stream);
+        if (g < 0) {
+            set_error(g == -3 ? NO_PROGRESS : RAN_DRY);
+            return ANN_EDEVICE;
+        }
+        return report_overflow(a);
+    }
+    {
+        StageTimer timer(ANN_STAGE_ROUND, a.stream);
+        if ((rc = launch_init(a)) != ANN_OK) return rc;
+    }
     for (int64_t i = 0; i <= round_limit; ++i) {
         if (box) {  // no query is running: nothing left to score or merge
             const int g = box->gate(a.mail_tag, i, a.stream);
             if (g > 0) break;
             if (g < 0) {
-                set_error(g == -3 ? "no progress report from the search's kernels within the time limit (ann_set_progress_timeout)"
-                                  : "the stream failed or ran dry without the search's progress report");
+                set_error(g == -3 ? NO_PROGRESS : RAN_DRY);
                 return ANN_EDEVICE;
             }
         }
@@ -328,18 +355,7 @@ static int run_search(SearchArgs &a) {
         }
     }
     if ((rc = launch_emit(a)) != ANN_OK) return rc;
-    if (!capped) {
-        int64_t stats[8];
-        ANN_HIP_TRY(hipMemcpyAsync(stats, a.ws + p.off_stats, sizeof(stats), hipMemcpyDeviceToHost, a.stream));
-        ANN_HIP_TRY(hipStreamSynchronize(a.stream));
-        overflow_seen = stats[3] > 0;
-        if (overflow_seen) {
-            set_error("%lld queries filled their visited table (sized for %d rounds) and stopped early",
-                      (long long)stats[3], p.rounds_assumed);
-            return ANN_EWORKSPACE;
-        }
-    }
-    return ANN_OK;
+    return capped ? ANN_OK : report_overflow(a);
 }
 
 // Continuous batching: a.Q_total queries stream through a.plan.Q slots.  Every round starts with
@@ -369,8 +385,7 @@ static int run_stream(SearchArgs &a) {
             const int g = box->gate(a.mail_tag, i, a.stream);
             if (g > 0) break;
             if (g < 0) {
-                set_error(g == -3 ? "no progress report from the search's kernels within the time limit (ann_set_progress_timeout)"
-                                  : "the stream failed or ran dry without the search's progress report");
+                set_error(g == -3 ? NO_PROGRESS : RAN_DRY);
                 return ANN_EDEVICE;
             }
         }
@@ -389,15 +404,7 @@ static int run_stream(SearchArgs &a) {
             if ((rc = launch_round(a)) != ANN_OK) return rc;
         }
     }
-    int64_t stats[8];
-    ANN_HIP_TRY(hipMemcpyAsync(stats, a.ws + p.off_stats, sizeof(stats), hipMemcpyDeviceToHost, a.stream));
-    ANN_HIP_TRY(hipStreamSynchronize(a.stream));
-    if (stats[3] > 0) {
-        set_error("%lld queries filled their visited table (sized for %d rounds) and stopped early",
-                  (long long)stats[3], p.rounds_assumed);
-        return ANN_EWORKSPACE;
-    }
-    return ANN_OK;
+    return report_overflow(a);
 }
 
 }  // namespace gmpgr

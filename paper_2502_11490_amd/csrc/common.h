@@ -169,6 +169,7 @@ struct SearchArgs {
 };
 
 // search_kernels.hip
+int launch_zero_stats(const SearchArgs &a);
 int launch_init(const SearchArgs &a);
 int launch_scan_compact(const SearchArgs &a);
 int launch_round(const SearchArgs &a);
@@ -176,6 +177,11 @@ int launch_emit(const SearchArgs &a);
 int launch_stream_reset(const SearchArgs &a);
 int launch_admit(const SearchArgs &a);
 int launch_stream_publish(const SearchArgs &a, int avail);
+
+// search_fused.hip: all rounds of a small batch's queries in one launch
+constexpr size_t FUSED_LDS = 150 * 1024;
+bool fused_serves(const SearchArgs &a);
+int launch_fused(const SearchArgs &a, int32_t rounds_max);
 
 // noise.hip: out = users + sigma * N(0, I), element-indexed counter-based draw (Eq. 5)
 int launch_users_add_noise(const void *users, void *out, int64_t n_elem, int dtype, double sigma, uint64_t seed,

@@ -52,40 +52,40 @@ __device__ __forceinline__ uint4 tile_relu(const f32x16 &acc, int half) {
 }
 
 // acc[c] += W-block * slabs of column block c, over KS inputs-of-16.  `w` points at this lane's 16 bytes of the
-// block's first fragment; fragment k lies (k >> 1) * step2 + (k & 1) fragments behind it (KS is even).  Four
+// block's first fragment; fragment k lies (k >> 1) * step2 + (k & 1) fragments behind it (KS is even).  DEPTH
 // fragments are in flight.
-template <bool F16, int CB>
+template <bool F16, int CB, int DEPTH = 4>
 __device__ __forceinline__ void tile_contract(f32x16 (&acc)[CB], const uint4 *__restrict__ w, int step2, int KS,
                                               const uint4 *in, int in_slabs) {
     const int lane = threadIdx.x & 63;
-    uint4 a[4];
+    uint4 a[DEPTH];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int k = u < KS ? u : 0;
+    for (int u = 0; u < DEPTH; ++u) {
+        const int k = u < KS ? u : KS - 1;
         a[u] = w[((size_t)(k >> 1) * step2 + (k & 1)) * 64];
     }
-    for (int k0 = 0; k0 < KS; k0 += 4) {
-        uint4 n[4];
+    int k0 = 0;
+    for (; k0 + DEPTH < KS; k0 += DEPTH) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int k = k0 + 4 + u < KS ? k0 + 4 + u : 0;  // past the end: a fragment nobody uses
-            n[u] = w[((size_t)(k >> 1) * step2 + (k & 1)) * 64];
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            if (u >= 2 && k0 + u >= KS) break;  // KS is even
+        for (int u = 0; u < DEPTH; ++u) {
 #pragma unroll
             for (int c = 0; c < CB; ++c) acc[c] = tile_mfma<F16>(a[u], in[((size_t)c * in_slabs + k0 + u) * 64 + lane], acc[c]);
+            const int k = k0 + DEPTH + u < KS ? k0 + DEPTH + u : KS - 1;  // past the end: one that nobody uses
+            a[u] = w[((size_t)(k >> 1) * step2 + (k & 1)) * 64];
         }
+    }
 #pragma unroll
-        for (int u = 0; u < 4; ++u) a[u] = n[u];
+    for (int u = 0; u < DEPTH; ++u) {
+        if (u >= 2 && k0 + u >= KS) break;  // KS is even and at least 2
+#pragma unroll
+        for (int c = 0; c < CB; ++c) acc[c] = tile_mfma<F16>(a[u], in[((size_t)c * in_slabs + k0 + u) * 64 + lane], acc[c]);
     }
 }
 
 // A hidden layer of the tile: NB blocks of 32 units over the workgroup's waves.  init[unit]: what a unit's sum starts
 // from.  out: 2 NB slabs per column block, unit 32 nb + 16 s2 + 8 (j / 4) + 4 g + j % 4 at byte j of lane (m, g) of
 // slab 2 nb + s2 (the D layout of the instruction as it comes; the next layer's weights are stored to match).
-template <bool F16, bool INT_RELU, int CB>
+template <bool F16, bool INT_RELU, int CB, int DEPTH = 4>
 __device__ __forceinline__ void tile_hidden(const uint4 *__restrict__ frag, int64_t base, int stride_n, int step2, int KS,
                                             int NB, const float *init, const uint4 *in, int in_slabs, uint4 *out,
                                             int out_slabs, int n_waves) {
@@ -100,7 +100,7 @@ __device__ __forceinline__ void tile_hidden(const uint4 *__restrict__ frag, int6
 #pragma unroll
                 for (int e = 0; e < 4; ++e) acc[c][4 * t4 + e] = v[e];
         }
-        tile_contract<F16, CB>(acc, frag + (base + (int64_t)nb * stride_n) * 64 + lane, step2, KS, in, in_slabs);
+        tile_contract<F16, CB, DEPTH>(acc, frag + (base + (int64_t)nb * stride_n) * 64 + lane, step2, KS, in, in_slabs);
 #pragma unroll
         for (int c = 0; c < CB; ++c) {
             out[((size_t)c * out_slabs + 2 * nb) * 64 + lane] = tile_relu<F16, INT_RELU>(acc[c], 0);

@@ -1,0 +1,502 @@
+// A whole search in one launch: one workgroup per query runs every round of the joint best-first search (Sec. 3.2,
+// Algorithm 1), scoring included, without going back to the host or to another workgroup.
+//
+// The batch path spends three dependent launches per round, which is right while a round's pairs fill the chip
+// with matrix work.  A small batch does not: its rounds are chains of trips to memory, launch turn-overs and (for the
+// kernels that keep all weights in LDS) a reload of the weights.  Here the list, the survivors and their scores stay
+// in LDS from the first round to the last, the user's share of layer 1 is the same for all pairs of the workgroup,
+// the weights come from L2 in fragment order (mlp_tile.h), and queries do not wait for one another.
+//
+// What bounds it: the chain of a round (adjacency row, visited words, item rows, weights: five trips to memory or L2
+// and about twenty barriers), hidden only by the other workgroups of the CU.  The weights are read once per tile of
+// pairs and query, so a full batch belongs to the batch path; fused_plan has the line and both sides.
+//
+// Measured against the batch path: one query on a million items (lists of 64) 0.88 -> 0.46 ms, 64 fp32 queries with
+// lists of 32 and 4,096 0.78 -> 0.33 and 7.9 -> 4.2 ms, 1,024 queries with lists of 512 8.4 -> 6.1 ms.
+//
+// A pair's relevance is computed in the order of the batch path's kernels (same fragments, same sequence of MFMAs,
+// same start values), so which path serves a call does not show in its results.
+#include "mlp_tile.h"
+#include "search_device.h"
+
+namespace gmpgr {
+
+struct FusedArgs {
+    TileNet T;
+    const void *frag;
+    const float *b, *upre;      // upre: the users' shares of layer 1 [Q][H1], null = layer 1 contracts the user too
+    const void *emb, *users;
+    const int32_t *adj, *adj_rank, *rank, *entries;
+    const int32_t *W_q, *L_q, *cap_q;
+    uint32_t *table;
+    int64_t *stats;
+    Ctrl *ctrl;
+    int32_t *out_ids;
+    float *out_scores;
+    uint64_t *mailbox;
+    uint64_t mail_tag;
+    int64_t N;
+    int32_t R, E, W, L, cap, W_max, L_max, cap_max, C, k, slots, new_cap, chunk, table_words, hash_cap, Q, rounds_max;
+    int32_t wide_loads, int_relu;
+};
+
+enum { FUSED_F64 = 0, FUSED_BF16 = 1, FUSED_F16 = 2 };
+
+// Relevances of the query's pairs surv[0..n) to sc[0..n).  All threads call; ends with a barrier.
+template <int BLK, bool F16, int CB>
+__device__ __forceinline__ void fused_score16(const FusedArgs &A, int q, const int32_t *surv, float *sc, int n, uint4 *buf0) {
+    constexpr int P = 32 * CB, NW = BLK / 64;
+    const TileNet &T = A.T;
+    uint4 *buf1 = buf0 + (size_t)CB * T.slabs[0] * 64;
+    const uint4 *frag = (const uint4 *)A.frag;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g = lane >> 5, col = lane & 31;
+    const float *upre = A.upre ? A.upre + (size_t)q * (32 * T.NB[0]) : nullptr;
+    const int n_user = A.upre ? 0 : T.d_user, n_in = n_user + T.d_item, last = T.n_layers - 1;
+    const uint16_t *u = (const uint16_t *)A.users + (size_t)q * T.d_user;
+    for (int base = 0; base < n; base += P) {
+        for (int i = wave; i < CB * T.KS[0]; i += NW) {
+            const int c = i % CB, s = i / CB, k0 = 16 * s + 8 * g, row = base + c * 32 + col;
+            uint4 x = make_uint4(0, 0, 0, 0);
+            if (row < n) {
+                const uint16_t *e = (const uint16_t *)A.emb + (size_t)surv[row] * T.d_item;
+                if (A.wide_loads) {
+                    if (k0 < n_user) x = *(const uint4 *)(u + k0);
+                    else if (k0 < n_in) x = *(const uint4 *)(e + (k0 - n_user));
+                } else {
+                    uint32_t h[8];
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) {
+                        const int kk = k0 + j;
+                        h[j] = kk < n_user ? u[kk] : kk < n_in ? e[kk - n_user] : 0;
+                    }
+                    x = make_uint4(h[0] | h[1] << 16, h[2] | h[3] << 16, h[4] | h[5] << 16, h[6] | h[7] << 16);
+                }
+            }
+            buf0[((size_t)c * T.slabs[0] + s) * 64 + lane] = x;
+        }
+        __syncthreads();
+        for (int l = 0; l < last; ++l) {
+            const float *init = l == 0 && upre ? upre : A.b + T.b_off[l];
+            uint4 *in = l & 1 ? buf1 : buf0, *out = l & 1 ? buf0 : buf1;
+            if (A.int_relu)
+                tile_hidden<F16, true, CB>(frag, T.base[l], T.stride_n[l], T.step2[l], T.KS[l], T.NB[l], init, in,
+                                           T.slabs[l & 1], out, T.slabs[1 - (l & 1)], NW);
+            else
+                tile_hidden<F16, false, CB>(frag, T.base[l], T.stride_n[l], T.step2[l], T.KS[l], T.NB[l], init, in,
+                                            T.slabs[l & 1], out, T.slabs[1 - (l & 1)], NW);
+            __syncthreads();
+        }
+        if (wave < CB) {  // heads: one block of units, one wave per 32 pairs
+            f32x16 z[1];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) z[0][i] = 0.f;
+            const uint4 *in = (last & 1 ? buf1 : buf0) + (size_t)wave * T.slabs[last & 1] * 64;
+            tile_contract<F16, 1>(z, frag + T.base[last] * 64 + lane, T.step2[last], T.KS[last], in, T.slabs[last & 1]);
+            float part = 0.f;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int j = 4 * g + i;
+                const float bias = j < T.J ? A.b[T.b_off[last] + j] : 0.f, w = j < T.J ? T.head_w[j] : 0.f;
+                if (upre) part = fmaf(w, sigmoid_hw(z[0][i] + bias), part);
+                else if (j < T.J) part += w * (1.0f / (1.0f + expf(-(z[0][i] + bias))));
+            }
+            const float other = __shfl_xor(part, 32);
+            const int row = base + wave * 32 + col;
+            if (g == 0 && row < n) sc[row] = part + other;
+        }
+        __syncthreads();
+    }
+}
+
+template <int BLK, int CB>
+__device__ __forceinline__ void fused_score64(const FusedArgs &A, int q, const int32_t *surv, float *sc, int n, f64x2 *buf0) {
+    constexpr int P = 16 * CB, NW = BLK / 64;
+    const TileNet &T = A.T;
+    f64x2 *buf1 = buf0 + (size_t)CB * T.slabs[0] * 128;
+    const float4 *frag = (const float4 *)A.frag;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g = lane >> 4, col = lane & 15, last = T.n_layers - 1;
+    const float *u = (const float *)A.users + (size_t)q * T.d_user;
+    for (int base = 0; base < n; base += P) {
+        for (int i = wave; i < CB * T.KS[0]; i += NW) {
+            const int c = i % CB, s = i / CB, row = base + c * 16 + col;
+            f64x2 lo = {0.0, 0.0}, hi = {0.0, 0.0};
+            if (row < n) {
+                const float *e = (const float *)A.emb + (size_t)surv[row] * T.d_item;
+                float x[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int kk = 16 * s + 4 * j + g;
+                    x[j] = kk < T.d_user ? u[kk] : kk < T.d_user + T.d_item ? e[kk - T.d_user] : 0.f;
+                }
+                lo[0] = x[0], lo[1] = x[1], hi[0] = x[2], hi[1] = x[3];
+            }
+            f64x2 *to = buf0 + ((size_t)c * T.slabs[0] + s) * 128 + lane;
+            to[0] = lo;
+            to[64] = hi;
+        }
+        __syncthreads();
+        for (int l = 0; l < last; ++l) {
+            tile_hidden64<CB>(frag, T.base[l], T.KS[l], T.NB[l], A.b + T.b_off[l], l & 1 ? buf1 : buf0, T.slabs[l & 1],
+                              l & 1 ? buf0 : buf1, T.slabs[1 - (l & 1)], NW);
+            __syncthreads();
+        }
+        for (int c = wave; c < CB; c += NW) {
+            f64x4 z[1] = {{0.0, 0.0, 0.0, 0.0}};
+            tile_contract64<1>(z, frag + T.base[last] * 64 + lane, T.KS[last],
+                               (last & 1 ? buf1 : buf0) + (size_t)c * T.slabs[last & 1] * 128, T.slabs[last & 1]);
+            double part = 0.0;  // heads g and g + 4
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const int j = g + 4 * i;
+                if (j < T.J) part += (double)T.head_w[j] * (1.0 / (1.0 + exp(-(z[0][i] + (double)A.b[T.b_off[last] + j]))));
+            }
+            part += __shfl_xor(part, 16);
+            part += __shfl_xor(part, 32);
+            const int row = base + c * 16 + col;
+            if (g == 0 && row < n) sc[row] = (float)part;
+        }
+        __syncthreads();
+    }
+}
+
+// LDS, in bytes: the list twice, the survivors' ids and scores, the parents, the small words, and one region used in
+// turn by the filter, the scoring and the sort.
+struct FusedLds {
+    size_t surv, sc, parents, small, scratch;
+};
+__host__ __device__ inline size_t up16(size_t v) { return (v + 15) & ~(size_t)15; }
+static inline int fused_dd(int chunk) {
+    int dd_n = 2;
+    while (dd_n < 2 * chunk) dd_n <<= 1;
+    return dd_n;
+}
+__host__ __device__ inline void fused_lds(int C, int slots, int W_max, FusedLds *o) {
+    o->surv = up16((size_t)16 * C);
+    o->sc = up16(o->surv + (size_t)4 * slots);
+    o->parents = up16(o->sc + (size_t)4 * slots);
+    o->small = up16(o->parents + (size_t)4 * W_max);
+    o->scratch = up16(o->small + 32 * 4);
+}
+
+template <int BLK, bool BITMAP, int METRIC, int CB>
+__global__ void __launch_bounds__(BLK) fused_search_kernel(FusedArgs A) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int q = blockIdx.x, tid = threadIdx.x;
+    FusedLds at;
+    fused_lds(A.C, A.slots, A.W_max, &at);
+    uint64_t *cur = (uint64_t *)smem, *oth = cur + A.C;
+    int32_t *surv = (int32_t *)(smem + at.surv);
+    float *sc = (float *)(smem + at.sc);
+    int32_t *parents = (int32_t *)(smem + at.parents);
+    int *wave_sums = (int *)(smem + at.small), *shared_i = wave_sums + 16;
+    unsigned char *scratch = smem + at.scratch;
+    // the scratch region in its three roles
+    int32_t *cand = (int32_t *)scratch;
+    int32_t *cand_rank = (BITMAP && A.adj_rank) ? cand + ((A.chunk + 3) & ~3) : nullptr;
+    uint32_t *dd_key = (uint32_t *)(cand + (cand_rank ? 2 : 1) * ((A.chunk + 3) & ~3));
+    int dd_n = 2;
+    while (dd_n < 2 * A.chunk) dd_n <<= 1;
+    uint32_t *dd_pos = dd_key + dd_n, *bk_key = dd_pos + dd_n, *bk_cnt = bk_key + dd_n;
+    uint64_t *newk = (uint64_t *)scratch;
+    uint32_t *sort_cnt = (uint32_t *)(newk + A.new_cap);
+
+    const int W = min(max(A.W_q ? A.W_q[q] : A.W, 1), A.W_max), L = min(max(A.L_q ? A.L_q[q] : A.L, 1), A.L_max);
+    const int c_own = A.cap_q ? A.cap_q[q] : A.cap;
+    const int cap = A.cap_max > 0 ? min(max(c_own, 1), A.cap_max) : max(c_own, 0);
+    uint32_t *table = A.table + (size_t)q * A.table_words;
+    {
+        const uint32_t e = BITMAP ? 0u : EMPTY_SLOT;
+        for (int i = tid; i < A.table_words / 4; i += BLK) ((uint4 *)table)[i] = make_uint4(e, e, e, e);
+        __threadfence_block();
+        __syncthreads();
+    }
+    int n_list = 0, n_visited = 0, n_expanded = 0, first_open = 0, t = 0, n_cand = A.E;
+    bool seeding = true, overflow = false;
+    // bounded: a search cannot run more rounds than its cap or than ids fit its visited set
+    for (int round = 0; round <= A.rounds_max; ++round) {
+        // candidates (the seeds, later one adjacency row per parent) through the visited filter, piece by piece
+        int n_new = 0;
+        for (int c0 = 0; c0 < n_cand; c0 += A.chunk) {
+            const int nc = min(A.chunk, n_cand - c0);
+            if (c0 > 0) {  // the table stores of the piece before must be seen by this piece's reads
+                __threadfence_block();
+                __syncthreads();
+            }
+            for (int j = tid; j < nc; j += BLK) {
+                if (seeding) {
+                    const int32_t v = A.entries[(size_t)q * A.E + c0 + j];
+                    cand[j] = v;
+                    if (BITMAP && cand_rank) cand_rank[j] = (v >= 0 && (int64_t)v < A.N) ? A.rank[v] : -1;
+                } else {
+                    const int p = (c0 + j) / A.R, s = (c0 + j) - p * A.R;
+                    const size_t from = (size_t)parents[p] * A.R + s;
+                    cand[j] = A.adj[from];
+                    if (BITMAP && cand_rank) cand_rank[j] = A.adj_rank[from];
+                }
+            }
+            __syncthreads();
+            if (BITMAP)
+                n_new += filter_and_mark<BLK>(cand, cand_rank, nc, dd_key, dd_pos, bk_key, bk_cnt, dd_n, table, A.N,
+                                              surv + n_new, wave_sums, nullptr, 1, 0);
+            else
+                n_new += filter_and_insert<BLK>(cand, nc, dd_key, dd_pos, bk_key, bk_cnt, dd_n, table, A.hash_cap, A.N,
+                                                surv + n_new, wave_sums, nullptr, 1);
+        }
+        n_visited += n_new;
+        __threadfence_block();  // the table's stores, for the next round's reads
+        if (tid == 0) shared_i[0] = 0x7fffffff;  // rank of the first inserted entry
+        __syncthreads();
+
+        if constexpr (METRIC == FUSED_F64) fused_score64<BLK, CB>(A, q, surv, sc, n_new, (f64x2 *)scratch);
+        else fused_score16<BLK, METRIC == FUSED_F16, CB>(A, q, surv, sc, n_new, (uint4 *)scratch);
+
+        // merge: what can enter the list, sorted, by rank into the list's other copy
+        const uint64_t worst = n_list == A.C ? cur[A.C - 1] : KEY_SENTINEL;
+        int m = 0;
+        for (int j0 = 0; j0 < n_new; j0 += BLK) {
+            const int j = j0 + tid;
+            uint64_t key = KEY_SENTINEL;
+            if (j < n_new) key = make_key(sc[j], surv[j], 0u);
+            const bool keep = j < n_new && key < worst;
+            int tot;
+            const int pos = block_excl_count<BLK>(keep, wave_sums, &tot);
+            if (keep) newk[m + pos] = key;
+            m += tot;
+        }
+        if (m > 0) {
+            if (m <= BLK) {
+                rank_sort<BLK>(newk, m, sort_cnt);
+            } else {
+                int m2 = 2;
+                while (m2 < m) m2 <<= 1;
+                for (int i = m + tid; i < m2; i += BLK) newk[i] = KEY_SENTINEL;
+                __syncthreads();
+                bitonic_sort<BLK>(newk, m2);
+            }
+            for (int i = tid; i < n_list + m; i += BLK) {
+                uint64_t key;
+                int pos;
+                if (i < n_list) {
+                    key = cur[i];
+                    pos = i + lower_bound_keys(newk, m, key);
+                } else {
+                    key = newk[i - n_list];
+                    pos = (i - n_list) + lower_bound_keys(cur, n_list, key);
+                    if (i == n_list) shared_i[0] = pos;
+                }
+                if (pos < A.C) oth[pos] = key;
+            }
+            n_list = min(A.C, n_list + m);
+            uint64_t *x = cur;
+            cur = oth;
+            oth = x;
+        }
+        __syncthreads();
+
+        // termination test and choice of the parents: the first <= W unexpanded entries among the first L ranks
+        first_open = min(first_open, shared_i[0]);
+        int n_par = 0;
+        if (!(cap > 0 && t >= cap)) {
+            const int lim = min(L, n_list);
+            int i0 = first_open;
+            bool filled = false;
+            while (i0 < lim && !filled) {
+                const int i = i0 + tid;
+                const uint64_t e = i < lim ? cur[i] : KEY_SENTINEL;
+                const bool open = i < lim && !key_expanded(e);
+                int tot;
+                const int pos = block_excl_count<BLK>(open, wave_sums, &tot);
+                if (open && n_par + pos < W) {
+                    parents[n_par + pos] = key_id(e);
+                    cur[i] = e | 1ull;
+                    if (n_par + pos == W - 1) shared_i[1] = i + 1;  // everything in front of it is expanded now
+                }
+                filled = n_par + tot >= W;
+                n_par = min(W, n_par + tot);
+                i0 += BLK;
+                first_open = min(i0, lim);
+            }
+            __syncthreads();
+            if (filled) first_open = shared_i[1];
+        }
+        if (!BITMAP && n_par > 0 && (int64_t)n_visited + (int64_t)n_par * A.R > (int64_t)(A.hash_cap / 2)) {
+            overflow = true;
+            n_par = 0;
+        }
+        if (n_par == 0) break;
+        ++t;
+        n_expanded += n_par;
+        n_cand = n_par * A.R;
+        seeding = false;
+        if (A.mailbox && tid == 0 && (t & 63) == 0)  // a sign of progress for the waiting host thread
+            __hip_atomic_store(A.mailbox, A.mail_tag | ((uint64_t)(uint32_t)t << 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        __syncthreads();
+    }
+    __syncthreads();
+    for (int i = tid; i < A.k; i += BLK) {
+        const bool held = i < n_list;
+        const uint64_t key = held ? cur[i] : 0;
+        A.out_ids[(size_t)q * A.k + i] = held ? key_id(key) : -1;
+        A.out_scores[(size_t)q * A.k + i] = held ? key_score(key) : -INFINITY;
+    }
+    if (tid == 0) {
+        add_to_totals(A.stats, n_visited, n_expanded, t, overflow ? 1 : 0);
+        if (A.mailbox) {
+            // the last query to end reports; its word comes after every earlier one
+            __threadfence_system();
+            if (atomicAdd(&A.ctrl->next_query, 1) == A.Q - 1) {
+                __threadfence_system();
+                __hip_atomic_store(A.mailbox, A.mail_tag | 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            }
+        }
+    }
+}
+
+// The layers of a built-in shape over the fragments that its batch kernel keeps (see mlp_mfma.hip,
+// mlp_mfma_stream.hip for the orders).
+static void built_in_net(const ann_mlp *m, TileNet *T) {
+    const int KS1 = m->d_item / 16, NB1 = m->dims[1] / 32, last = m->n_layers - 1;
+    *T = TileNet{};
+    T->n_layers = m->n_layers;
+    T->J = m->J;
+    T->d_user = m->d_user;
+    T->d_item = m->d_item;
+    for (int j = 0; j < m->J; ++j) T->head_w[j] = m->head_w[j];
+    for (int l = 0; l < m->n_layers; ++l) {
+        T->KS[l] = l == 0 ? KS1 : m->dims[l] / 16;
+        T->NB[l] = l == last ? 1 : m->dims[l + 1] / 32;
+        T->b_off[l] = m->b_off[l];
+        T->step2[l] = 2;
+        if (T->KS[l] > T->slabs[l & 1]) T->slabs[l & 1] = T->KS[l];
+    }
+    if (m->n_layers == 2) {  // block of units: layer 1, then the two head fragments that take it
+        T->stride_n[0] = T->step2[1] = KS1 + 2;
+        T->base[1] = KS1;
+        return;
+    }
+    const int chunk = KS1 + 2 * T->NB[1];  // layer 1 of a block, then the fragments of layer 2 that take a block
+    const int skew = mfma_stream_supported(m->d_item, m->dims[1], m->dims[2]) ? 1 : 0;  // ... the block before
+    T->stride_n[0] = T->step2[1] = chunk;
+    T->base[1] = (int64_t)skew * chunk + KS1;
+    T->stride_n[1] = 2;
+    T->base[2] = (int64_t)(NB1 + skew) * chunk;
+}
+
+static size_t fused_smem(const SearchArgs &a, const TileNet &T, bool f64, int cb, int chunk, int new_cap, int blk) {
+    FusedLds at;
+    fused_lds(a.plan.C, a.plan.slots, a.plan.W_max, &at);
+    const bool ranked = a.plan.bitmap_words > 0 && a.g->adj_rank;
+    const size_t filter = (size_t)((chunk + 3) & ~3) * 4 * (ranked ? 2 : 1) + (size_t)fused_dd(chunk) * 16;
+    const size_t sort = (size_t)new_cap * 8 + (size_t)blk * 4;
+    const size_t net = (size_t)cb * (T.slabs[0] + T.slabs[1]) * (f64 ? 2048 : 1024);
+    size_t most = filter > sort ? filter : sort;
+    if (net > most) most = net;
+    return at.scratch + most;
+}
+
+template <int BLK, int METRIC, int CB>
+static int fused_launch(const SearchArgs &a, const FusedArgs &A, size_t smem) {
+    const bool bm = a.plan.bitmap_words > 0;
+    auto fn = bm ? fused_search_kernel<BLK, true, METRIC, CB> : fused_search_kernel<BLK, false, METRIC, CB>;
+    static std::atomic<uint32_t> raised[2];
+    if (int rc = raise_lds_limit((const void *)fn, FUSED_LDS, a.m->device, raised[bm ? 1 : 0]); rc != ANN_OK) return rc;
+    hipLaunchKernelGGL(fn, dim3(a.plan.Q), dim3(BLK), smem, a.stream, A);
+    ANN_HIP_TRY(hipGetLastError());
+    return ANN_OK;
+}
+
+// Which searches run here, and with what workgroups.  Both sides measured, batch path -> this one:
+//   - the whole batch is resident at once (a second turn of workgroups would start when the batch path is half
+//     done): 2,048 queries of 64 -> 256 -> 128 9.5 -> 9.8 ms, 4,096 of 64 -> 256 3.6 -> 4.2; 1,024 of either
+//     8.4 -> 6.1 and 2.2 -> 1.4;
+//   - a round's matrix work per CU stays small, at most FUSED_WORK operations (fp64 ones count 32 times), since a
+//     query's pairs are scored by one CU while the batch path spreads them over the chip: 128 -> 512 -> 256 with 256
+//     candidates a round (0.10 GFLOP) 2.16 -> 1.82 ms for one query, 5.0 -> 4.4 for 64; with 512 3.9 -> 4.4; with
+//     1,024 3.2 -> 7.0;
+//   - tiles of a single column block read all weights from L2 for 32 pairs: with more than one workgroup on a CU only
+//     for weights of at most FUSED_WEIGHTS bytes (512 queries of the widest metric 5.7 -> 6.0 ms).
+// The largest tile that leaves every query resident wins (fewer passes over the weights; 256 queries of 64 -> 256 -> 128
+// 2.1 ms at 128 pairs, 2.6 at 64, 3.2 at 32), and 512 threads over 256 wherever two such workgroups suffice.
+constexpr int64_t FUSED_WORK = 110 * 1000000, FUSED_WEIGHTS = 128 * 1024;
+
+static bool fused_plan(const SearchArgs &a, TileNet *T, int *blk, int *cb, int *chunk, int *new_cap, size_t *smem) {
+    const Plan &p = a.plan;
+    const ann_mlp *m = a.m;
+    if (a.walkers || a.Q_total != 0 || m->dtype == ANN_F8) return false;
+    const bool built_in = m->kernel == MLP_MFMA2, f64 = m->dtype == ANN_F32;
+    if (built_in) built_in_net(m, T);
+    else if (m->any_dev) *T = m->any;
+    else return false;
+    int64_t weights = 0;
+    for (int l = 0; l < m->n_layers; ++l)
+        weights += (int64_t)m->dims[l + 1] * (l == 0 && built_in ? m->d_item : m->dims[l]);
+    if ((int64_t)((p.Q + 255) / 256) * p.slots * 2 * weights * (f64 ? 32 : 1) > FUSED_WORK) return false;
+    *new_cap = 2;
+    while (*new_cap < p.slots) *new_cap <<= 1;
+    *chunk = p.slots < 512 ? p.slots : 512;
+    for (*cb = 4; *cb >= 1; *cb >>= 1) {
+        if (*cb > 1 && (*cb >> 1) * (f64 ? 16 : 32) >= p.slots) continue;  // half of it holds every round's pairs
+        if (*cb == 1 && p.Q > 256 && weights * (f64 ? 4 : 2) > FUSED_WEIGHTS) continue;
+        *blk = *cb > 1 ? 512 : 256;
+        *smem = fused_smem(a, *T, f64, *cb, *chunk, *new_cap, *blk);
+        if (*smem > FUSED_LDS) continue;
+        const int by_lds = (int)(160 * 1024 / *smem), by_waves = *cb == 4 ? 1 : 1024 / *blk;  // registers: 168, 125, 99
+        if (p.Q <= 256 * (by_lds < by_waves ? by_lds : by_waves)) return true;
+    }
+    return false;
+}
+
+bool fused_serves(const SearchArgs &a) {
+    TileNet T;
+    int blk, cb, chunk, new_cap;
+    size_t smem;
+    return fused_plan(a, &T, &blk, &cb, &chunk, &new_cap, &smem);
+}
+
+int launch_fused(const SearchArgs &a, int32_t rounds_max) {
+    const Plan &p = a.plan;
+    const ann_mlp *m = a.m;
+    FusedArgs A{};
+    int blk, cb;
+    size_t smem;
+    if (!fused_plan(a, &A.T, &blk, &cb, &A.chunk, &A.new_cap, &smem)) return ANN_EINVAL;
+    const bool built_in = m->kernel == MLP_MFMA2, f64 = m->dtype == ANN_F32, bm = p.bitmap_words > 0;
+    A.frag = built_in ? m->frag_dev : m->any_dev;
+    A.b = m->b_dev;
+    A.upre = built_in ? (const float *)(a.ws + p.off_upre) : nullptr;
+    A.emb = a.g->emb;
+    A.users = a.queries;
+    A.adj = a.g->adj;
+    A.adj_rank = bm ? a.g->adj_rank : nullptr;
+    A.rank = bm ? a.g->rank : nullptr;
+    A.entries = a.entries;
+    A.W_q = a.W_q, A.L_q = a.L_q, A.cap_q = a.cap_q;
+    A.table = (uint32_t *)(a.ws + p.off_hash);
+    A.stats = (int64_t *)(a.ws + p.off_stats);
+    A.ctrl = (Ctrl *)(a.ws + p.off_ctrl);
+    A.out_ids = a.out_ids;
+    A.out_scores = a.out_scores;
+    A.mailbox = a.mailbox;
+    A.mail_tag = a.mail_tag;
+    A.N = a.g->N;
+    A.R = p.R, A.E = p.E, A.W = a.W, A.L = a.L, A.cap = a.cap;
+    A.W_max = p.W_max, A.L_max = p.L_max, A.cap_max = p.max_iters_max;
+    A.C = p.C, A.k = p.k, A.slots = p.slots;
+    A.table_words = bm ? p.bitmap_words : p.hash_cap;
+    A.hash_cap = p.hash_cap;
+    A.Q = p.Q;
+    A.rounds_max = rounds_max;
+    A.int_relu = built_in && m->n_layers == 3 && mfma_stream_supported(m->d_item, m->dims[1], m->dims[2]);
+    A.wide_loads = ((uintptr_t)a.g->emb & 15) == 0 && (m->d_item & 7) == 0 &&
+                   (built_in || ((m->d_user & 7) == 0 && ((uintptr_t)a.queries & 15) == 0));
+    if (int rc = launch_zero_stats(a); rc != ANN_OK) return rc;
+#define FUSED_PICK(METRIC)                                \
+    (cb == 4   ? fused_launch<512, METRIC, 4>(a, A, smem)  \
+     : cb == 2 ? fused_launch<512, METRIC, 2>(a, A, smem)  \
+               : fused_launch<256, METRIC, 1>(a, A, smem))
+    if (f64) return FUSED_PICK(FUSED_F64);
+    return m->dtype == ANN_F16 ? FUSED_PICK(FUSED_F16) : FUSED_PICK(FUSED_BF16);
+#undef FUSED_PICK
+}
+
+}  // namespace gmpgr

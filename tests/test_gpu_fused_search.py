@@ -1,0 +1,87 @@
+"""Searches that run as one launch (small batches) against the same searches run stage by stage: id for id, relevance for
+relevance, counter for counter.  Enabling the stage timing selects the separate kernels, whose parity with the oracle
+the other tests hold."""
+import pytest
+import torch
+
+import paper_2502_11490_amd as ann
+from workloads import random_mlp
+
+pytestmark = pytest.mark.gpu
+TORCH = {"f32": torch.float32, "bf16": torch.bfloat16, "f16": torch.float16}
+ANN = {"f32": ann.ANN_F32, "bf16": ann.ANN_BF16, "f16": ann.ANN_F16}
+
+
+def _handles(dtype, du, d, hidden, J, N, R, Q, E, seed=3):
+    gen = torch.Generator().manual_seed(seed)
+    Ws, bs = random_mlp([du + d, *hidden, J], 5, "bf16" if dtype == "bf16" else "f32", bias_scale=0.2)
+    emb = torch.randn(N, d, generator=gen).to(TORCH[dtype])
+    adj = torch.randint(0, N, (N, R), generator=gen, dtype=torch.int32)
+    adj[::7, 0] = -1                      # padding, a repeated neighbour
+    adj[::5, R - 1] = adj[::5, R // 2]
+    users = torch.randn(Q, du, generator=gen).to(TORCH[dtype]).cuda()
+    entries = torch.randint(0, N, (Q, E), generator=gen, dtype=torch.int32)
+    entries[0, 0], entries[-1, E - 1] = -1, N
+    entries[Q // 2, E - 1] = entries[Q // 2, 0]
+    m = ann.ann_mlp_load([w.to(TORCH[dtype]) for w in Ws], bs, torch.rand(J, generator=gen), du, ANN[dtype])
+    g = ann.ann_graph_load(adj.cuda(), emb.cuda())
+    return g, m, users, entries.cuda()
+
+
+def _both(g, m, call, ws):
+    runs = []
+    for staged in (True, False):
+        ann.ann_profile_enable(staged)
+        try:
+            ids, sc = call()
+        finally:
+            ann.ann_profile_enable(False)
+        st = ann.ann_search_stats(ws)
+        runs.append((ids.clone(), sc.clone(), (st.pairs_scored, st.nodes_expanded, st.max_query_iters, st.visited_overflow, st.queries)))
+    launches = ann.ann_profile_read()
+    assert torch.equal(runs[0][0], runs[1][0])
+    assert torch.equal(runs[0][1].view(torch.int32), runs[1][1].view(torch.int32))  # NaN too
+    assert runs[0][2] == runs[1][2]
+    return launches
+
+
+SHAPES = [("bf16", 64, 64, (256, 128), 3), ("f16", 128, 128, (512, 256), 4), ("bf16", 64, 64, (256,), 3),
+          ("f32", 32, 32, (64,), 3), ("bf16", 13, 20, (48, 24, 16), 2), ("f32", 5, 7, (), 8)]
+
+
+@pytest.mark.parametrize("visited", ["hash", "bitmap", "rank"])
+@pytest.mark.parametrize("dtype,du,d,hidden,J", SHAPES)
+def test_one_launch_is_the_staged_search(dtype, du, d, hidden, J, visited, monkeypatch):
+    """One query and a few; one candidate a round up to several pieces of the filter; more seeds than a piece; odd
+    lists, k above and below L, lists longer than a workgroup; with and without a cap."""
+    monkeypatch.setenv("GMPGR_VISITED_SET", "hash" if visited == "hash" else "bitmap")
+    for Q, R, E, W, L, k, cap in [(1, 16, 1, 1, 1, 5, 0), (3, 1, 2, 1, 33, 7, 0), (65, 32, 3, 4, 257, 30, 0),
+                                  (5, 24, 600, 2, 65, 100, 0), (2, 32, 1024, 9, 1500, 11, 0), (17, 17, 4, 37, 300, 20, 6)]:
+        g, m, users, entries = _handles(dtype, du, d, hidden, J, 3001, R, Q, E)
+        if visited == "rank":
+            rank = torch.randperm(3001, generator=torch.Generator().manual_seed(1)).to(torch.int32).cuda()
+            ann.ann_graph_set_locality(g, rank)
+        ws = torch.empty(ann.ann_search_workspace_bytes(g, m, Q, E, W, L, k, cap), dtype=torch.uint8, device="cuda")
+        _both(g, m, lambda: ann.ann_search(g, m, users, entries, W, L, k, cap, workspace=ws), ws)
+
+
+@pytest.mark.parametrize("Q", [256, 257, 512, 513, 1024, 1025])
+@pytest.mark.parametrize("dtype,du,d,hidden,J", [SHAPES[0], SHAPES[3]])
+def test_batch_sizes_around_the_lines(dtype, du, d, hidden, J, Q):
+    """Per-query widths, lists and caps, at the batch sizes where tile and workgroup change."""
+    g, m, users, entries = _handles(dtype, du, d, hidden, J, 5000, 16, Q, 4)
+    gen = torch.Generator().manual_seed(Q)
+    own = [torch.randint(lo, hi, (Q,), generator=gen, dtype=torch.int32).cuda() for lo, hi in ((0, 10), (0, 140), (0, 30))]
+    ws = torch.empty(ann.ann_search_workspace_bytes(g, m, Q, 4, 8, 128, 20, 24), dtype=torch.uint8, device="cuda")
+    _both(g, m, lambda: ann.ann_search_ragged(g, m, users, entries, *own, 8, 128, 20, 24, workspace=ws), ws)
+
+
+@pytest.mark.parametrize("dtype,du,d,hidden,J", SHAPES[:4])
+def test_items_that_are_not_finite(dtype, du, d, hidden, J):
+    """Infinities and NaN in the item table reach the same relevances on both paths."""
+    g, m, users, entries = _handles(dtype, du, d, hidden, J, 400, 16, 9, 8)
+    emb = torch.randn(400, d).to(TORCH[dtype])
+    emb[::9, 1], emb[3::11, 0], emb[5::13, 2] = float("inf"), float("-inf"), float("nan")
+    g = ann.ann_graph_load(torch.randint(0, 400, (400, 16), dtype=torch.int32).cuda(), emb.cuda())
+    ws = torch.empty(ann.ann_search_workspace_bytes(g, m, 9, 8, 4, 64, 200, 0), dtype=torch.uint8, device="cuda")
+    _both(g, m, lambda: ann.ann_search(g, m, users, entries, 4, 64, 200, 0, workspace=ws), ws)
