@@ -159,8 +159,7 @@ struct Mailbox {
         }
         host = (volatile uint64_t *)h;
         dev = (uint64_t *)d;
-        host[0] = 0;
-        host[1] = 0;
+        for (int i = 0; i < 3; ++i) host[i] = 0;
         ok = true;
         return true;
     }
@@ -174,6 +173,11 @@ struct Mailbox {
         seq = (seq + 1) & 0xFFFFFFull;
         if (seq == 0) seq = 1;
         return seq << 40;
+    }
+    // Is the search `tag` down to at most `few` running queries, with none waiting?  (A late look is safe: never more.)
+    bool down_to(uint64_t tag, int few) const {
+        const uint64_t w = host[MAIL_RUNNING];
+        return few > 0 && (w >> 40) == (tag >> 40) && (w & 0xFFFFFFFFFFull) <= (uint64_t)few;
     }
     // Before enqueuing round `i` (0-based): 1 = the search has finished, 0 = go on, -1 = the stream reports an
     // error, or has run everything enqueued so far without the progress the kernels would have reported.
@@ -192,7 +196,7 @@ struct Mailbox {
         if (seen_rounds) *seen_rounds = 0;
         const auto start = std::chrono::steady_clock::now();
         auto last = start;
-        uint64_t seen = *host;
+        uint64_t seen = *host, sign = host[MAIL_SIGN];
         for (int spin = 0;; ++spin) {
             const uint64_t w = *host;
             int r = enough(w);
@@ -200,8 +204,10 @@ struct Mailbox {
             if (spin > 4096) sched_yield();  // a long wait: let another thread have the core between looks
             if ((spin & 1023) == 1023) {
                 const auto now = std::chrono::steady_clock::now();
-                if (w != seen) {  // the device is making progress: the limit below counts from the last report
+                const uint64_t s = host[MAIL_SIGN];
+                if (w != seen || s != sign) {  // the device is making progress: the limit below counts from the last report
                     seen = w;
+                    sign = s;
                     last = now;
                     continue;
                 }
@@ -321,7 +327,7 @@ static int run_search(SearchArgs &a) {
     // stage times are those of the separate kernels: a profiled search runs them
     const bool fused = !g_prof.on && fused_serves(a);
     if (fused) {
-        if ((rc = launch_fused(a, (int32_t)(round_limit < 0x7ffffffe ? round_limit : 0x7ffffffe))) != ANN_OK) return rc;
+        if ((rc = launch_fused(a, (int32_t)(round_limit < 0x7ffffffe ? round_limit : 0x7ffffffe), 0)) != ANN_OK) return rc;
         if (capped) return ANN_OK;
         const int g = box->gate(a.mail_tag, INT64_MAX, a.stream);
         if (g < 0) {
@@ -334,6 +340,7 @@ static int run_search(SearchArgs &a) {
         StageTimer timer(ANN_STAGE_ROUND, a.stream);
         if ((rc = launch_init(a)) != ANN_OK) return rc;
     }
+    int tail = box && !g_prof.on ? fused_tail(a) : 0;
     for (int64_t i = 0; i <= round_limit; ++i) {
         if (box) {  // no query is running: nothing left to score or merge
             const int g = box->gate(a.mail_tag, i, a.stream);
@@ -341,6 +348,10 @@ static int run_search(SearchArgs &a) {
             if (g < 0) {
                 set_error(g == -3 ? NO_PROGRESS : RAN_DRY);
                 return ANN_EDEVICE;
+            }
+            if (box->down_to(a.mail_tag, tail)) {  // the last queries run to their end in one launch
+                if ((rc = launch_fused(a, (int32_t)(round_limit < 0x7ffffffe ? round_limit : 0x7ffffffe), tail)) != ANN_OK) return rc;
+                tail = 0;
             }
         }
         a.round_index = (int32_t)i;
@@ -380,6 +391,7 @@ static int run_stream(SearchArgs &a) {
     const int64_t per_query = p.max_iters_max > 0 ? (int64_t)p.max_iters_max + 2
                                                   : (p.bitmap_words > 0 ? a.g->N : (int64_t)p.hash_cap / 2) + 3;
     const int64_t round_limit = per_query * (((int64_t)a.Q_total + p.Q - 1) / p.Q + 1);
+    int tail = g_prof.on ? 0 : fused_tail(a);
     for (int64_t i = 0; i <= round_limit; ++i) {
         {   // nothing running after an admission step, and nothing left to admit: every result is written
             const int g = box->gate(a.mail_tag, i, a.stream);
@@ -387,6 +399,10 @@ static int run_stream(SearchArgs &a) {
             if (g < 0) {
                 set_error(g == -3 ? NO_PROGRESS : RAN_DRY);
                 return ANN_EDEVICE;
+            }
+            if (box->down_to(a.mail_tag, tail)) {  // nothing waits: the last queries run to their end in one launch
+                if ((rc = launch_fused(a, (int32_t)(per_query < 0x7ffffffe ? per_query : 0x7ffffffe), tail)) != ANN_OK) return rc;
+                tail = 0;
             }
         }
         a.round_index = (int32_t)i;

@@ -103,6 +103,10 @@ struct ann_mlp {
 
 namespace gmpgr {
 
+// Words of the progress mailbox in pinned host memory (all carry the search's tag): rounds packed and finished,
+// queries still running (written once none is waiting), a sign of life of a search in one launch.
+enum { MAIL_ROUNDS = 0, MAIL_RUNNING = 1, MAIL_SIGN = 2 };
+
 // Device workspace layout; every offset is in bytes from the workspace base, 256-aligned.
 struct Plan {
     int32_t Q, E, W_max, L_max, k, C, R, max_iters_max, rounds_assumed;
@@ -178,10 +182,12 @@ int launch_stream_reset(const SearchArgs &a);
 int launch_admit(const SearchArgs &a);
 int launch_stream_publish(const SearchArgs &a, int avail);
 
-// search_fused.hip: all rounds of a small batch's queries in one launch
+// search_fused.hip: all rounds of a small batch's queries in one launch (tail = 0), or all that are left of the last
+// queries of a large one (tail = the most that may be running, as fused_tail gives it)
 constexpr size_t FUSED_LDS = 150 * 1024;
 bool fused_serves(const SearchArgs &a);
-int launch_fused(const SearchArgs &a, int32_t rounds_max);
+int fused_tail(const SearchArgs &a);  // running queries from which on the tail goes there, 0 = never
+int launch_fused(const SearchArgs &a, int32_t rounds_max, int32_t tail);
 
 // noise.hip: out = users + sigma * N(0, I), element-indexed counter-based draw (Eq. 5)
 int launch_users_add_noise(const void *users, void *out, int64_t n_elem, int dtype, double sigma, uint64_t seed,

@@ -35,6 +35,11 @@ struct FusedArgs {
     float *out_scores;
     uint64_t *mailbox;
     uint64_t mail_tag;
+    // searches that the batch path began (resume): their state, list and survivors not yet scored
+    QState *state;
+    uint64_t *pool;
+    int32_t *counts;
+    const int32_t *cand, *slot_query;
     int64_t N;
     int32_t R, E, W, L, cap, W_max, L_max, cap_max, C, k, slots, new_cap, chunk, table_words, hash_cap, Q, rounds_max;
     int32_t wide_loads, int_relu;
@@ -178,7 +183,9 @@ __host__ __device__ inline void fused_lds(int C, int slots, int W_max, FusedLds 
     o->scratch = up16(o->small + 32 * 4);
 }
 
-template <int BLK, bool BITMAP, int METRIC, int CB>
+// RESUME: the slot's search goes on from where the batch path's last round left it (survivors chosen, not yet scored)
+// and its list and state go back there, for the kernels that write the results; slots without a running search leave.
+template <int BLK, bool BITMAP, int METRIC, int CB, bool RESUME>
 __global__ void __launch_bounds__(BLK) fused_search_kernel(FusedArgs A) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int q = blockIdx.x, tid = threadIdx.x;
@@ -200,17 +207,32 @@ __global__ void __launch_bounds__(BLK) fused_search_kernel(FusedArgs A) {
     uint64_t *newk = (uint64_t *)scratch;
     uint32_t *sort_cnt = (uint32_t *)(newk + A.new_cap);
 
-    const int W = min(max(A.W_q ? A.W_q[q] : A.W, 1), A.W_max), L = min(max(A.L_q ? A.L_q[q] : A.L, 1), A.L_max);
-    const int c_own = A.cap_q ? A.cap_q[q] : A.cap;
+    int n_list = 0, n_visited = 0, n_expanded = 0, first_open = 0, t = 0, n_cand = A.E, user = q, pending = 0;
+    if (RESUME) {
+        pending = __builtin_amdgcn_readfirstlane(A.counts[q]);
+        if (pending < 0) return;
+        const QState *st = A.state + q;
+        if (__builtin_amdgcn_readfirstlane(st->done)) return;
+        n_list = __builtin_amdgcn_readfirstlane(st->n_list);
+        n_visited = __builtin_amdgcn_readfirstlane(st->n_visited);
+        n_expanded = __builtin_amdgcn_readfirstlane(st->n_expanded);
+        first_open = __builtin_amdgcn_readfirstlane(st->first_open);
+        t = __builtin_amdgcn_readfirstlane(st->t);
+        if (A.slot_query) user = __builtin_amdgcn_readfirstlane(A.slot_query[q]);
+        for (int i = tid; i < n_list; i += BLK) cur[i] = A.pool[(size_t)q * A.C + i];
+        for (int i = tid; i < pending; i += BLK) surv[i] = A.cand[(size_t)q * A.slots + i];
+        n_cand = 0;
+    }
+    const int W = min(max(A.W_q ? A.W_q[user] : A.W, 1), A.W_max), L = min(max(A.L_q ? A.L_q[user] : A.L, 1), A.L_max);
+    const int c_own = A.cap_q ? A.cap_q[user] : A.cap;
     const int cap = A.cap_max > 0 ? min(max(c_own, 1), A.cap_max) : max(c_own, 0);
     uint32_t *table = A.table + (size_t)q * A.table_words;
-    {
+    if (!RESUME) {
         const uint32_t e = BITMAP ? 0u : EMPTY_SLOT;
         for (int i = tid; i < A.table_words / 4; i += BLK) ((uint4 *)table)[i] = make_uint4(e, e, e, e);
         __threadfence_block();
         __syncthreads();
     }
-    int n_list = 0, n_visited = 0, n_expanded = 0, first_open = 0, t = 0, n_cand = A.E;
     bool seeding = true, overflow = false;
     // bounded: a search cannot run more rounds than its cap or than ids fit its visited set
     for (int round = 0; round <= A.rounds_max; ++round) {
@@ -243,12 +265,13 @@ __global__ void __launch_bounds__(BLK) fused_search_kernel(FusedArgs A) {
                                                 surv + n_new, wave_sums, nullptr, 1);
         }
         n_visited += n_new;
+        if (RESUME && round == 0) n_new = pending;  // counted by the round that found them
         __threadfence_block();  // the table's stores, for the next round's reads
         if (tid == 0) shared_i[0] = 0x7fffffff;  // rank of the first inserted entry
         __syncthreads();
 
-        if constexpr (METRIC == FUSED_F64) fused_score64<BLK, CB>(A, q, surv, sc, n_new, (f64x2 *)scratch);
-        else fused_score16<BLK, METRIC == FUSED_F16, CB>(A, q, surv, sc, n_new, (uint4 *)scratch);
+        if constexpr (METRIC == FUSED_F64) fused_score64<BLK, CB>(A, user, surv, sc, n_new, (f64x2 *)scratch);
+        else fused_score16<BLK, METRIC == FUSED_F16, CB>(A, user, surv, sc, n_new, (uint4 *)scratch);
 
         // merge: what can enter the list, sorted, by rank into the list's other copy
         const uint64_t worst = n_list == A.C ? cur[A.C - 1] : KEY_SENTINEL;
@@ -329,10 +352,24 @@ __global__ void __launch_bounds__(BLK) fused_search_kernel(FusedArgs A) {
         n_cand = n_par * A.R;
         seeding = false;
         if (A.mailbox && tid == 0 && (t & 63) == 0)  // a sign of progress for the waiting host thread
-            __hip_atomic_store(A.mailbox, A.mail_tag | ((uint64_t)(uint32_t)t << 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            __hip_atomic_store(A.mailbox + MAIL_SIGN, A.mail_tag | (uint32_t)t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         __syncthreads();
     }
     __syncthreads();
+    if (RESUME) {
+        for (int i = tid; i < n_list; i += BLK) A.pool[(size_t)q * A.C + i] = cur[i];
+        if (tid == 0) {
+            QState *st = A.state + q;
+            st->n_list = n_list;
+            st->n_visited = n_visited;
+            st->n_expanded = n_expanded;
+            st->first_open = first_open;
+            st->t = t;
+            st->done = overflow ? 3 : 1;
+            A.counts[q] = -1;
+        }
+        return;
+    }
     for (int i = tid; i < A.k; i += BLK) {
         const bool held = i < n_list;
         const uint64_t key = held ? cur[i] : 0;
@@ -342,10 +379,9 @@ __global__ void __launch_bounds__(BLK) fused_search_kernel(FusedArgs A) {
     if (tid == 0) {
         add_to_totals(A.stats, n_visited, n_expanded, t, overflow ? 1 : 0);
         if (A.mailbox) {
-            // the last query to end reports; its word comes after every earlier one
+            // the last query to end reports
             __threadfence_system();
             if (atomicAdd(&A.ctrl->next_query, 1) == A.Q - 1) {
-                __threadfence_system();
                 __hip_atomic_store(A.mailbox, A.mail_tag | 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
             }
         }
@@ -394,10 +430,10 @@ static size_t fused_smem(const SearchArgs &a, const TileNet &T, bool f64, int cb
     return at.scratch + most;
 }
 
-template <int BLK, int METRIC, int CB>
+template <int BLK, int METRIC, int CB, bool RESUME>
 static int fused_launch(const SearchArgs &a, const FusedArgs &A, size_t smem) {
     const bool bm = a.plan.bitmap_words > 0;
-    auto fn = bm ? fused_search_kernel<BLK, true, METRIC, CB> : fused_search_kernel<BLK, false, METRIC, CB>;
+    auto fn = bm ? fused_search_kernel<BLK, true, METRIC, CB, RESUME> : fused_search_kernel<BLK, false, METRIC, CB, RESUME>;
     static std::atomic<uint32_t> raised[2];
     if (int rc = raise_lds_limit((const void *)fn, FUSED_LDS, a.m->device, raised[bm ? 1 : 0]); rc != ANN_OK) return rc;
     hipLaunchKernelGGL(fn, dim3(a.plan.Q), dim3(BLK), smem, a.stream, A);
@@ -419,10 +455,10 @@ static int fused_launch(const SearchArgs &a, const FusedArgs &A, size_t smem) {
 // 2.1 ms at 128 pairs, 2.6 at 64, 3.2 at 32), and 512 threads over 256 wherever two such workgroups suffice.
 constexpr int64_t FUSED_WORK = 110 * 1000000, FUSED_WEIGHTS = 128 * 1024;
 
-static bool fused_plan(const SearchArgs &a, TileNet *T, int *blk, int *cb, int *chunk, int *new_cap, size_t *smem) {
+static bool fused_plan(const SearchArgs &a, int Q, TileNet *T, int *blk, int *cb, int *chunk, int *new_cap, size_t *smem) {
     const Plan &p = a.plan;
     const ann_mlp *m = a.m;
-    if (a.walkers || a.Q_total != 0 || m->dtype == ANN_F8) return false;
+    if (a.walkers || m->dtype == ANN_F8) return false;
     const bool built_in = m->kernel == MLP_MFMA2, f64 = m->dtype == ANN_F32;
     if (built_in) built_in_net(m, T);
     else if (m->any_dev) *T = m->any;
@@ -430,40 +466,47 @@ static bool fused_plan(const SearchArgs &a, TileNet *T, int *blk, int *cb, int *
     int64_t weights = 0;
     for (int l = 0; l < m->n_layers; ++l)
         weights += (int64_t)m->dims[l + 1] * (l == 0 && built_in ? m->d_item : m->dims[l]);
-    if ((int64_t)((p.Q + 255) / 256) * p.slots * 2 * weights * (f64 ? 32 : 1) > FUSED_WORK) return false;
+    if ((int64_t)((Q + 255) / 256) * p.slots * 2 * weights * (f64 ? 32 : 1) > FUSED_WORK) return false;
     *new_cap = 2;
     while (*new_cap < p.slots) *new_cap <<= 1;
     *chunk = p.slots < 512 ? p.slots : 512;
     for (*cb = 4; *cb >= 1; *cb >>= 1) {
         if (*cb > 1 && (*cb >> 1) * (f64 ? 16 : 32) >= p.slots) continue;  // half of it holds every round's pairs
-        if (*cb == 1 && p.Q > 256 && weights * (f64 ? 4 : 2) > FUSED_WEIGHTS) continue;
+        if (*cb == 1 && Q > 256 && weights * (f64 ? 4 : 2) > FUSED_WEIGHTS) continue;
         *blk = *cb > 1 ? 512 : 256;
         *smem = fused_smem(a, *T, f64, *cb, *chunk, *new_cap, *blk);
         if (*smem > FUSED_LDS) continue;
         const int by_lds = (int)(160 * 1024 / *smem), by_waves = *cb == 4 ? 1 : 1024 / *blk;  // registers: 168, 125, 99
-        if (p.Q <= 256 * (by_lds < by_waves ? by_lds : by_waves)) return true;
+        if (Q <= 256 * (by_lds < by_waves ? by_lds : by_waves)) return true;
     }
     return false;
 }
 
-bool fused_serves(const SearchArgs &a) {
+static bool fused_takes(const SearchArgs &a, int Q) {
     TileNet T;
     int blk, cb, chunk, new_cap;
     size_t smem;
-    return fused_plan(a, &T, &blk, &cb, &chunk, &new_cap, &smem);
+    return fused_plan(a, Q, &T, &blk, &cb, &chunk, &new_cap, &smem);
 }
 
-int launch_fused(const SearchArgs &a, int32_t rounds_max) {
+bool fused_serves(const SearchArgs &a) { return a.Q_total == 0 && fused_takes(a, a.plan.Q); }
+
+int fused_tail(const SearchArgs &a) {
+    if (a.Q_total < 0) return 0;
+    return fused_takes(a, 512) ? 512 : fused_takes(a, 256) ? 256 : 0;
+}
+
+int launch_fused(const SearchArgs &a, int32_t rounds_max, int32_t tail) {
     const Plan &p = a.plan;
     const ann_mlp *m = a.m;
     FusedArgs A{};
     int blk, cb;
     size_t smem;
-    if (!fused_plan(a, &A.T, &blk, &cb, &A.chunk, &A.new_cap, &smem)) return ANN_EINVAL;
+    if (!fused_plan(a, tail > 0 ? tail : p.Q, &A.T, &blk, &cb, &A.chunk, &A.new_cap, &smem)) return ANN_EINVAL;
     const bool built_in = m->kernel == MLP_MFMA2, f64 = m->dtype == ANN_F32, bm = p.bitmap_words > 0;
     A.frag = built_in ? m->frag_dev : m->any_dev;
     A.b = m->b_dev;
-    A.upre = built_in ? (const float *)(a.ws + p.off_upre) : nullptr;
+    A.upre = !built_in ? nullptr : a.upre_all ? a.upre_all : (const float *)(a.ws + p.off_upre);
     A.emb = a.g->emb;
     A.users = a.queries;
     A.adj = a.g->adj;
@@ -478,6 +521,11 @@ int launch_fused(const SearchArgs &a, int32_t rounds_max) {
     A.out_scores = a.out_scores;
     A.mailbox = a.mailbox;
     A.mail_tag = a.mail_tag;
+    A.state = (QState *)(a.ws + p.off_state);
+    A.pool = (uint64_t *)(a.ws + p.off_pool);
+    A.counts = (int32_t *)(a.ws + p.off_counts);
+    A.cand = (const int32_t *)(a.ws + p.off_cand);
+    A.slot_query = a.slot_query;
     A.N = a.g->N;
     A.R = p.R, A.E = p.E, A.W = a.W, A.L = a.L, A.cap = a.cap;
     A.W_max = p.W_max, A.L_max = p.L_max, A.cap_max = p.max_iters_max;
@@ -489,13 +537,17 @@ int launch_fused(const SearchArgs &a, int32_t rounds_max) {
     A.int_relu = built_in && m->n_layers == 3 && mfma_stream_supported(m->d_item, m->dims[1], m->dims[2]);
     A.wide_loads = ((uintptr_t)a.g->emb & 15) == 0 && (m->d_item & 7) == 0 &&
                    (built_in || ((m->d_user & 7) == 0 && ((uintptr_t)a.queries & 15) == 0));
-    if (int rc = launch_zero_stats(a); rc != ANN_OK) return rc;
-#define FUSED_PICK(METRIC)                                \
-    (cb == 4   ? fused_launch<512, METRIC, 4>(a, A, smem)  \
-     : cb == 2 ? fused_launch<512, METRIC, 2>(a, A, smem)  \
-               : fused_launch<256, METRIC, 1>(a, A, smem))
-    if (f64) return FUSED_PICK(FUSED_F64);
-    return m->dtype == ANN_F16 ? FUSED_PICK(FUSED_F16) : FUSED_PICK(FUSED_BF16);
+    if (tail <= 0)
+        if (int rc = launch_zero_stats(a); rc != ANN_OK) return rc;
+#define FUSED_PICK(METRIC, RESUME)                                \
+    (cb == 4   ? fused_launch<512, METRIC, 4, RESUME>(a, A, smem)  \
+     : cb == 2 ? fused_launch<512, METRIC, 2, RESUME>(a, A, smem)  \
+               : fused_launch<256, METRIC, 1, RESUME>(a, A, smem))
+    if (tail > 0)
+        return f64                     ? FUSED_PICK(FUSED_F64, true)
+               : m->dtype == ANN_F16   ? FUSED_PICK(FUSED_F16, true)
+                                       : FUSED_PICK(FUSED_BF16, true);
+    return f64 ? FUSED_PICK(FUSED_F64, false) : m->dtype == ANN_F16 ? FUSED_PICK(FUSED_F16, false) : FUSED_PICK(FUSED_BF16, false);
 #undef FUSED_PICK
 }
 

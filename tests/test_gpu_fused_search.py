@@ -85,3 +85,22 @@ def test_items_that_are_not_finite(dtype, du, d, hidden, J):
     g = ann.ann_graph_load(torch.randint(0, 400, (400, 16), dtype=torch.int32).cuda(), emb.cuda())
     ws = torch.empty(ann.ann_search_workspace_bytes(g, m, 9, 8, 4, 64, 200, 0), dtype=torch.uint8, device="cuda")
     _both(g, m, lambda: ann.ann_search(g, m, users, entries, 4, 64, 200, 0, workspace=ws), ws)
+
+
+@pytest.mark.parametrize("visited", ["hash", "bitmap"])
+@pytest.mark.parametrize("dtype,du,d,hidden,J", SHAPES[:4])
+def test_last_queries_of_a_large_batch(dtype, du, d, hidden, J, visited, monkeypatch):
+    """A batch too large for one launch ends in one: the list, the state and the survivors move over in the middle of
+    the search.  Lists of very different lengths, so that a few queries run long after the others; also through slots."""
+    monkeypatch.setenv("GMPGR_VISITED_SET", visited)
+    Q, R, E, W, L, k = 1400, 16, 3, 4, 301, 40
+    g, m, users, entries = _handles(dtype, du, d, hidden, J, 4001, R, Q, E)
+    own = [torch.full((Q,), W, dtype=torch.int32), torch.full((Q,), 9, dtype=torch.int32), torch.zeros(Q, dtype=torch.int32)]
+    own[1][::11] = L
+    own = [o.cuda() for o in own]
+    ws = torch.empty(ann.ann_search_workspace_bytes(g, m, Q, E, W, L, k, 0), dtype=torch.uint8, device="cuda")
+    _both(g, m, lambda: ann.ann_search_ragged(g, m, users, entries, *own, W, L, k, 0, workspace=ws), ws)
+    want = ann.ann_search(g, m, users, entries, W, 60, k, 0)
+    for slots in (1100, 70):
+        ids, sc = ann.ann_search_stream(g, m, users, entries, slots, W, 60, k)
+        assert torch.equal(ids, want[0]) and torch.equal(sc, want[1])
