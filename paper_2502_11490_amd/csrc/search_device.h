@@ -77,9 +77,7 @@ __device__ int filter_and_insert(const int32_t *cand, int n_cand, uint32_t *dd_k
                                  uint32_t *bk_key, uint32_t *bk_cnt, int dd_n, uint32_t *table, int hash_cap,
                                  int64_t N, int32_t *out, int *wave_sums, uint16_t *out_tag, int tag_div,
                                  int tag_base = 0) {
-    const int n_buckets = hash_cap >> 4;
-    const uint32_t bmask = (uint32_t)n_buckets - 1u;
-    const int bshift = 32 - (31 - __clz(n_buckets));  // n_buckets = 2^b (b >= 2) -> top b bits
+    const uint32_t n_buckets = (uint32_t)hash_cap >> 4;
     for (int i = threadIdx.x; i < dd_n; i += BLK) {
         dd_key[i] = EMPTY_SLOT;
         dd_pos[i] = 0xFFFFFFFFu;
@@ -114,7 +112,7 @@ __device__ int filter_and_insert(const int32_t *cand, int n_cand, uint32_t *dd_k
                 uint32_t s = hash_id((uint32_t)v) & dd_mask;
                 while (dd_key[s] != (uint32_t)v) s = (s + 1u) & dd_mask;
                 active = (dd_pos[s] == (uint32_t)p);
-                bkt = hash_id((uint32_t)v) >> bshift;
+                bkt = __umulhi(hash_id((uint32_t)v), n_buckets);  // the hash's place among the buckets
             }
         }
         for (;;) {
@@ -143,7 +141,7 @@ __device__ int filter_and_insert(const int32_t *cand, int n_cand, uint32_t *dd_k
                 if (found) {
                     active = false;  // scored in an earlier round
                 } else if (cnt == 16) {
-                    bkt = (bkt + 1u) & bmask;  // full: the id can only be further on
+                    bkt = bkt + 1u == n_buckets ? 0u : bkt + 1u;  // full: the id can only be further on
                 } else {
                     uint32_t s = hash_id(bkt) & dd_mask;
                     for (;;) {
@@ -157,7 +155,7 @@ __device__ int filter_and_insert(const int32_t *cand, int n_cand, uint32_t *dd_k
                         fresh = true;
                         active = false;
                     } else {
-                        bkt = (bkt + 1u) & bmask;  // filled up by this pass: try the next bucket
+                        bkt = bkt + 1u == n_buckets ? 0u : bkt + 1u;  // filled up by this pass: try the next bucket
                     }
                 }
             }
