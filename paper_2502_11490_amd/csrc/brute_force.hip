@@ -14,8 +14,8 @@
 
 namespace gmpgr {
 
-constexpr int BF_BLOCK = 256;
-constexpr int BF_PIECE = BF_BLOCK * 4;  // scores looked at between two looks at the buffer's fill
+constexpr int BF_WIDE = 1024;           // threads of the fold of a long row ...
+constexpr int BF_WIDE_FROM = 16384;     // ... of at least this many scores
 constexpr int BF_CAND = 2048;           // keys better than the current k-th, waiting to be merged
 constexpr int BF_KMAX = 2048;           // largest k
 constexpr int64_t BF_PAIRS = (int64_t)1 << 24;  // pairs scored per pass
@@ -40,8 +40,13 @@ __global__ void __launch_bounds__(256) bf_clear_kernel(uint64_t *best, int64_t n
 // KEY_SENTINEL = no entry yet.  The scores belong to items i0 .. i0 + nc (ids == nullptr) or to the ids
 // ids[b * nc ..] (entries outside [0, N) are no candidates).  Keys that cannot enter (not below the current
 // k-th) are dropped as they are read; the others wait in an LDS buffer that is sorted and merged by rank whenever
-// the next piece might not fit.  A waiting key goes behind the list's keys that equal it (a candidate id given
-// twice), so the merge's destinations are a permutation whether or not the keys are distinct.
+// the next piece might not fit.  A piece is four scores a thread, requested while the piece before is looked at; one
+// barrier counts the threads that keep something, an upper bound of the buffer's fill.  A long row is a chain of
+// pieces on one CU, hence the largest workgroup there: 65 rows of 65,536 scores 98 -> 33 us a pass; a candidate list
+// of 1,024 is one piece of 256 threads, and several rows share a CU.  A waiting key goes behind the list's keys that
+// equal it (a candidate id given twice), so the merge's destinations are a permutation whether or not the keys are
+// distinct.
+template <int BF_BLOCK>
 __global__ void __launch_bounds__(BF_BLOCK)
 bf_topk_kernel(const float *__restrict__ scores, int nc, int32_t i0, const int32_t *__restrict__ ids, int64_t N,
                uint64_t *best_g, int k, int q0) {
@@ -90,27 +95,51 @@ bf_topk_kernel(const float *__restrict__ scores, int nc, int32_t i0, const int32
         __syncthreads();
     };
 
-    for (int base = 0; base < nc; base += BF_PIECE) {
-        __syncthreads();
-        const int held = n_cand;
-        __syncthreads();  // nobody appends before everybody has read the fill
-        if (held + BF_PIECE > BF_CAND) fold(held);
-        const uint64_t bar = worst;
-        float s[4];
-        int32_t id[4];
+    float s[4], s_next[4];
+    int32_t id[4], id_next[4];
+    auto request = [&](int base) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const int idx = base + r * BF_BLOCK + threadIdx.x;
-            s[r] = idx < nc ? row[idx] : 0.0f;
-            id[r] = idx >= nc ? -1 : row_ids ? row_ids[idx] : i0 + idx;
+            const int64_t idx = (int64_t)base + r * BF_BLOCK + threadIdx.x;
+            s_next[r] = idx < nc ? row[idx] : 0.0f;
+            id_next[r] = idx >= nc ? -1 : row_ids ? row_ids[idx] : i0 + (int32_t)idx;
         }
+    };
+    __syncthreads();  // the bar is written
+    int held = 0;     // at least the buffer's fill; the same in every thread
+    request(0);
+    for (int base = 0; base < nc; base += 4 * BF_BLOCK) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            if (id[r] >= 0 && (int64_t)id[r] < N) {
-                const uint64_t key = make_key(s[r], id[r], 0);
-                if (key < bar) cand[atomicAdd(&n_cand, 1)] = key;
+        for (int r = 0; r < 4; ++r) s[r] = s_next[r], id[r] = id_next[r];
+        if (base + 4 * BF_BLOCK < nc) request(base + 4 * BF_BLOCK);
+        const uint64_t bar = worst;
+        uint32_t keep = 0;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            if (id[r] >= 0 && (int64_t)id[r] < N && make_key(s[r], id[r], 0) < bar) keep |= 1u << r;
+        const int more = 4 * __syncthreads_count(keep != 0);
+        if (held + more <= BF_CAND) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if ((keep >> r) & 1u) cand[atomicAdd(&n_cand, 1)] = make_key(s[r], id[r], 0);
+            held += more;
+            continue;
+        }
+#pragma unroll 1
+        for (int r = 0; r < 4; ++r) {  // score by score, with the buffer folded in whenever it might run over
+            __syncthreads();
+            held = n_cand;
+            __syncthreads();  // nobody appends before everybody has read the fill
+            if (held + BF_BLOCK > BF_CAND) fold(held);
+            if ((keep >> r) & 1u) {
+                const uint64_t key = make_key(r == 0 ? s[0] : r == 1 ? s[1] : r == 2 ? s[2] : s[3],
+                                              r == 0 ? id[0] : r == 1 ? id[1] : r == 2 ? id[2] : id[3], 0);
+                if (key < worst) cand[atomicAdd(&n_cand, 1)] = key;
             }
         }
+        __syncthreads();
+        held = n_cand;
+        __syncthreads();
     }
     __syncthreads();
     fold(n_cand);
@@ -240,7 +269,8 @@ static int best_k(const ann_graph *g, const ann_mlp *m, const void *queries_dev,
             rc = mfma ? launch_mlp_mfma(g, m, upre, pq, cand ? ids : pi, count, M, Q, sc, 0, s)
                       : launch_mlp_alu(g, m, queries_dev, pq, cand ? ids : pi, nullptr, M, Q, sc, 0, s);
             if (rc != ANN_OK) break;
-            hipLaunchKernelGGL(bf_topk_kernel, dim3(qb), dim3(BF_BLOCK), 0, s, sc, nc, (int32_t)i0, ids, g->N, best, k,
+            hipLaunchKernelGGL(nc >= BF_WIDE_FROM ? bf_topk_kernel<BF_WIDE> : bf_topk_kernel<256>, dim3(qb),
+                               dim3(nc >= BF_WIDE_FROM ? BF_WIDE : 256), 0, s, sc, nc, (int32_t)i0, ids, g->N, best, k,
                                q0);
             launched();
         }
