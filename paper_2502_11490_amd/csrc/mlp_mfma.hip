@@ -21,10 +21,7 @@
 // eight waves (two per SIMD, 256 registers each) so that one wave's item-row gather and
 // conversions overlap the other's MFMAs.
 //
-// Weights do not fit in registers and (for the largest metric) not in LDS either: they are
-// streamed through LDS in chunks, chunk nb = the 32 layer-1 units nb*32.. and the slab of
-// layer-2 weights that consumes exactly those units, double buffered; when all chunks fit
-// they are loaded once and stay resident.
+// All weights are loaded into LDS once per launch and stay.
 //
 // Numerics (bf16 mode of the library): bf16 inputs and weights, fp32 accumulation inside the
 // MFMA, hidden activations rounded to bf16 (nearest even) after ReLU, head logits, sigmoid
@@ -131,7 +128,7 @@ user_pre_kernel(const uint16_t *__restrict__ W1, int n_in, int d_user, int H1, c
 //     [D/16 + 2*n2 + s2]    lane (m,g): W2[n2*32+m][nb*32 + 16*s2 + 8*(j/4) + 4g + j%4], j < 8
 //   then the head layer, H2/16 fragments, rows >= J are zero:
 //     [2*n2 + s2]           lane (m,g): W3[m][n2*32 + 16*s2 + 8*(j/4) + 4g + j%4]
-template <int D, int H1, int H2, int CB, bool RESIDENT, int WAVES, bool F16>
+template <int D, int H1, int H2, int CB, int WAVES, bool F16>
 __global__ void __launch_bounds__(64 * WAVES)
 mlp_mfma2_kernel(const uint16_t *__restrict__ emb, int64_t N, const float *__restrict__ upre,
                  const uint4 *__restrict__ frag, const float *__restrict__ b2, const float *__restrict__ b3,
@@ -143,28 +140,23 @@ mlp_mfma2_kernel(const uint16_t *__restrict__ emb, int64_t N, const float *__res
     constexpr int CHUNK_U4 = CHUNK_FR * 64;          // uint4 per chunk
     constexpr int W3_FR = 2 * NB2;
     constexpr int BLOCK_T = 64 * WAVES;
-    constexpr int RW = 32 * CB, TILE = RW * WAVES;
-    constexpr int NBUF = RESIDENT ? NB1 : 2;
-    constexpr int ST = (CHUNK_U4 + BLOCK_T - 1) / BLOCK_T;  // staged uint4 per thread and chunk
+    constexpr int RW = 32 * CB;
+    constexpr int ALL_U4 = NB1 * CHUNK_U4 + W3_FR * 64;
+    static_assert(ALL_U4 % BLOCK_T == 0, "whole rounds of loads");
     extern __shared__ __align__(16) uint4 lds[];
-    uint4 *wbuf = lds;                                // [NBUF][CHUNK_U4]
-    uint4 *w3buf = lds + (size_t)NBUF * CHUNK_U4;     // [W3_FR * 64]
+    uint4 *wbuf = lds;                                // [NB1][CHUNK_U4]
+    uint4 *w3buf = lds + (size_t)NB1 * CHUNK_U4;      // [W3_FR * 64]
 
+    // The waves share nothing but the weights.  Pairs go to them 64 at a time, to every workgroup's first wave before
+    // any second one: a list that does not fill the chip then leaves no CU idle while another has several waves to run.
     int64_t M = (int64_t)*M_dev;
     if (M > M_max) M = M_max;
-    const int64_t n_tiles = (M + TILE - 1) / TILE;
+    const int64_t n_tiles = (M + RW - 1) / RW, step = (int64_t)gridDim.x * WAVES;
     if ((int64_t)blockIdx.x >= n_tiles) return;
 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int g = lane >> 5, col = lane & 31;
-
-    // head-layer fragments, and either every chunk (resident) or chunk 0
-    for (int i = threadIdx.x; i < W3_FR * 64; i += BLOCK_T) w3buf[i] = frag[(size_t)NB1 * CHUNK_U4 + i];
-    {
-        const int n_pre = RESIDENT ? NB1 * CHUNK_U4 : CHUNK_U4;
-        for (int i = threadIdx.x; i < n_pre; i += BLOCK_T) wbuf[i] = frag[i];
-    }
-    __syncthreads();
+    const int64_t first = (int64_t)wave * gridDim.x + blockIdx.x;
 
     float hw[4], bb3[4];
 #pragma unroll
@@ -185,7 +177,7 @@ mlp_mfma2_kernel(const uint16_t *__restrict__ emb, int64_t N, const float *__res
         Ids r;
 #pragma unroll
         for (int c = 0; c < CB; ++c) {
-            int64_t row = tile * TILE + (int64_t)wave * RW + c * 32 + col;
+            int64_t row = tile * RW + c * 32 + col;
             row = row < M ? row : M - 1;
             const int32_t v = pair_id[row], q = pair_q[row];
             r.bad[c] = ((uint64_t)(int64_t)v >= (uint64_t)N) | ((uint32_t)q >= (uint32_t)Q);
@@ -203,13 +195,20 @@ mlp_mfma2_kernel(const uint16_t *__restrict__ emb, int64_t N, const float *__res
             for (int s = 0; s < KS1; ++s) xf[c][s] = src[2 * s];
         }
     };
-    Ids idc = load_ids(blockIdx.x), idn = load_ids((int64_t)blockIdx.x + gridDim.x);
-    gather(idc);
+    Ids idc = load_ids(first), idn = load_ids(first + step);
+    {   // every weight, all requests in flight at once, under the trip for the pair ids
+        uint4 w[ALL_U4 / BLOCK_T];
+#pragma unroll
+        for (int i = 0; i < ALL_U4 / BLOCK_T; ++i) w[i] = frag[threadIdx.x + i * BLOCK_T];
+        gather(idc);
+#pragma unroll
+        for (int i = 0; i < ALL_U4 / BLOCK_T; ++i) lds[threadIdx.x + i * BLOCK_T] = w[i];
+    }
+    __syncthreads();
 
-    int cur = 0;
 #pragma unroll 1
-    for (int64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
-        const int64_t row0 = tile * TILE + (int64_t)wave * RW;
+    for (int64_t tile = first; tile < n_tiles; tile += step) {
+        const int64_t row0 = tile * RW;
         const float *up[CB];
         bool bad[CB];
 #pragma unroll
@@ -218,7 +217,7 @@ mlp_mfma2_kernel(const uint16_t *__restrict__ emb, int64_t N, const float *__res
             bad[c] = idc.bad[c];
         }
         idc = idn;                                             // the next batch ...
-        idn = load_ids(tile + 2 * (int64_t)gridDim.x);         // ... and the one after it
+        idn = load_ids(tile + 2 * step);                       // ... and the one after it
         f32x16 acc2[NB2][CB];
         // the bias pointer is laundered once per batch: otherwise the loads below are hoisted
         // out of the batch loop and their 16*NB2 values are carried (spilled) across it
@@ -240,17 +239,7 @@ mlp_mfma2_kernel(const uint16_t *__restrict__ emb, int64_t N, const float *__res
 
 #pragma unroll 1
         for (int nb = 0; nb < NB1; ++nb) {
-            const uint4 *wc = wbuf + (size_t)(RESIDENT ? nb : cur) * CHUNK_U4;
-            uint4 stage[ST];
-            if (!RESIDENT) {
-                const int nxt = (nb + 1 == NB1) ? 0 : nb + 1;
-                const uint4 *srcw = frag + (size_t)nxt * CHUNK_U4;
-#pragma unroll
-                for (int t = 0; t < ST; ++t) {
-                    int i = threadIdx.x + t * BLOCK_T;
-                    if (i < CHUNK_U4) stage[t] = srcw[i];
-                }
-            }
+            const uint4 *wc = wbuf + (size_t)nb * CHUNK_U4;
             // layer 1, units nb*32 .. nb*32+31: accumulators start from the per-query user term
             f32x16 acc1[CB];
 #pragma unroll
@@ -285,16 +274,6 @@ mlp_mfma2_kernel(const uint16_t *__restrict__ emb, int64_t N, const float *__res
                     for (int c = 0; c < CB; ++c)
                         acc2[n2][c] = mfma16<F16>(a, hf[c][s2], acc2[n2][c]);
                 }
-            }
-            if (!RESIDENT) {
-                uint4 *dst = wbuf + (size_t)(cur ^ 1) * CHUNK_U4;
-#pragma unroll
-                for (int t = 0; t < ST; ++t) {
-                    int i = threadIdx.x + t * BLOCK_T;
-                    if (i < CHUNK_U4) dst[i] = stage[t];
-                }
-                __syncthreads();
-                cur ^= 1;
             }
         }
 
@@ -521,20 +500,18 @@ int launch_user_pre(const ann_mlp *m, const void *queries, int32_t Q, float *upr
     return ANN_OK;
 }
 
-template <int D, int H1, int H2, int CB, bool RESIDENT, int WAVES, bool F16>
+template <int D, int H1, int H2, int CB, int WAVES, bool F16>
 static int launch_one(const ann_graph *g, const ann_mlp *m, const float *upre, const int32_t *pair_q,
                       const int32_t *pair_id, const int32_t *M_dev, int64_t M_max, int32_t Q, float *scores,
                       hipStream_t stream) {
     constexpr int KS1 = D / 16, NB1 = H1 / 32, NB2 = H2 / 32;
     constexpr int CHUNK_U4 = (KS1 + 2 * NB2) * 64;
-    constexpr int NBUF = RESIDENT ? NB1 : 2;
-    constexpr size_t smem = ((size_t)NBUF * CHUNK_U4 + 2 * NB2 * 64) * 16;
-    constexpr int TILE = 32 * CB * WAVES;
+    constexpr size_t smem = ((size_t)NB1 * CHUNK_U4 + 2 * NB2 * 64) * 16;
     static_assert(smem <= 160 * 1024, "LDS budget");
-    auto fn = mlp_mfma2_kernel<D, H1, H2, CB, RESIDENT, WAVES, F16>;
+    auto fn = mlp_mfma2_kernel<D, H1, H2, CB, WAVES, F16>;
     static std::atomic<uint32_t> raised;
     if (int rc = raise_lds_limit((const void *)fn, smem, m->device, raised); rc != ANN_OK) return rc;
-    int64_t tiles = (M_max + TILE - 1) / TILE;
+    int64_t tiles = (M_max + 32 * CB - 1) / (32 * CB);
     int grid = (int)(tiles < 256 ? tiles : 256);
     const float *b2 = m->b_dev + m->b_off[1], *b3 = m->b_dev + m->b_off[2];
     hipLaunchKernelGGL(fn, dim3(grid), dim3(64 * WAVES), smem, stream, (const uint16_t *)g->emb, g->N, upre,
@@ -570,8 +547,8 @@ int launch_mlp_mfma(const ann_graph *g, const ann_mlp *m, const float *upre, con
         return launch_mlp_mfma_stream(g, m, upre, pair_q, pair_id, M_dev, M_max, Q, scores, stream);
     if (D == 64 && H1 == 256 && H2 == 128)
         return m->dtype == ANN_F16
-                   ? launch_one<64, 256, 128, 2, true, 8, true>(g, m, upre, pair_q, pair_id, M_dev, M_max, Q, scores, stream)
-                   : launch_one<64, 256, 128, 2, true, 8, false>(g, m, upre, pair_q, pair_id, M_dev, M_max, Q, scores, stream);
+                   ? launch_one<64, 256, 128, 2, 8, true>(g, m, upre, pair_q, pair_id, M_dev, M_max, Q, scores, stream)
+                   : launch_one<64, 256, 128, 2, 8, false>(g, m, upre, pair_q, pair_id, M_dev, M_max, Q, scores, stream);
     set_error("no MFMA kernel for item width %d, hidden %d, %d", D, H1, H2);
     return ANN_ENOTIMPL;
 }
