@@ -42,7 +42,7 @@ __global__ void __launch_bounds__(256) bf_clear_kernel(uint64_t *best, int64_t n
 // k-th) are dropped as they are read; the others wait in an LDS buffer that is sorted and merged by rank whenever
 // the next piece might not fit.  A piece is four scores a thread, requested while the piece before is looked at; one
 // barrier counts the threads that keep something, an upper bound of the buffer's fill.  A long row is a chain of
-// pieces on one CU, hence the largest workgroup there: 65 rows of 65,536 scores 98 -> 33 us a pass; a candidate list
+// pieces on one CU, hence the largest workgroup there: 65 rows of 65,536 scores 98 -> 42 us a pass; a candidate list
 // of 1,024 is one piece of 256 threads, and several rows share a CU.  A waiting key goes behind the list's keys that
 // equal it (a candidate id given twice), so the merge's destinations are a permutation whether or not the keys are
 // distinct.
