@@ -93,7 +93,7 @@ def kernel_source_id(names=("mlp_mfma_stream.hip", "mlp_mfma_stream_asm.inc", "m
     return h.hexdigest()[:16]
 
 
-ROUND_KERNEL_SOURCES = ("search_kernels.hip", "keys.h")
+ROUND_KERNEL_SOURCES = ("search_kernels.hip", "search_device.h", "keys.h")
 
 
 def recorded_traffic(workload: str, W: int, L: int, kernel: str = "mlp"):
