@@ -338,7 +338,9 @@ int ann_quantize_e4m3(const void *src_dev, int32_t src_dtype, int64_t n, float s
  * Relevance (Eq. 5-8) of an explicit list of M pairs: out_dev[r] = relevance(user q_idx[r],
  * item item[r]).  q_idx_dev, item_dev: [M] int32; out_dev: [M] fp32.  Pairs whose indices
  * are out of range get NaN.  Uses the same kernels as the search.  `tile_rows` (0 = default)
- * sets how many pairs one batch of Algorithm 2 holds; results do not depend on it.
+ * sets how many pairs one batch of Algorithm 2 holds at most, for metrics whose widths are the caller's own and fp32
+ * ones (batches of 16, 32 or 64 pairs in fp32, 32 or 64 in the 16-bit formats; powers of two up to 64 with
+ * ANN_MLP_GENERIC and very wide layers); the kernels of the built-in shapes have batches of a fixed size.  Results do not depend on it.
  * The call allocates and frees a small temporary on `stream`'s device and synchronises.
  */
 int ann_score_pairs(const ann_graph *g, const ann_mlp *m, const void *queries_dev, int32_t Q,

@@ -210,7 +210,7 @@ bool any_supported(const ann_mlp *m);
 int build_any_fragments(ann_mlp *m, const void *const *W_host, hipStream_t stream);
 int launch_mlp_any(const ann_graph *g, const ann_mlp *m, const void *queries, const int32_t *pair_q,
                    const int32_t *pair_id, const int32_t *M_dev, int64_t M_max, int32_t Q, float *scores,
-                   hipStream_t stream);
+                   int32_t tile_rows, hipStream_t stream);
 int launch_user_pre(const ann_mlp *m, const void *queries, int32_t Q, float *upre, hipStream_t stream);
 int launch_mlp_mfma(const ann_graph *g, const ann_mlp *m, const float *upre, const int32_t *pair_q,
                     const int32_t *pair_id, const int32_t *M_dev, int64_t M_max, int32_t Q, float *scores,

@@ -140,7 +140,7 @@ int launch_mlp_alu(const ann_graph *g, const ann_mlp *m, const void *queries, co
                    const int32_t *pair_id, const int32_t *M_dev, int64_t M_max, int32_t Q, float *scores,
                    int32_t tile_rows, hipStream_t stream) {
     if (M_max <= 0) return ANN_OK;
-    if (any_supported(m)) return launch_mlp_any(g, m, queries, pair_q, pair_id, M_dev, M_max, Q, scores, stream);
+    if (any_supported(m)) return launch_mlp_any(g, m, queries, pair_q, pair_id, M_dev, M_max, Q, scores, tile_rows, stream);
     AluMlpParams P;
     P.n_layers = m->n_layers;
     int maxw = 0;

@@ -221,14 +221,18 @@ int build_any_fragments(ann_mlp *m, const void *const *W_host, hipStream_t strea
 
 int launch_mlp_any(const ann_graph *g, const ann_mlp *m, const void *queries, const int32_t *pair_q,
                    const int32_t *pair_id, const int32_t *M_dev, int64_t M_max, int32_t Q, float *scores,
-                   hipStream_t stream) {
+                   int32_t tile_rows, hipStream_t stream) {
     if (M_max <= 0) return ANN_OK;
     const TileNet &T = m->any;
     const bool f64 = m->dtype == ANN_F32;
     const int unit = f64 ? 16 : 32;
-    // Pairs per batch: as many as leave room for two workgroups on a CU, fewer while a CU would stay idle.
+    // Pairs per batch: as many as leave room for two workgroups on a CU, fewer while a CU would stay idle.  The caller's
+    // own number is a limit instead, down to one block of columns (and the LDS one upwards).
     int cb = f64 ? 4 : 2;
-    while (cb > 1 && (any_smem(T, f64, cb) > 80 * 1024 || (M_max + unit * cb - 1) / (unit * cb) < 512)) cb >>= 1;
+    if (tile_rows > 0)
+        while (cb > 1 && (any_smem(T, f64, cb) > ANY_LDS || unit * cb > tile_rows)) cb >>= 1;
+    else
+        while (cb > 1 && (any_smem(T, f64, cb) > 80 * 1024 || (M_max + unit * cb - 1) / (unit * cb) < 512)) cb >>= 1;
     const size_t smem = any_smem(T, f64, cb);
     const int64_t tiles = (M_max + unit * cb - 1) / (unit * cb);
     const int grid = (int)(tiles < 1024 ? tiles : 1024);

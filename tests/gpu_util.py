@@ -2,6 +2,8 @@
 library handles, and build the oracle's view of the same arrays."""
 from __future__ import annotations
 
+import ctypes
+
 import numpy as np
 import torch
 
@@ -33,3 +35,28 @@ def host_view(wl):
 
 def same_list_fraction(a: np.ndarray, b: np.ndarray) -> float:
     return float(np.mean(np.all(a == b, axis=1)))
+
+
+class _KernelNode(ctypes.Structure):  # hipKernelNodeParams
+    _fields_ = [("block", ctypes.c_uint * 3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p),
+                ("grid", ctypes.c_uint * 3), ("params", ctypes.c_void_p), ("lds", ctypes.c_uint)]
+
+
+def captured_launches(call):
+    """The kernel launches that `call` enqueues, recorded into a HIP graph: (workgroups, threads of one) each."""
+    with open("/proc/self/maps") as f:  # the runtime that is loaded already
+        hip = ctypes.CDLL(next(line.split()[-1] for line in f if "libamdhip64.so" in line))
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        call()
+    handle, n = ctypes.c_void_p(graph.raw_cuda_graph()), ctypes.c_size_t()
+    assert hip.hipGraphGetNodes(handle, None, ctypes.byref(n)) == 0
+    nodes, kind, p, out = (ctypes.c_void_p * n.value)(), ctypes.c_int(), _KernelNode(), []
+    assert hip.hipGraphGetNodes(handle, nodes, ctypes.byref(n)) == 0
+    for node in nodes:
+        assert hip.hipGraphNodeGetType(ctypes.c_void_p(node), ctypes.byref(kind)) == 0
+        assert kind.value == 0, "a node that is not a kernel"
+        assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(p)) == 0
+        out.append((p.grid[0], p.block[0]))
+    return out

@@ -9,6 +9,7 @@ import pytest
 import torch
 
 import oracle
+from gpu_util import captured_launches
 from workloads import random_mlp, to_host
 
 pytestmark = pytest.mark.gpu
@@ -76,3 +77,28 @@ def test_own_widths_pairs_out_of_range_and_infinities(dtype):
     assert list(np.isnan(got)) == list(np.isnan(want)) and np.isnan(got[[1, 2, 3, 6]]).all()
     keep = ~np.isnan(want)
     np.testing.assert_allclose(got[keep], want[keep], atol=1e-6 if dtype == "f32" else 2e-3)
+
+
+@pytest.mark.parametrize("dtype,d_user,d,hidden", [("f32", 32, 32, (64,)), ("f32", 13, 20, (48, 24, 16)),
+                                                   ("bf16", 13, 20, (48, 24, 16)), ("f16", 80, 96, (192, 96))])
+def test_batches_of_every_size_give_a_pair_the_same_bits(dtype, d_user, d, hidden):
+    """tile_rows is the most pairs a batch holds (one workgroup each), down to one block of columns; a pair's relevance
+    is the same bit for bit whichever batch it lies in, a list too short for large batches by itself included."""
+    gen = torch.Generator().manual_seed(7)
+    N, Q, M, J = 700, 41, 40_003, 3
+    Ws, bs = random_mlp([d_user + d, *hidden, J], 5, "bf16" if dtype == "bf16" else "f32", bias_scale=0.2)
+    emb, users = (torch.randn(n, w, generator=gen).to(TORCH[dtype]).cuda() for n, w in ((N, d), (Q, d_user)))
+    g = ann.ann_graph_load(torch.zeros(N, 1, dtype=torch.int32, device="cuda"), emb)
+    m = ann.ann_mlp_load([w.to(TORCH[dtype]) for w in Ws], bs, torch.rand(J, generator=gen), d_user, ANN[dtype])
+    q, it = (torch.randint(0, n, (M,), generator=gen, dtype=torch.int32).cuda() for n in (Q, N))
+    base = ann.ann_score_pairs(g, m, users, q, it)  # long enough for the largest batches
+    short, least = 1234, 16 if dtype == "f32" else 32
+    for tile_rows in (0, 1, 16, 31, 32, 63, 64, 1000):
+        out = torch.empty(short, device="cuda")
+        call = lambda: ann.ann_score_pairs(g, m, users, q[:short], it[:short], out=out, tile_rows=tile_rows)
+        call()
+        assert torch.equal(out, base[:short]), tile_rows
+        pairs = max(least, 64 if tile_rows >= 64 else 32 if tile_rows >= 32 else 16)
+        if tile_rows > 0:
+            assert captured_launches(call) == [(-(-short // pairs), 256)], tile_rows
+        assert torch.equal(ann.ann_score_pairs(g, m, users, q, it, tile_rows=tile_rows), base), tile_rows
