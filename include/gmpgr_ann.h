@@ -144,8 +144,9 @@ int ann_mlp_uses_mfma(const ann_mlp *m);
  *     E + rounds * W_max * R ids,  rounds = max_iters_max > 0 ? max_iters_max
  *                                                            : 2 * ceil(L_max / W_max) + 32
  * (at most N).  A query that would outgrow its table stops early and is counted in
- * ann_stats.visited_overflow.  Where such a table takes a megabyte or more and one bit per item (N / 8 bytes
- * per query) is at most twice its size, the visited set is that bitmap instead, which cannot fill up.  The
+ * ann_stats.visited_overflow.  Without a cap the table's size is rounded up to a power of two.  Where it takes (with a
+ * cap: would then take) a megabyte or more and one bit per item (N / 8 bytes per query) is at most twice the table's
+ * size, the visited set is that bitmap instead, which cannot fill up.  The
  * environment variable GMPGR_VISITED_SET = "hash" or "bitmap", read by this call and by every search,
  * overrides the choice (for measurements and tests; it must not change between sizing and searching).
  * Returns 0 on invalid arguments (see ann_last_error).

@@ -81,23 +81,25 @@ bool make_plan(const ann_graph *g, const ann_mlp *m, int32_t Q, int32_t E, int32
         set_error("visited table of %lld entries per query is too large", (long long)cap);
         return false;
     }
-    p->hash_cap = next_pow2(cap < 64 ? 64 : cap);
+    // With a cap the ids are bounded, so nothing beyond twice that bound is needed (whole 256-byte pieces); without one
+    // the power of two stands, as its slack decides which searches outgrow their table.  Seeding clears the tables at
+    // memory speed: 8,192 queries of at most 32,772 ids each, 743 -> 372 us.
+    const int64_t rounded = next_pow2(cap < 64 ? 64 : cap);
+    p->hash_cap = (int32_t)(max_iters_max > 0 && cap >= 64 ? (cap + 63) & ~63ll : rounded);
     // one bit per item is the smaller visited set once the table outgrows N / 8 bytes (long lists): all probes
     // of a batch then fall into a far smaller address range, and seeding has far less to clear
-    // (measured: already faster at 1.2 x the table's size; taken up to twice its size, for tables of a megabyte or
-    // more: a small table is cheaper to clear than a bitmap of all items).  GMPGR_VISITED_SET =
+    // (measured: already faster at 1.2 x the table's size; taken up to twice its size, for tables that round up to a
+    // megabyte or more: a small table is cheaper to clear than a bitmap of all items).  8,192 capped queries with tables
+    // of 0.53 MB, table against bitmap: 11.2 | 10.9 ms at 1.4 x the table's size, 10.8 | 10.8 at 1.9, 10.8 | 11.2 at 2.4,
+    // 11.0 | 12.4 at 3.8; a locality order changes neither side there.  GMPGR_VISITED_SET =
     // "bitmap" / "hash" overrides the rule, for measurements and for tests of either form at any size.
     const int64_t words = ((g->N + 31) / 32 + 63) & ~63ll;
-    bool bitmap = p->hash_cap >= (1 << 18) && words <= 2 * (int64_t)p->hash_cap;
+    bool bitmap = rounded >= (1 << 18) && words <= 2 * (int64_t)p->hash_cap;
     if (const char *force = getenv("GMPGR_VISITED_SET")) {
         if (!strcmp(force, "bitmap")) bitmap = true;
         if (!strcmp(force, "hash")) bitmap = false;
     }
     p->bitmap_words = bitmap ? (int32_t)words : 0;
-    // With a cap the ids are bounded, so nothing beyond twice that bound is needed (whole 256-byte pieces); without one
-    // the power of two stands, as its slack decides which searches outgrow their table.  Seeding clears the tables at
-    // memory speed: 8,192 queries of at most 32,772 ids each, 743 -> 372 us.
-    if (max_iters_max > 0 && cap >= 64) p->hash_cap = (int32_t)((cap + 63) & ~63ll);
     p->M_max = (int64_t)Q * p->slots;
     if (p->M_max > 0x7fffffffll) {
         set_error("Q * max(W*R,E) = %lld pairs per round exceeds 2^31", (long long)p->M_max);

@@ -111,7 +111,7 @@ enum { MAIL_ROUNDS = 0, MAIL_RUNNING = 1, MAIL_SIGN = 2 };
 struct Plan {
     int32_t Q, E, W_max, L_max, k, C, R, max_iters_max, rounds_assumed;
     int32_t slots;          // survivors kept per query and round: max(W_max*R, E)
-    int32_t hash_cap;       // per-query visited table entries (power of two)
+    int32_t hash_cap;       // per-query visited table entries (a power of two; with a round cap a multiple of 64)
     int32_t bitmap_words;   // > 0: the visited set is a bitmap of this many 32-bit words per query instead
     int64_t M_max;          // Q * slots
     int32_t H1;             // first hidden width (user-half pre-activations), 0 if unused

@@ -109,3 +109,19 @@ def test_rank_must_be_a_permutation():
     ann.ann_graph_set_locality(g, None)
     ids0, _ = ann.ann_search(g, m, dev["users"], dev["entries"], 2, 16, 5, 0)
     assert torch.equal(ids, ids0)
+
+
+def test_form_of_the_visited_set_follows_the_size_it_has():
+    """A bitmap is taken up to twice the table's own size: with a round cap that is the exact bound (4 + 128 * 512 ids
+    here, 132,160 entries), without one the power of two (262,144 entries, for the same number of ids)."""
+    adj = torch.zeros(10_000_000, 1, dtype=torch.int32, device="cuda")
+    emb = torch.zeros(10_000_000, 1, device="cuda")
+    m = ann.ann_mlp_load([torch.ones(1, 2)], [torch.zeros(1)], torch.ones(1), 1, ann.ANN_F32)
+    at = {N: ann.ann_graph_load(adj[:N], emb[:N]) for N in (8_300_000, 8_400_000, 8_500_000, 10_000_000)}
+    form = lambda N, L, cap: ann.ann_search_visited_set_is_bitmap(at[N], m, 64, 4, 512, L, 10, cap)
+    size = lambda N, L, cap: ann.ann_search_workspace_bytes(at[N], m, 64, 4, 512, L, 10, cap)
+    assert form(8_400_000, 64, 128) and not form(8_500_000, 64, 128) and not form(10_000_000, 64, 128)
+    assert size(8_500_000, 64, 128) < size(8_400_000, 64, 128)      # the smaller form, not only the other one
+    assert form(10_000_000, 24_576, 0)                              # 2 * 48 + 32 rounds are assumed
+    # 130,112 entries round up to less than a megabyte, 131,136 to one (a bitmap of 259,392 words)
+    assert not form(8_300_000, 64, 126) and form(8_300_000, 64, 127)
