@@ -165,7 +165,7 @@ size_t ann_search_workspace_bytes(const ann_graph *g, const ann_mlp *m, int32_t 
  *                   256-byte aligned; contents need not be preserved between calls
  *   out_ids_dev   : [Q][k] int32, out_scores_dev : [Q][k] fp32 (padding: -1 / -inf)
  * With max_iters > 0 the call only enqueues work.  With max_iters = 0 it also follows the
- * device's progress (a word in pinned host memory that the kernels update every round) to learn
+ * device's progress (words in pinned host memory that the kernels update, see ann_set_progress_timeout) to learn
  * when every query has converged, stays a few rounds ahead of the device meanwhile, and waits
  * on `stream` once, at the end (so such a call cannot be recorded into a HIP graph; a capped
  * one can: it launches kernels only).  Work enqueued on `stream` before the call is waited for up to
@@ -407,11 +407,13 @@ int ann_score_pairs_noalloc(const ann_graph *g, const ann_mlp *m, const void *qu
 
 /*
  * Searches that run until every query has converged (ann_search / ann_search_layers with max_iters = 0,
- * ann_search_stream) follow the progress word their kernels store to pinned host memory every round.  This sets,
+ * ann_search_stream) follow the progress their kernels report to pinned host memory: every round of the batch, and
+ * where the search of a small batch, or that of the last queries of a large one, is a single launch, after the first
+ * and every eighth round of a query (rounds take microseconds to a few hundred of them).  This sets,
  * for the whole process, how long such a call waits for the NEXT report while `stream` stays busy before it gives
  * up with ANN_EDEVICE (default 600 s, 0 = wait for ever).  The limit counts from the last report seen, so work
  * the caller enqueued on the stream ahead of the search must finish within it too.  A call that gives up has
- * enqueued only complete rounds; its kernels end by themselves, nothing is left waiting on the device, and the
+ * enqueued only complete rounds or the whole search; its kernels end by themselves, nothing is left waiting on the device, and the
  * results are undefined.  While it waits the calling thread yields the core between looks at the word.
  */
 int ann_set_progress_timeout(double seconds);

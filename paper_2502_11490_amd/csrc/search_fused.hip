@@ -351,7 +351,9 @@ __global__ void __launch_bounds__(BLK) fused_search_kernel(FusedArgs A) {
         n_expanded += n_par;
         n_cand = n_par * A.R;
         seeding = false;
-        if (A.mailbox && tid == 0 && (t & 63) == 0)  // a sign of progress for the waiting host thread
+        // A sign of progress for the waiting host thread, after a query's first round and every eighth one: a store that
+        // nobody waits for, but a thousand workgroups send theirs over one link.
+        if (A.mailbox && tid == 0 && (t & 7) == 1)
             __hip_atomic_store(A.mailbox + MAIL_SIGN, A.mail_tag | (uint32_t)t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         __syncthreads();
     }

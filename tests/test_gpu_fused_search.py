@@ -104,3 +104,38 @@ def test_last_queries_of_a_large_batch(dtype, du, d, hidden, J, visited, monkeyp
     for slots in (1100, 70):
         ids, sc = ann.ann_search_stream(g, m, users, entries, slots, W, 60, k)
         assert torch.equal(ids, want[0]) and torch.equal(sc, want[1])
+
+
+def slow_rounds(W):
+    """A search of one query with slow rounds: every parent's row is one item of the next layer and 63 filler items, all
+    ids multiples of 1,024, which fall on one slot of the filter's table in LDS and walk through it one by one.  W items a
+    layer, 60 layers; relevance grows from layer to layer, the fillers have the least."""
+    R, layers, groups, step = 64, 60, 8, 1024
+    n_fill = groups * (R - 1)
+    N = (n_fill + (layers + 1) * W) * step
+    adj = torch.full((N, R), -1, dtype=torch.int32, device="cuda")
+    fill = torch.arange(n_fill, dtype=torch.int32, device="cuda").view(groups, R - 1) * step
+    node = lambda layer: (n_fill + layer * W + torch.arange(W, device="cuda")) * step
+    for layer in range(layers):
+        adj[node(layer), 0] = node(layer + 1).int()
+        adj[node(layer), 1:] = fill.repeat(-(-W // groups), 1)[:W]
+    emb = torch.full((N, 1), -4.0, device="cuda")
+    emb[torch.arange(n_fill, N // step, device="cuda") * step, 0] = torch.linspace(-3, 3, (layers + 1) * W, device="cuda")
+    m = ann.ann_mlp_load([torch.tensor([[0.0, 1.0]])], [torch.zeros(1)], torch.ones(1), 1, ann.ANN_F32)
+    return ann.ann_graph_load(adj, emb), m, torch.zeros(1, 1, device="cuda"), node(0).int()[None].contiguous(), W, W, W, layers
+
+
+def test_a_search_in_one_launch_reports_its_progress():
+    """36 ms of one query's rounds, 0.6 ms each and fewer than 64, under a limit far below that (a wait is looked at after
+    20 ms without a report): the kernel reports often enough for the call to see that it goes on."""
+    g, m, users, entries, W, L, k, layers = slow_rounds(32)
+    ws = torch.empty(ann.ann_search_workspace_bytes(g, m, 1, W, W, L, k, 0), dtype=torch.uint8, device="cuda")
+    want = ann.ann_search(g, m, users, entries, W, L, k, 0, workspace=ws)
+    assert ann.ann_search_stats(ws).max_query_iters == layers + 1
+    ann.ann_set_progress_timeout(1e-3)
+    try:
+        got = ann.ann_search(g, m, users, entries, W, L, k, 0, workspace=ws)
+    finally:
+        ann.ann_set_progress_timeout(600.0)
+        torch.cuda.synchronize()
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
