@@ -173,7 +173,7 @@ struct SearchArgs {
 };
 
 // search_kernels.hip
-int launch_zero_stats(const SearchArgs &a);
+int launch_zero_stats(const SearchArgs &a, int32_t one_launch);  // one_launch: queries that one launch will run
 int launch_init(const SearchArgs &a);
 int launch_scan_compact(const SearchArgs &a);
 int launch_round(const SearchArgs &a);

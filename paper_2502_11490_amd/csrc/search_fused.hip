@@ -369,6 +369,7 @@ __global__ void __launch_bounds__(BLK) fused_search_kernel(FusedArgs A) {
             st->t = t;
             st->done = overflow ? 3 : 1;
             A.counts[q] = -1;
+            atomicAdd((unsigned long long *)&A.stats[7], 1ull);
         }
         return;
     }
@@ -540,7 +541,7 @@ int launch_fused(const SearchArgs &a, int32_t rounds_max, int32_t tail) {
     A.wide_loads = ((uintptr_t)a.g->emb & 15) == 0 && (m->d_item & 7) == 0 &&
                    (built_in || ((m->d_user & 7) == 0 && ((uintptr_t)a.queries & 15) == 0));
     if (tail <= 0)
-        if (int rc = launch_zero_stats(a); rc != ANN_OK) return rc;
+        if (int rc = launch_zero_stats(a, p.Q); rc != ANN_OK) return rc;
 #define FUSED_PICK(METRIC, RESUME)                                \
     (cb == 4   ? fused_launch<512, METRIC, 4, RESUME>(a, A, smem)  \
      : cb == 2 ? fused_launch<512, METRIC, 2, RESUME>(a, A, smem)  \

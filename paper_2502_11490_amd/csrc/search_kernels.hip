@@ -78,11 +78,12 @@ __device__ __forceinline__ int visited_filter(const int32_t *cand, const int32_t
 // Counters and control block start at zero (a kernel, not a memset, so that a caller may
 // capture the launch sequence into a HIP graph).
 // stats[5], stats[6]: bytes of one adjacency row and of one item row, from which ann_search_stats derives the
-// algorithmic bytes of the gather stages.
+// algorithmic bytes of the gather stages.  stats[7]: queries that one launch ran to their end (search_fused.hip).
 __global__ void zero_stats_kernel(int64_t *stats, Ctrl *ctrl, int Q, int keep_stats, int adj_row_bytes,
-                                  int item_row_bytes) {
+                                  int item_row_bytes, int one_launch) {
     if (threadIdx.x < 16 && !keep_stats)
         stats[threadIdx.x] = threadIdx.x == 4 ? Q : threadIdx.x == 5 ? adj_row_bytes : threadIdx.x == 6 ? item_row_bytes : 0;
+    if (threadIdx.x == 7) stats[7] += one_launch;  // the thread that has just cleared it
     if (threadIdx.x < 16) ((int32_t *)ctrl)[threadIdx.x] = 0;
 }
 
@@ -701,10 +702,10 @@ static size_t seed_smem(const ann_graph *g, const Plan &p) {
     return (size_t)((p.E + 3) & ~3) * 4 * (ranked(g, p) ? 2 : 1) + (size_t)dd_n * 16 + (WAVES + 1) * 4;
 }
 
-int launch_zero_stats(const SearchArgs &a) {
+int launch_zero_stats(const SearchArgs &a, int32_t one_launch) {
     const Plan &p = a.plan;
     hipLaunchKernelGGL(zero_stats_kernel, dim3(1), dim3(64), 0, a.stream, (int64_t *)(a.ws + p.off_stats),
-                       (Ctrl *)(a.ws + p.off_ctrl), p.Q, a.keep_stats ? 1 : 0, p.R * 4, item_row_bytes(a.g));
+                       (Ctrl *)(a.ws + p.off_ctrl), p.Q, a.keep_stats ? 1 : 0, p.R * 4, item_row_bytes(a.g), one_launch);
     ANN_HIP_TRY(hipGetLastError());
     return ANN_OK;
 }
@@ -713,7 +714,7 @@ int launch_init(const SearchArgs &a) {
     const Plan &p = a.plan;
     size_t smem = seed_smem(a.g, p);
     int64_t *stats = (int64_t *)(a.ws + p.off_stats);
-    if (int rc = launch_zero_stats(a); rc != ANN_OK) return rc;
+    if (int rc = launch_zero_stats(a, 0); rc != ANN_OK) return rc;
     hipLaunchKernelGGL(init_kernel, dim3(p.Q), dim3(BLOCK), smem, a.stream, a.entries,
                        ranked(a.g, p) ? a.g->rank : nullptr, p.E, a.g->N,
                        (QState *)(a.ws + p.off_state), (uint32_t *)(a.ws + p.off_hash), table_cap_arg(p),

@@ -1,6 +1,7 @@
 """Searches that run as one launch (small batches) against the same searches run stage by stage: id for id, relevance for
 relevance, counter for counter.  Enabling the stage timing selects the separate kernels, whose parity with the oracle
-the other tests hold."""
+the other tests hold.  Every case also says which path it takes: the queries that one launch runs to their end
+are counted in the eighth word of the workspace's counters (at byte 256)."""
 import pytest
 import torch
 
@@ -28,41 +29,65 @@ def _handles(dtype, du, d, hidden, J, N, R, Q, E, seed=3):
     return g, m, users, entries.cuda()
 
 
-def _both(g, m, call, ws):
+def _ended_in_one_launch(ws):
+    torch.cuda.synchronize()
+    return int(ws[256:320].view(torch.int64)[7])
+
+
+def _both(g, m, call, ws, path, overflow=None):
+    """path: "one" = the whole batch in one launch, "staged" = no query, "tail" = the last ones.  overflow: the arrays
+    that a call writes which ends with ANN_EWORKSPACE."""
     runs = []
     for staged in (True, False):
         ann.ann_profile_enable(staged)
         try:
-            ids, sc = call()
+            if overflow is None:
+                ids, sc = call()
+            else:
+                ids, sc = overflow
+                ids.fill_(-7)
+                with pytest.raises(ann.AnnError) as e:
+                    call()
+                assert e.value.code == ann.ANN_EWORKSPACE and "visited table" in str(e.value)
         finally:
             ann.ann_profile_enable(False)
         st = ann.ann_search_stats(ws)
         runs.append((ids.clone(), sc.clone(), (st.pairs_scored, st.nodes_expanded, st.max_query_iters, st.visited_overflow, st.queries)))
-    launches = ann.ann_profile_read()
+        ended = _ended_in_one_launch(ws)
+        if staged or path == "staged":
+            assert ended == 0
+        else:
+            assert ended == st.queries if path == "one" else 0 < ended < st.queries
     assert torch.equal(runs[0][0], runs[1][0])
     assert torch.equal(runs[0][1].view(torch.int32), runs[1][1].view(torch.int32))  # NaN too
     assert runs[0][2] == runs[1][2]
-    return launches
+    return runs[0]
 
 
 SHAPES = [("bf16", 64, 64, (256, 128), 3), ("f16", 128, 128, (512, 256), 4), ("bf16", 64, 64, (256,), 3),
           ("f32", 32, 32, (64,), 3), ("bf16", 13, 20, (48, 24, 16), 2), ("f32", 5, 7, (), 8)]
+# candidates per round (of at most 256 queries) up to which one launch serves them: 110 million operations a CU over the
+# metric's weights without the user's share of layer 1 in its built-in shapes, fp32 counted 32 times
+MOST = {SHAPES[0]: 1110, SHAPES[1]: 278, SHAPES[2]: 3206, SHAPES[3]: 400, SHAPES[4]: 17449, SHAPES[5]: 17903}
 
 
 @pytest.mark.parametrize("visited", ["hash", "bitmap", "rank"])
 @pytest.mark.parametrize("dtype,du,d,hidden,J", SHAPES)
 def test_one_launch_is_the_staged_search(dtype, du, d, hidden, J, visited, monkeypatch):
     """One query and a few; one candidate a round up to several pieces of the filter; more seeds than a piece; odd
-    lists, k above and below L, lists longer than a workgroup; with and without a cap."""
+    lists, k above and below L, lists longer than a workgroup; with and without a cap.  The widest metric and the fp32
+    one take the staged path at 600 candidates and more, and one launch at the sizes just below their lines."""
     monkeypatch.setenv("GMPGR_VISITED_SET", "hash" if visited == "hash" else "bitmap")
     for Q, R, E, W, L, k, cap in [(1, 16, 1, 1, 1, 5, 0), (3, 1, 2, 1, 33, 7, 0), (65, 32, 3, 4, 257, 30, 0),
-                                  (5, 24, 600, 2, 65, 100, 0), (2, 32, 1024, 9, 1500, 11, 0), (17, 17, 4, 37, 300, 20, 6)]:
+                                  (5, 24, 600, 2, 65, 100, 0), (2, 32, 1024, 9, 1500, 11, 0), (17, 17, 4, 37, 300, 20, 6),
+                                  (5, 24, 278, 2, 65, 100, 0), (2, 32, 277, 8, 1500, 11, 0), (17, 17, 4, 16, 300, 20, 6)]:
         g, m, users, entries = _handles(dtype, du, d, hidden, J, 3001, R, Q, E)
         if visited == "rank":
             rank = torch.randperm(3001, generator=torch.Generator().manual_seed(1)).to(torch.int32).cuda()
             ann.ann_graph_set_locality(g, rank)
         ws = torch.empty(ann.ann_search_workspace_bytes(g, m, Q, E, W, L, k, cap), dtype=torch.uint8, device="cuda")
-        _both(g, m, lambda: ann.ann_search(g, m, users, entries, W, L, k, cap, workspace=ws), ws)
+        path = "one" if max(W * R, E) <= MOST[dtype, du, d, hidden, J] else "staged"
+        _both(g, m, lambda: ann.ann_search(g, m, users, entries, W, L, k, cap, workspace=ws), ws, path)
 
 
 @pytest.mark.parametrize("Q", [256, 257, 512, 513, 1024, 1025])
@@ -73,7 +98,8 @@ def test_batch_sizes_around_the_lines(dtype, du, d, hidden, J, Q):
     gen = torch.Generator().manual_seed(Q)
     own = [torch.randint(lo, hi, (Q,), generator=gen, dtype=torch.int32).cuda() for lo, hi in ((0, 10), (0, 140), (0, 30))]
     ws = torch.empty(ann.ann_search_workspace_bytes(g, m, Q, 4, 8, 128, 20, 24), dtype=torch.uint8, device="cuda")
-    _both(g, m, lambda: ann.ann_search_ragged(g, m, users, entries, *own, 8, 128, 20, 24, workspace=ws), ws)
+    _both(g, m, lambda: ann.ann_search_ragged(g, m, users, entries, *own, 8, 128, 20, 24, workspace=ws), ws,
+          "one" if Q <= (1024 if dtype == "bf16" else 768) else "staged")
 
 
 @pytest.mark.parametrize("dtype,du,d,hidden,J", SHAPES[:4])
@@ -84,14 +110,16 @@ def test_items_that_are_not_finite(dtype, du, d, hidden, J):
     emb[::9, 1], emb[3::11, 0], emb[5::13, 2] = float("inf"), float("-inf"), float("nan")
     g = ann.ann_graph_load(torch.randint(0, 400, (400, 16), dtype=torch.int32).cuda(), emb.cuda())
     ws = torch.empty(ann.ann_search_workspace_bytes(g, m, 9, 8, 4, 64, 200, 0), dtype=torch.uint8, device="cuda")
-    _both(g, m, lambda: ann.ann_search(g, m, users, entries, 4, 64, 200, 0, workspace=ws), ws)
+    _both(g, m, lambda: ann.ann_search(g, m, users, entries, 4, 64, 200, 0, workspace=ws), ws, "one")
 
 
 @pytest.mark.parametrize("visited", ["hash", "bitmap"])
 @pytest.mark.parametrize("dtype,du,d,hidden,J", SHAPES[:4])
 def test_last_queries_of_a_large_batch(dtype, du, d, hidden, J, visited, monkeypatch):
     """A batch too large for one launch ends in one: the list, the state and the survivors move over in the middle of
-    the search.  Lists of very different lengths, so that a few queries run long after the others; also through slots."""
+    the search.  Lists of very different lengths, so that a few queries run long after the others (the enqueuing thread
+    is at most four rounds ahead of the device and sees that few are left); also through slots, where six of seven
+    queries have no valid seed and end at once."""
     monkeypatch.setenv("GMPGR_VISITED_SET", visited)
     Q, R, E, W, L, k = 1400, 16, 3, 4, 301, 40
     g, m, users, entries = _handles(dtype, du, d, hidden, J, 4001, R, Q, E)
@@ -99,11 +127,18 @@ def test_last_queries_of_a_large_batch(dtype, du, d, hidden, J, visited, monkeyp
     own[1][::11] = L
     own = [o.cuda() for o in own]
     ws = torch.empty(ann.ann_search_workspace_bytes(g, m, Q, E, W, L, k, 0), dtype=torch.uint8, device="cuda")
-    _both(g, m, lambda: ann.ann_search_ragged(g, m, users, entries, *own, W, L, k, 0, workspace=ws), ws)
-    want = ann.ann_search(g, m, users, entries, W, 60, k, 0)
-    for slots in (1100, 70):
-        ids, sc = ann.ann_search_stream(g, m, users, entries, slots, W, 60, k)
-        assert torch.equal(ids, want[0]) and torch.equal(sc, want[1])
+    _both(g, m, lambda: ann.ann_search_ragged(g, m, users, entries, *own, W, L, k, 0, workspace=ws), ws,
+          "tail")
+    few = entries.clone()
+    few[torch.arange(Q, device="cuda") % 7 != 0] = -1
+    for seeds in (entries, few):
+        want = ann.ann_search(g, m, users, seeds, W, 60, k, 0)
+        for slots in (1100, 70):
+            ws = torch.empty(ann.ann_search_stream_workspace_bytes(g, m, Q, slots, E, W, 60, k, 0), dtype=torch.uint8, device="cuda")
+            ids, sc = ann.ann_search_stream(g, m, users, seeds, slots, W, 60, k, workspace=ws)
+            assert torch.equal(ids, want[0]) and torch.equal(sc, want[1])
+            if seeds is few or slots == 70:
+                assert 0 < _ended_in_one_launch(ws) < Q
 
 
 def slow_rounds(W):
