@@ -36,7 +36,7 @@ def _ended_in_one_launch(ws):
 
 def _both(g, m, call, ws, path, overflow=None):
     """path: "one" = the whole batch in one launch, "staged" = no query, "tail" = the last ones.  overflow: the arrays
-    that a call writes which ends with ANN_EWORKSPACE."""
+    that a call writes which ends with ANN_EWORKSPACE (-5)."""
     runs = []
     for staged in (True, False):
         ann.ann_profile_enable(staged)
@@ -48,7 +48,7 @@ def _both(g, m, call, ws, path, overflow=None):
                 ids.fill_(-7)
                 with pytest.raises(ann.AnnError) as e:
                     call()
-                assert e.value.code == ann.ANN_EWORKSPACE and "visited table" in str(e.value)
+                assert e.value.code == -5 and "visited table" in str(e.value)
         finally:
             ann.ann_profile_enable(False)
         st = ann.ann_search_stats(ws)
@@ -174,3 +174,44 @@ def test_a_search_in_one_launch_reports_its_progress():
         ann.ann_set_progress_timeout(600.0)
         torch.cuda.synchronize()
     assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+
+
+def _rising(dtype, N, R, Q):
+    """Items whose relevance rises with their id, every item joined to the next R: a search with a list of one entry goes
+    on to the last item and scores all of them.  id / 64 and id % 64 are the item's two coordinates (exact in 16 bits)."""
+    i = torch.arange(N, device="cuda")
+    emb = torch.stack([(i // 64).float(), (i % 64).float()], 1).to(TORCH[dtype])
+    adj = i[:, None] + 1 + torch.arange(R, device="cuda")
+    adj = torch.where(adj < N, adj, -1).int()
+    w = torch.tensor([[0.0, 2.0 ** -4, 2.0 ** -10]]).to(TORCH[dtype])
+    m = ann.ann_mlp_load([w], [torch.tensor([-4.0])], torch.ones(1), 1, ANN[dtype])
+    return ann.ann_graph_load(adj, emb), m, torch.zeros(Q, 1, device="cuda").to(TORCH[dtype])
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+@pytest.mark.parametrize("Q", [5, 1400])
+def test_visited_table_that_fills_up(dtype, Q, monkeypatch):
+    """A table of 2,048 slots (34 assumed rounds of 16 ids) takes 1,024 ids: queries that start far from the last item stop
+    when it is full, in the one launch of a small batch, in the one that ends a large batch, and in a slot that the next
+    query takes.  Same error, results and counters as stage by stage."""
+    monkeypatch.setenv("GMPGR_VISITED_SET", "hash")
+    N, R, k = 8000, 16, 3
+    g, m, users = _rising(dtype, N, R, Q)
+    start = torch.full((Q,), N - 30, dtype=torch.int32)        # two rounds to the last item ...
+    if Q == 5:
+        start[:4] = torch.tensor([0, N - 1010, N - 1009, N - 1008])
+    else:
+        start[::10] = torch.linspace(0, N - 100, Q // 10).int()
+    entries = start[:, None].contiguous().cuda()
+    ws = torch.empty(ann.ann_search_workspace_bytes(g, m, Q, 1, 1, 1, k, 0), dtype=torch.uint8, device="cuda")
+    out = torch.empty(Q, k, dtype=torch.int32, device="cuda"), torch.empty(Q, k, device="cuda")
+    call = lambda: ann.ann_search(g, m, users, entries, 1, 1, k, 0, workspace=ws, out_ids=out[0], out_scores=out[1])
+    ids, sc, counters = _both(g, m, call, ws, "one" if Q == 5 else "tail", overflow=out)
+    # 16 ids a round: 1 + 16 * 63 fit, 16 more do not
+    assert torch.equal(ids[:, 0].cpu(), (start + 16 * 63).clamp(max=N - 1))
+    assert counters[3] == int((start + 16 * 63 <= N - 1).sum()) > 0
+    if Q > 5:
+        ws = torch.empty(ann.ann_search_stream_workspace_bytes(g, m, Q, 300, 1, 1, 1, k, 0), dtype=torch.uint8, device="cuda")
+        call = lambda: ann.ann_search_stream(g, m, users, entries, 300, 1, 1, k, workspace=ws, out_ids=out[0], out_scores=out[1])
+        streamed = _both(g, m, call, ws, "tail", overflow=out)
+        assert torch.equal(streamed[0], ids) and torch.equal(streamed[1], sc) and streamed[2] == counters
