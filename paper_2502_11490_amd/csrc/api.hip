@@ -1,6 +1,6 @@
 // C ABI of the library (include/gmpgr_ann.h): argument checks, handles, workspace plan and
-// the host side of the round loop.  Every step of the search runs in the kernels of
-// search_kernels.hip, mlp_alu.hip and mlp_mfma.hip; nothing here computes a score or a rank.
+// the host side of the round loop.  Every step of the search runs in the kernels of search_kernels.hip,
+// search_fused.hip and the mlp_*.hip files; nothing here computes a score or a rank.
 #include <stdarg.h>
 #include <stdio.h>
 #include <stdlib.h>

@@ -3,9 +3,10 @@
 // This is the path for metrics loaded with ANN_MLP_GENERIC and for layers too wide for the matrix-core
 // kernels (mlp_any.hip: activations of 32 pairs, fp32 16, in LDS).
 // A workgroup takes one batch of T pairs from the dense pair list (the fixed-size batch of
-// Algorithm 2), keeps the activations of the whole batch in LDS and walks the layers; a thread owns one pair and a strided set of output units, so a weight is
-// read once per wave (all lanes of a wave share the output unit) and the activations are
-// read from LDS with an odd row stride (no bank conflicts).
+// Algorithm 2), keeps the activations of the whole batch in LDS and walks the layers; a thread
+// owns one pair and a strided set of output units, so a weight is read once per wave (all lanes
+// of a wave share the output unit) and the activations are read from LDS with an odd row stride
+// (no bank conflicts).
 //
 // Numerics, fp32 mode: x = concat(user, item) (Eq. 5); every layer is a sequential FMA chain
 // over the inputs in index order (Eq. 7) carried in fp64 (the vector ALUs run fp64 at half the

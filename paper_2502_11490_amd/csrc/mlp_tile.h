@@ -52,12 +52,12 @@ __device__ __forceinline__ uint4 tile_relu(const f32x16 &acc, int half) {
 }
 
 // acc[c] += W-block * slabs of column block c, over KS inputs-of-16.  `w` points at this lane's 16 bytes of the
-// block's first fragment; fragment k lies (k >> 1) * step2 + (k & 1) fragments behind it (KS is even).  DEPTH
-// fragments are in flight.
-template <bool F16, int CB, int DEPTH = 4>
+// block's first fragment; fragment k lies (k >> 1) * step2 + (k & 1) fragments behind it (KS is even).
+template <bool F16, int CB>
 __device__ __forceinline__ void tile_contract(f32x16 (&acc)[CB], const uint4 *__restrict__ w, int step2, int KS,
                                               const uint4 *in, int in_slabs) {
     const int lane = threadIdx.x & 63;
+    constexpr int DEPTH = 4;  // fragments in flight; 8 lost more by their registers than they hid (1,024 queries 6.1 -> 8.5 ms)
     uint4 a[DEPTH];
 #pragma unroll
     for (int u = 0; u < DEPTH; ++u) {
@@ -85,7 +85,7 @@ __device__ __forceinline__ void tile_contract(f32x16 (&acc)[CB], const uint4 *__
 // A hidden layer of the tile: NB blocks of 32 units over the workgroup's waves.  init[unit]: what a unit's sum starts
 // from.  out: 2 NB slabs per column block, unit 32 nb + 16 s2 + 8 (j / 4) + 4 g + j % 4 at byte j of lane (m, g) of
 // slab 2 nb + s2 (the D layout of the instruction as it comes; the next layer's weights are stored to match).
-template <bool F16, bool INT_RELU, int CB, int DEPTH = 4>
+template <bool F16, bool INT_RELU, int CB>
 __device__ __forceinline__ void tile_hidden(const uint4 *__restrict__ frag, int64_t base, int stride_n, int step2, int KS,
                                             int NB, const float *init, const uint4 *in, int in_slabs, uint4 *out,
                                             int out_slabs, int n_waves) {
@@ -100,7 +100,7 @@ __device__ __forceinline__ void tile_hidden(const uint4 *__restrict__ frag, int6
 #pragma unroll
                 for (int e = 0; e < 4; ++e) acc[c][4 * t4 + e] = v[e];
         }
-        tile_contract<F16, CB, DEPTH>(acc, frag + (base + (int64_t)nb * stride_n) * 64 + lane, step2, KS, in, in_slabs);
+        tile_contract<F16, CB>(acc, frag + (base + (int64_t)nb * stride_n) * 64 + lane, step2, KS, in, in_slabs);
 #pragma unroll
         for (int c = 0; c < CB; ++c) {
             out[((size_t)c * out_slabs + 2 * nb) * 64 + lane] = tile_relu<F16, INT_RELU>(acc[c], 0);

@@ -76,7 +76,7 @@ extern "C" int ann_score_pairs_noalloc(const ann_graph *g, const ann_mlp *m, con
         return ANN_EINVAL;
     }
     hipStream_t s = (hipStream_t)stream;
-    if (m->kernel != MLP_MFMA2)  // the plain ALU kernels take the count as an argument and need no user term
+    if (m->kernel != MLP_MFMA2)  // the kernels for any widths take the count as an argument and need no user term
         return launch_mlp_alu(g, m, queries_dev, q_idx_dev, item_dev, nullptr, M, Q, out_dev, 0, s);
     const size_t need = (size_t)Q * (size_t)m->dims[1];
     if (need > SCRATCH_UPRE_FLOATS) {
