@@ -21,9 +21,11 @@
 // eight waves (two per SIMD, 256 registers each) so that one wave's item-row gather and
 // conversions overlap the other's MFMAs.
 //
-// All weights are loaded into LDS once per launch and stay.  Handing out 64 pairs a wave over all workgroups, with the
-// weight loads under the trip for the pair ids, against 512 pairs a workgroup and the weights first: a launch with few
-// pairs 17 -> 11 us, the 65 rounds of 8,192 ragged queries 65 -> 59 us on average, the longest lists 222 -> 217.
+// All weights are loaded into LDS once per launch and stay.  Two things matter to lists that do not fill the chip, each
+// measured with the other in place (8,192 ragged queries; 2,048 queries with lists of 256): 64 pairs a wave handed out
+// over all workgroups, against 512 a workgroup, 7.57 -> 7.34 and 6.73 -> 6.29 ms; the weight loads in flight together
+// under the trip for the pair ids, against a loop in front of it, 7.51 -> 7.32 and 6.50 -> 6.29.  Together a launch with
+// few pairs 17 -> 11 us, the searches 7.73 -> 7.36 and 6.98 -> 6.30 ms.
 //
 // Numerics (bf16 mode of the library): bf16 inputs and weights, fp32 accumulation inside the
 // MFMA, hidden activations rounded to bf16 (nearest even) after ReLU, head logits, sigmoid
@@ -314,11 +316,13 @@ mlp_mfma2_kernel(const uint16_t *__restrict__ emb, int64_t N, const float *__res
 // without the middle layer.  Per block of 32 hidden units: layer 1 from the user term, ReLU,
 // bf16, and at once the two head MFMAs that consume those units; nothing but 2 x 16 head
 // accumulators lives across blocks.  All weights (D/16 + 2 fragments per block) stay in LDS.
-// (Handing out single waves' worths as above, with the rows fetched one batch ahead, made this kernel a fifth slower:
-// 96 registers instead of 80, and a query's user terms read by several CUs.)
-// The kernel is bound by the item-row gather, not by the MFMAs (about 250 flop per gathered
-// byte, below the ridge of the chip), so its few registers and 48 KB of LDS are what matter:
-// three workgroups share a CU and hide each other's gather latency.
+// (Handing out single waves' worths as above together with rows fetched one batch ahead made this kernel a fifth
+// slower: 96 registers instead of 80, and a query's user terms read by several CUs.  The two, and the weight loads of the
+// kernel above, have not been tried apart.)
+// What bounds it is the chain of a block of units (user terms from memory, MFMAs, ReLU and packing, head MFMAs), of
+// which a batch runs eight one after the other, with three workgroups a CU to fill the waits.  1,200,000 pairs of 16,384
+// users and 20 million items take 83 us, 14 G pairs/s; with every user term read from one row 77, with the item rows in
+// the cache 79, with both 71, and the matrix instructions alone are 23.
 // Fragment order: block nb: [s < D/16] W1_item as above; [D/16 + s2] lane (m,g):
 // W_head[m][nb*32 + 16*s2 + 8*(j/4) + 4g + j%4], rows >= J zero.
 template <int D, int H1, int CB, bool F16>

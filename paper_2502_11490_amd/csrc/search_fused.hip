@@ -8,8 +8,10 @@
 // the weights come from L2 in fragment order (mlp_tile.h), and queries do not wait for one another.
 //
 // What bounds it: the chain of a round (adjacency row, visited words, item rows, weights: five trips to memory or L2
-// and about twenty barriers), hidden only by the other workgroups of the CU.  The weights are read once per tile of
-// pairs and query, so a full batch belongs to the batch path; fused_plan has the line and both sides.
+// and about twenty barriers), hidden only by the other workgroups of the CU.  Shares of a round by clock stamps: gather
+// and filter 18 to 30 %, scoring 45 to 68 (its weights come from L2 once per tile), new keys and their sort 5 to 10, the
+// merge 6 (19 for lists of 4,096, all of which it rewrites), the choice of parents 3 to 7.  A full batch belongs to the
+// batch path; fused_plan has the line and both sides.
 //
 // Measured against the batch path: one query on a million items (lists of 64) 0.88 -> 0.46 ms, 64 fp32 queries with
 // lists of 32 and 4,096 0.78 -> 0.33 and 7.9 -> 4.2 ms, 1,024 queries with lists of 512 8.4 -> 6.1 ms.
@@ -444,16 +446,21 @@ static int fused_launch(const SearchArgs &a, const FusedArgs &A, size_t smem) {
     return ANN_OK;
 }
 
-// Which searches run here, and with what workgroups.  Both sides measured, batch path -> this one:
+// Which searches run here, and with what workgroups.  Both sides measured, batch path (beyond 512 queries with its last
+// queries in one launch) -> this one, lists of L, W nodes a round, 32 candidates a node:
 //   - the whole batch is resident at once (a second turn of workgroups would start when the batch path is half
-//     done): 2,048 queries of 64 -> 256 -> 128 9.5 -> 9.8 ms, 4,096 of 64 -> 256 3.6 -> 4.2; 1,024 of either
-//     8.4 -> 6.1 and 2.2 -> 1.4;
+//     done).  64 -> 256 -> 128, 2,048 queries, W = 4, L = 256 6.4 -> 7.5 ms; 1,024 queries, W = 4, L = 64 1.9 -> 1.6,
+//     L = 256 4.9 -> 4.9, L = 512 7.1 -> 6.2, W = 8, L = 512 5.4 -> 5.5, W = 1, L = 256 12.3 -> 7.6; 512 queries,
+//     W = 4, L = 256 4.8 -> 3.2, W = 8, L = 512 4.5 -> 3.4.  64 -> 256, W = 4, L = 64: 2,048 queries 2.24 -> 2.25, 1,024
+//     1.8 -> 1.4;
 //   - a round's matrix work per CU stays small, at most FUSED_WORK operations (fp64 ones count 32 times), since a
-//     query's pairs are scored by one CU while the batch path spreads them over the chip: 128 -> 512 -> 256 with 256
-//     candidates a round (0.10 GFLOP) 2.16 -> 1.82 ms for one query, 5.0 -> 4.4 for 64; with 512 3.9 -> 4.4; with
-//     1,024 3.2 -> 7.0;
+//     query's pairs are scored by one CU while the batch path spreads them over the chip.  128 -> 512 -> 256, 64 queries,
+//     W = 8 (0.10 GFLOP) 5.1 -> 4.2 ms, W = 16 5.2 -> 5.8; 256 queries, W = 8 6.2 -> 5.0, and W = 16, beyond the line,
+//     8.2 -> 6.5 as well.  fp32 32 -> 64, 16 candidates a node: 64 queries, W = 16, L = 4,096 9.3 -> 6.4, and 1,024
+//     queries, W = 8, L = 512, beyond the line, 4.3 -> 3.4;
 //   - tiles of a single column block read all weights from L2 for 32 pairs: with more than one workgroup on a CU only
-//     for weights of at most FUSED_WEIGHTS bytes (512 queries of the widest metric 5.7 -> 6.0 ms).
+//     for weights of at most FUSED_WEIGHTS bytes (512 queries of the widest metric, W = 4 7.1 -> 8.6 ms; with W = 1,
+//     where a round is mostly launches, 18.7 -> 12.1).
 // The largest tile that leaves every query resident wins (fewer passes over the weights; 256 queries of 64 -> 256 -> 128
 // 2.1 ms at 128 pairs, 2.6 at 64, 3.2 at 32), and 512 threads over 256 wherever two such workgroups suffice.
 constexpr int64_t FUSED_WORK = 110 * 1000000, FUSED_WEIGHTS = 128 * 1024;
