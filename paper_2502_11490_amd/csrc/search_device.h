@@ -55,6 +55,9 @@ __device__ void rank_sort(uint64_t *keys, int m, uint32_t *cnt) {
     __syncthreads();
 }
 
+// The visited filters of the walkers, which need the first of equal candidates to win: whose neighbour it is decides where a
+// walker goes next.
+//
 // Drops ids that are out of range, repeated inside cand[0..n_cand) (first occurrence kept)
 // or already in this query's visited table; inserts the rest into the table and writes them,
 // in their order of occurrence, to out[0..n_new).  Returns n_new (same in every thread).
@@ -67,8 +70,7 @@ __device__ void rank_sort(uint64_t *keys, int m, uint32_t *cnt) {
 //                   bucket or, if that one is full, in the next ones up to the first bucket that
 //                   is not full.  The caller guarantees n_visited + n_cand <= hash_cap / 2.
 //
-// The table of a query is touched by one workgroup only, so it needs no global atomics (they
-// cost three times a plain access here): every candidate reads its whole bucket once (one line),
+// The table of a query is touched by one workgroup only, so it needs no global atomics: every candidate reads its whole bucket once (one line),
 // decides "seen / room / full" from that snapshot, and the candidates that arrive at the same
 // bucket in the same pass take consecutive free slots by a rank drawn from an LDS counter.
 // Stores of a pass become visible to the next pass through a workgroup-scope fence + barrier.
@@ -277,6 +279,131 @@ __device__ int filter_and_mark(const int32_t *cand, const int32_t *cand_rank, in
         }
     }
     return n_new;
+}
+
+// The visited set of a search without walkers: enters the candidates v[u] that are in range and new to the query;
+// fresh[u] says which.  One atomic per candidate decides "seen", "repeated in this round" and "new" at once: of equal
+// candidates exactly one finds the id absent, whichever it is (what a search returns does not depend on the order of its
+// survivors).  The UNROLL atomics of a thread are in flight together.
+//   at[u] : BITMAP: the bit that stands for the candidate; else scratch
+//   table : BITMAP: one bit per item; else hash_cap slots of one id each, EMPTY_SLOT = free, an id lies in the first free
+//           slot from its home on.  The caller guarantees n_visited + n_cand <= hash_cap / 2.
+//   PEEK  : the word is read first, and the atomic left out where it shows the id, or another one in its slot: an atomic
+//           makes its line dirty whatever it finds, and full batches are bound by that traffic.  (What was read may be
+//           older than the set; it only ever grows, so the atomic has the last word.)
+// A query's set belongs to one workgroup, so the atomics need no more than workgroup scope: they are carried out in
+// the L2 slice, like a load or a store.  (At device scope, the default of atomicCAS, they go to the memory side and
+// cost several times as much.)
+// Against the filters below, which sort out repetitions in LDS tables first (five barriers, 16 KB of tables for 512
+// candidates, 64-byte buckets read whole): one query in one launch 473 -> 412 us, 64 fp32 queries 335 -> 270 us (lists of
+// 4,096: 4.18 -> 3.63 ms).  In full batches, with PEEK: 2,048 8-bit queries with lists of 2,048 29.7 -> 28.3 ms, 6,001 fp16
+// queries in slots 30.0 -> 29.1, 8,192 ragged ones 7.39 -> 7.05; without it 31.9, 29.7 and 7.50, and 16,384 queries of a
+// table of 20 million items 8.8 ms where they take 8.05 with it.
+//   meanwhile(u, v, may_be_new) : called once per candidate v while the atomics travel
+template <bool BITMAP, bool PEEK, int UNROLL, class Meanwhile>
+__device__ __forceinline__ void visited_enter(const int32_t (&v)[UNROLL], uint32_t (&at)[UNROLL], bool (&fresh)[UNROLL],
+                                              uint32_t *table, int hash_cap, int64_t N, Meanwhile meanwhile) {
+    uint32_t old[UNROLL];
+#pragma unroll
+    for (int u = 0; u < UNROLL; ++u) {
+        fresh[u] = v[u] >= 0 && (int64_t)v[u] < N;
+        old[u] = BITMAP ? 0u : EMPTY_SLOT;
+        if (!BITMAP) at[u] = __umulhi(hash_id((uint32_t)v[u]), (uint32_t)hash_cap);
+        if (PEEK && fresh[u]) old[u] = table[BITMAP ? at[u] >> 5 : at[u]];
+    }
+    if (BITMAP) {
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u) {
+            const uint32_t bit = 1u << (at[u] & 31);
+            fresh[u] = fresh[u] && !(old[u] & bit);
+            if (fresh[u]) old[u] = __hip_atomic_fetch_or(&table[at[u] >> 5], bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u) meanwhile(u, v[u], fresh[u]);
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u) fresh[u] = fresh[u] && !((old[u] >> (at[u] & 31)) & 1u);
+        return;
+    }
+    bool maybe[UNROLL];
+#pragma unroll
+    for (int u = 0; u < UNROLL; ++u) maybe[u] = fresh[u] && old[u] != (uint32_t)v[u];
+#pragma unroll
+    for (int u = 0; u < UNROLL; ++u)
+        if (fresh[u] && old[u] == EMPTY_SLOT)
+            __hip_atomic_compare_exchange_strong(&table[at[u]], &old[u], (uint32_t)v[u], __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_WORKGROUP);
+#pragma unroll
+    for (int u = 0; u < UNROLL; ++u) meanwhile(u, v[u], maybe[u]);
+#pragma unroll
+    for (int u = 0; u < UNROLL; ++u) {
+        // another id in the slot: on to the next one.  Ends: at least half of the slots are free
+        bool open = fresh[u] && old[u] != EMPTY_SLOT && old[u] != (uint32_t)v[u];
+        fresh[u] = fresh[u] && old[u] == EMPTY_SLOT;
+        while (open) {
+            at[u] = at[u] + 1 == (uint32_t)hash_cap ? 0u : at[u] + 1;
+            uint32_t seen = EMPTY_SLOT;
+            if (PEEK) seen = table[at[u]];
+            if (seen == EMPTY_SLOT)
+                __hip_atomic_compare_exchange_strong(&table[at[u]], &seen, (uint32_t)v[u], __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_WORKGROUP);
+            fresh[u] = seen == EMPTY_SLOT;
+            open = !fresh[u] && seen != (uint32_t)v[u];
+        }
+    }
+}
+
+struct Nothing {
+    __device__ __forceinline__ void operator()(int, int32_t, bool) const {}
+};
+
+// The same for a workgroup: new candidates to out[0..n_new) in candidate order.  Returns n_new (same in every thread).
+//   candidate(p, &bit) : the id of candidate p (p < n_cand) and, with a bitmap, the bit that stands for it
+template <int BLK, bool BITMAP, bool PEEK, int UNROLL, class Candidate, class Meanwhile>
+__device__ __forceinline__ int visit(Candidate candidate, int n_cand, uint32_t *table, int hash_cap, int64_t N,
+                                     int32_t *out, int *wave_sums, Meanwhile meanwhile) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int n_new = 0;
+    for (int p0 = 0; p0 < n_cand; p0 += BLK * UNROLL) {
+        const int per = min(UNROLL, (n_cand - p0 + BLK - 1) / BLK);  // candidates of a wave follow one another
+        int32_t v[UNROLL];
+        uint32_t at[UNROLL];
+        bool fresh[UNROLL];
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u) {
+            const int p = p0 + (wave * per + u) * 64 + lane;
+            v[u] = -1;
+            at[u] = 0;
+            if (u < per && p < n_cand) v[u] = candidate(p, &at[u]);
+        }
+        visited_enter<BITMAP, PEEK, UNROLL>(v, at, fresh, table, hash_cap, N, meanwhile);
+        int mine = 0, before = 0, total = 0;
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u) mine += __popcll(__ballot(fresh[u]));
+        if (lane == 0) wave_sums[wave] = mine;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < BLK / 64; ++w) {
+            const int c = wave_sums[w];
+            if (w < wave) before += c;
+            total += c;
+        }
+        __syncthreads();
+        int32_t *to = out + n_new + before;
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u) {
+            const unsigned long long b = __ballot(fresh[u]);
+            if (fresh[u]) to[__popcll(b & ((1ull << lane) - 1ull))] = v[u];
+            to += __popcll(b);
+        }
+        n_new += total;
+    }
+    return n_new;
+}
+
+// A table is filled by plain stores, then used by the atomics above, in one kernel: the stores have arrived.
+__device__ __forceinline__ void visited_cleared() {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
 }
 
 // A query's counters join the totals once, when its result is written: every workgroup adding to the

@@ -43,7 +43,7 @@ struct FusedArgs {
     int32_t *counts;
     const int32_t *cand, *slot_query;
     int64_t N;
-    int32_t R, E, W, L, cap, W_max, L_max, cap_max, C, k, slots, new_cap, chunk, table_words, hash_cap, Q, rounds_max;
+    int32_t R, E, W, L, cap, W_max, L_max, cap_max, C, k, slots, new_cap, table_words, hash_cap, Q, rounds_max;
     int32_t wide_loads, int_relu;
 };
 
@@ -167,16 +167,11 @@ __device__ __forceinline__ void fused_score64(const FusedArgs &A, int q, const i
 }
 
 // LDS, in bytes: the list twice, the survivors' ids and scores, the parents, the small words, and one region used in
-// turn by the filter, the scoring and the sort.
+// turn by the scoring and the sort.
 struct FusedLds {
     size_t surv, sc, parents, small, scratch;
 };
 __host__ __device__ inline size_t up16(size_t v) { return (v + 15) & ~(size_t)15; }
-static inline int fused_dd(int chunk) {
-    int dd_n = 2;
-    while (dd_n < 2 * chunk) dd_n <<= 1;
-    return dd_n;
-}
 __host__ __device__ inline void fused_lds(int C, int slots, int W_max, FusedLds *o) {
     o->surv = up16((size_t)16 * C);
     o->sc = up16(o->surv + (size_t)4 * slots);
@@ -199,13 +194,7 @@ __global__ void __launch_bounds__(BLK) fused_search_kernel(FusedArgs A) {
     int32_t *parents = (int32_t *)(smem + at.parents);
     int *wave_sums = (int *)(smem + at.small), *shared_i = wave_sums + 16;
     unsigned char *scratch = smem + at.scratch;
-    // the scratch region in its three roles
-    int32_t *cand = (int32_t *)scratch;
-    int32_t *cand_rank = (BITMAP && A.adj_rank) ? cand + ((A.chunk + 3) & ~3) : nullptr;
-    uint32_t *dd_key = (uint32_t *)(cand + (cand_rank ? 2 : 1) * ((A.chunk + 3) & ~3));
-    int dd_n = 2;
-    while (dd_n < 2 * A.chunk) dd_n <<= 1;
-    uint32_t *dd_pos = dd_key + dd_n, *bk_key = dd_pos + dd_n, *bk_cnt = bk_key + dd_n;
+    // the scratch region in its two roles (the other is the scoring's)
     uint64_t *newk = (uint64_t *)scratch;
     uint32_t *sort_cnt = (uint32_t *)(newk + A.new_cap);
 
@@ -232,43 +221,28 @@ __global__ void __launch_bounds__(BLK) fused_search_kernel(FusedArgs A) {
     if (!RESUME) {
         const uint32_t e = BITMAP ? 0u : EMPTY_SLOT;
         for (int i = tid; i < A.table_words / 4; i += BLK) ((uint4 *)table)[i] = make_uint4(e, e, e, e);
-        __threadfence_block();
-        __syncthreads();
+        visited_cleared();
     }
     bool seeding = true, overflow = false;
     // bounded: a search cannot run more rounds than its cap or than ids fit its visited set
     for (int round = 0; round <= A.rounds_max; ++round) {
-        // candidates (the seeds, later one adjacency row per parent) through the visited filter, piece by piece
-        int n_new = 0;
-        for (int c0 = 0; c0 < n_cand; c0 += A.chunk) {
-            const int nc = min(A.chunk, n_cand - c0);
-            if (c0 > 0) {  // the table stores of the piece before must be seen by this piece's reads
-                __threadfence_block();
-                __syncthreads();
+        // candidates (the seeds, later one adjacency row per parent) through the visited filter
+        auto candidate = [&](int j, uint32_t *bit) {
+            int32_t v;
+            if (seeding) {
+                v = A.entries[(size_t)q * A.E + j];
+                if (BITMAP) *bit = A.rank && v >= 0 && (int64_t)v < A.N ? (uint32_t)A.rank[v] : (uint32_t)v;
+            } else {
+                const int p = j / A.R;
+                const size_t from = (size_t)parents[p] * A.R + (j - p * A.R);
+                v = A.adj[from];
+                if (BITMAP) *bit = (uint32_t)(A.adj_rank ? A.adj_rank[from] : v);
             }
-            for (int j = tid; j < nc; j += BLK) {
-                if (seeding) {
-                    const int32_t v = A.entries[(size_t)q * A.E + c0 + j];
-                    cand[j] = v;
-                    if (BITMAP && cand_rank) cand_rank[j] = (v >= 0 && (int64_t)v < A.N) ? A.rank[v] : -1;
-                } else {
-                    const int p = (c0 + j) / A.R, s = (c0 + j) - p * A.R;
-                    const size_t from = (size_t)parents[p] * A.R + s;
-                    cand[j] = A.adj[from];
-                    if (BITMAP && cand_rank) cand_rank[j] = A.adj_rank[from];
-                }
-            }
-            __syncthreads();
-            if (BITMAP)
-                n_new += filter_and_mark<BLK>(cand, cand_rank, nc, dd_key, dd_pos, bk_key, bk_cnt, dd_n, table, A.N,
-                                              surv + n_new, wave_sums, nullptr, 1, 0);
-            else
-                n_new += filter_and_insert<BLK>(cand, nc, dd_key, dd_pos, bk_key, bk_cnt, dd_n, table, A.hash_cap, A.N,
-                                                surv + n_new, wave_sums, nullptr, 1);
-        }
+            return v;
+        };
+        int n_new = visit<BLK, BITMAP, false, 2>(candidate, n_cand, table, A.hash_cap, A.N, surv, wave_sums, Nothing{});
         n_visited += n_new;
         if (RESUME && round == 0) n_new = pending;  // counted by the round that found them
-        __threadfence_block();  // the table's stores, for the next round's reads
         if (tid == 0) shared_i[0] = 0x7fffffff;  // rank of the first inserted entry
         __syncthreads();
 
@@ -423,16 +397,12 @@ static void built_in_net(const ann_mlp *m, TileNet *T) {
     T->base[2] = (int64_t)(NB1 + skew) * chunk;
 }
 
-static size_t fused_smem(const SearchArgs &a, const TileNet &T, bool f64, int cb, int chunk, int new_cap, int blk) {
+static size_t fused_smem(const SearchArgs &a, const TileNet &T, bool f64, int cb, int new_cap, int blk) {
     FusedLds at;
     fused_lds(a.plan.C, a.plan.slots, a.plan.W_max, &at);
-    const bool ranked = a.plan.bitmap_words > 0 && a.g->adj_rank;
-    const size_t filter = (size_t)((chunk + 3) & ~3) * 4 * (ranked ? 2 : 1) + (size_t)fused_dd(chunk) * 16;
     const size_t sort = (size_t)new_cap * 8 + (size_t)blk * 4;
     const size_t net = (size_t)cb * (T.slabs[0] + T.slabs[1]) * (f64 ? 2048 : 1024);
-    size_t most = filter > sort ? filter : sort;
-    if (net > most) most = net;
-    return at.scratch + most;
+    return at.scratch + (net > sort ? net : sort);
 }
 
 template <int BLK, int METRIC, int CB, bool RESUME>
@@ -465,7 +435,7 @@ static int fused_launch(const SearchArgs &a, const FusedArgs &A, size_t smem) {
 // 2.1 ms at 128 pairs, 2.6 at 64, 3.2 at 32), and 512 threads over 256 wherever two such workgroups suffice.
 constexpr int64_t FUSED_WORK = 110 * 1000000, FUSED_WEIGHTS = 128 * 1024;
 
-static bool fused_plan(const SearchArgs &a, int Q, TileNet *T, int *blk, int *cb, int *chunk, int *new_cap, size_t *smem) {
+static bool fused_plan(const SearchArgs &a, int Q, TileNet *T, int *blk, int *cb, int *new_cap, size_t *smem) {
     const Plan &p = a.plan;
     const ann_mlp *m = a.m;
     if (a.walkers || m->dtype == ANN_F8) return false;
@@ -479,12 +449,11 @@ static bool fused_plan(const SearchArgs &a, int Q, TileNet *T, int *blk, int *cb
     if ((int64_t)((Q + 255) / 256) * p.slots * 2 * weights * (f64 ? 32 : 1) > FUSED_WORK) return false;
     *new_cap = 2;
     while (*new_cap < p.slots) *new_cap <<= 1;
-    *chunk = p.slots < 512 ? p.slots : 512;
     for (*cb = 4; *cb >= 1; *cb >>= 1) {
         if (*cb > 1 && (*cb >> 1) * (f64 ? 16 : 32) >= p.slots) continue;  // half of it holds every round's pairs
         if (*cb == 1 && Q > 256 && weights * (f64 ? 4 : 2) > FUSED_WEIGHTS) continue;
         *blk = *cb > 1 ? 512 : 256;
-        *smem = fused_smem(a, *T, f64, *cb, *chunk, *new_cap, *blk);
+        *smem = fused_smem(a, *T, f64, *cb, *new_cap, *blk);
         if (*smem > FUSED_LDS) continue;
         const int by_lds = (int)(160 * 1024 / *smem), by_waves = *cb == 4 ? 1 : 1024 / *blk;  // registers: 168, 125, 99
         if (Q <= 256 * (by_lds < by_waves ? by_lds : by_waves)) return true;
@@ -494,9 +463,9 @@ static bool fused_plan(const SearchArgs &a, int Q, TileNet *T, int *blk, int *cb
 
 static bool fused_takes(const SearchArgs &a, int Q) {
     TileNet T;
-    int blk, cb, chunk, new_cap;
+    int blk, cb, new_cap;
     size_t smem;
-    return fused_plan(a, Q, &T, &blk, &cb, &chunk, &new_cap, &smem);
+    return fused_plan(a, Q, &T, &blk, &cb, &new_cap, &smem);
 }
 
 bool fused_serves(const SearchArgs &a) { return a.Q_total == 0 && fused_takes(a, a.plan.Q); }
@@ -512,7 +481,7 @@ int launch_fused(const SearchArgs &a, int32_t rounds_max, int32_t tail) {
     FusedArgs A{};
     int blk, cb;
     size_t smem;
-    if (!fused_plan(a, tail > 0 ? tail : p.Q, &A.T, &blk, &cb, &A.chunk, &A.new_cap, &smem)) return ANN_EINVAL;
+    if (!fused_plan(a, tail > 0 ? tail : p.Q, &A.T, &blk, &cb, &A.new_cap, &smem)) return ANN_EINVAL;
     const bool built_in = m->kernel == MLP_MFMA2, f64 = m->dtype == ANN_F32, bm = p.bitmap_words > 0;
     A.frag = built_in ? m->frag_dev : m->any_dev;
     A.b = m->b_dev;

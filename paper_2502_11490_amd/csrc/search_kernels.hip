@@ -29,7 +29,7 @@ constexpr int WAVES = BLOCK / 64;
 #define ROUND_BIG_FROM 512   // candidates per query and round above which the round kernel runs larger workgroups
 #endif
 #ifndef FILTER_CHUNK
-#define FILTER_CHUNK 1024   // candidates of a round that pass the visited filter together
+#define FILTER_CHUNK 1024   // walkers: candidates of a round that pass the visited filter together
 #endif
 #ifndef ROUND_TILE_MAX
 #define ROUND_TILE_MAX 4096   // most list entries held in LDS at a time during the merge
@@ -61,20 +61,6 @@ constexpr int SCAN_WAVES = SCAN_BLOCK / 64;
 #define PHASE_START
 #endif
 
-// Either form of the visited set: table_cap > 0 = hash table of that many entries, table_cap < 0 = bitmap in a
-// region of -table_cap words.
-template <int BLK>
-__device__ __forceinline__ int visited_filter(const int32_t *cand, const int32_t *cand_rank, int n_cand, uint32_t *dd_key,
-                                              uint32_t *dd_pos, uint32_t *bk_key, uint32_t *bk_cnt, int dd_n,
-                                              uint32_t *table, int table_cap, int64_t N, int32_t *out, int *wave_sums,
-                                              uint16_t *out_tag, int tag_div, int tag_base) {
-    if (table_cap < 0)
-        return filter_and_mark<BLK>(cand, cand_rank, n_cand, dd_key, dd_pos, bk_key, bk_cnt, dd_n, table, N, out, wave_sums,
-                                    out_tag, tag_div, tag_base);
-    return filter_and_insert<BLK>(cand, n_cand, dd_key, dd_pos, bk_key, bk_cnt, dd_n, table, table_cap, N, out, wave_sums,
-                                  out_tag, tag_div, tag_base);
-}
-
 // Counters and control block start at zero (a kernel, not a memset, so that a caller may
 // capture the launch sequence into a HIP graph).
 // stats[5], stats[6]: bytes of one adjacency row and of one item row, from which ann_search_stats derives the
@@ -96,17 +82,7 @@ __device__ void seed_slot(int slot, int query, const int32_t *__restrict__ entri
                           int E, int64_t N, QState *state, uint32_t *hash, int hash_cap, int32_t *cand_g, int slots,
                           int32_t *counts,
                           const int32_t *W_q, const int32_t *L_q, const int32_t *cap_q, int W, int L, int cap,
-                          int W_max, int L_max, int cap_max, int64_t *stats, unsigned char *smem, uint16_t *tag_g) {
-    int dd_n = 2;
-    while (dd_n < 2 * E) dd_n <<= 1;
-    int32_t *cand = (int32_t *)smem;                 // [E]
-    int32_t *cand_rank = rank ? cand + ((E + 3) & ~3) : nullptr;   // [E] the seeds' places in the visited bitmap
-    uint32_t *dd_key = (uint32_t *)(cand + (rank ? 2 : 1) * ((E + 3) & ~3));
-    uint32_t *dd_pos = dd_key + dd_n;
-    uint32_t *bk_key = dd_pos + dd_n;
-    uint32_t *bk_cnt = bk_key + dd_n;
-    int *wave_sums = (int *)(bk_cnt + dd_n);
-
+                          int W_max, int L_max, int cap_max, unsigned char *smem, uint16_t *tag_g) {
     const int table_words = hash_cap < 0 ? -hash_cap : hash_cap;  // a multiple of 64, the table 256-byte aligned
     uint32_t *table = hash + (size_t)slot * table_words;
     {
@@ -115,15 +91,39 @@ __device__ void seed_slot(int slot, int query, const int32_t *__restrict__ entri
         const uint4 e4 = make_uint4(e, e, e, e);
         for (int i = threadIdx.x; i < table_words / 4; i += BLK) t4[i] = e4;
     }
-    for (int i = threadIdx.x; i < E; i += BLK) {
-        const int32_t v = entries[(size_t)query * E + i];
-        cand[i] = v;
-        if (rank) cand_rank[i] = (v >= 0 && (int64_t)v < N) ? rank[v] : -1;
+    visited_cleared();
+    int32_t *out = cand_g + (size_t)slot * slots;
+    const int32_t *seeds = entries + (size_t)query * E;
+    int n;
+    if (tag_g) {  // walkers: the first of equal seeds starts one (see filter_and_insert, filter_and_mark)
+        int dd_n = 2;
+        while (dd_n < 2 * E) dd_n <<= 1;
+        int32_t *cand = (int32_t *)smem;                                // [E]
+        int32_t *cand_rank = rank ? cand + ((E + 3) & ~3) : nullptr;    // [E] the seeds' places in the visited bitmap
+        uint32_t *dd_key = (uint32_t *)(cand + (rank ? 2 : 1) * ((E + 3) & ~3));
+        uint32_t *dd_pos = dd_key + dd_n, *bk_key = dd_pos + dd_n, *bk_cnt = bk_key + dd_n;
+        int *wave_sums = (int *)(bk_cnt + dd_n);
+        uint16_t *tag = tag_g + (size_t)slot * slots;
+        for (int i = threadIdx.x; i < E; i += BLK) {
+            const int32_t v = seeds[i];
+            cand[i] = v;
+            if (rank) cand_rank[i] = (v >= 0 && (int64_t)v < N) ? rank[v] : -1;
+        }
+        __syncthreads();
+        if (hash_cap < 0)
+            n = filter_and_mark<BLK>(cand, cand_rank, E, dd_key, dd_pos, bk_key, bk_cnt, dd_n, table, N, out, wave_sums, tag, 1, 0);
+        else
+            n = filter_and_insert<BLK>(cand, E, dd_key, dd_pos, bk_key, bk_cnt, dd_n, table, hash_cap, N, out, wave_sums, tag, 1, 0);
+    } else {
+        auto seed = [&](int p, uint32_t *bit) {
+            const int32_t v = seeds[p];
+            if (hash_cap < 0) *bit = rank && v >= 0 && (int64_t)v < N ? (uint32_t)rank[v] : (uint32_t)v;
+            return v;
+        };
+        int *wave_sums = (int *)smem;
+        n = hash_cap < 0 ? visit<BLK, true, false, 1>(seed, E, table, 0, N, out, wave_sums, Nothing{})
+                         : visit<BLK, false, false, 1>(seed, E, table, hash_cap, N, out, wave_sums, Nothing{});
     }
-    __threadfence_block();
-    __syncthreads();
-    int n = visited_filter<BLK>(cand, cand_rank, E, dd_key, dd_pos, bk_key, bk_cnt, dd_n, table, hash_cap, N,
-                                cand_g + (size_t)slot * slots, wave_sums, tag_g + (size_t)slot * slots, 1, 0);
     if (threadIdx.x == 0) {
         QState s;
         s.t = 0;
@@ -147,10 +147,10 @@ init_kernel(const int32_t *__restrict__ entries, const int32_t *__restrict__ ran
             uint32_t *hash,
             int hash_cap, int32_t *cand_g, int slots, int32_t *counts, const int32_t *W_q,
             const int32_t *L_q, const int32_t *cap_q, int W, int L, int cap, int W_max, int L_max,
-            int cap_max, int64_t *stats, uint16_t *tag_g) {
+            int cap_max, uint16_t *tag_g) {
     extern __shared__ __align__(16) unsigned char smem[];
     seed_slot<BLOCK>(blockIdx.x, blockIdx.x, entries, rank, E, N, state, hash, hash_cap, cand_g, slots, counts, W_q, L_q, cap_q, W,
-              L, cap, W_max, L_max, cap_max, stats, smem, tag_g);
+              L, cap, W_max, L_max, cap_max, smem, tag_g);
 }
 
 // First k entries of a slot's list to row `row` of the outputs, padded with (-1, -inf).
@@ -252,7 +252,7 @@ admit_kernel(const int32_t *__restrict__ entries, const int32_t *__restrict__ ra
     const int next = next_s;
     if (next < 0) return;
     seed_slot<BLOCK>(slot, next, entries, rank, E, N, state, hash, hash_cap, cand_g, slots, counts, W_q, L_q, cap_q, W, L, cap,
-              W_max, L_max, cap_max, stats, smem, tag_g);
+              W_max, L_max, cap_max, smem, tag_g);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -363,18 +363,17 @@ scan_compact_kernel(const int32_t *__restrict__ counts, int Q, const int32_t *__
 // otherwise only grows).  The scan for the first <= W unexpanded entries among the first L ranks starts
 // there, reading the list in pieces of one entry per thread (four per thread after the first piece).
 // Eight workgroups of 256 threads fill a CU's wave slots; that needs no more than 64 registers per lane.
-// BITMAP: the visited set is one bit per item (hash_cap < 0), else the hash table.  PIECES: a round may bring more
-// candidates than pass the filter at once (both are compile-time so that each build holds one filter, once, in
-// its 64 registers).  RESIDENT: the whole list fits one tile (C <= tile_keys); it is then requested at the very
-// start, together with the state, merged into a second LDS copy, and the parents are chosen from that copy: two
-// dependent trips to memory fewer per round than the tiled walk, which is what short lists are bound by.
-template <int BLK, bool BITMAP, bool PIECES, bool RESIDENT>
+// BITMAP: the visited set is one bit per item (hash_cap < 0), else the hash table.  RESIDENT: the whole list fits one tile
+// (C <= tile_keys); it is then requested at the very start, together with the state, merged into a second LDS copy, and
+// the parents are chosen from that copy: two dependent trips to memory fewer per round than the tiled walk, which is what
+// short lists are bound by.  WALKERS: the paper-literal rule, whose visited filter keeps the first of equal candidates.
+template <int BLK, bool BITMAP, bool RESIDENT, bool WALKERS>
 __global__ void __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(ROUND_WAVES_MIN, 8)))
 round_kernel(const int32_t *__restrict__ adj, const int32_t *__restrict__ adj_rank, int R, int64_t N, QState *state,
              uint64_t *pool_g, int C,
              uint32_t *hash, int hash_cap, int32_t *cand_g, int slots, int32_t *counts,
              const int32_t *__restrict__ offsets, const float *__restrict__ scores, int new_cap,
-             int W_max, int64_t *stats, uint16_t *tag_g, int walkers, int tile_keys, int chunk) {
+             int W_max, int64_t *stats, uint16_t *tag_g, int tile_keys, int chunk) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int q = blockIdx.x;
     PHASE_START
@@ -387,10 +386,9 @@ round_kernel(const int32_t *__restrict__ adj, const int32_t *__restrict__ adj_ra
     uint64_t *best = newk + new_cap;                          // [W_max]     walkers: best new child of each
     uint64_t *tile = best + ((W_max + 1) & ~1);               // [tile_keys] a piece of the stored list
     uint64_t *merged = tile + tile_keys;                      // [C]         RESIDENT only: the list after the merge
-    int32_t *cand = (int32_t *)newk;                          // [min(slots, FILTER_CHUNK)]
     uint64_t *pool = pool_g + (size_t)q * C;
     int32_t *cand_q = cand_g + (size_t)q * slots;
-    uint16_t *tag_q = tag_g + (size_t)q * slots;
+    uint16_t *tag_q = WALKERS ? tag_g + (size_t)q * slots : nullptr;
 
     // Everything the round needs first is requested at once, before any of it is looked at: the
     // workgroups of a launch start together, and every dependent trip to memory costs them all a few
@@ -418,17 +416,7 @@ round_kernel(const int32_t *__restrict__ adj, const int32_t *__restrict__ adj_ra
         if (threadIdx.x == 0) counts[q] = -1;
         return;
     }
-    // chunk: candidates that go through the visited filter together; with a bitmap addressed by rank their ranks
-    // (adj_rank holds the rank of every adjacency entry, row for row) sit behind them
-    int dd_n = 2;
-    while (dd_n < 2 * chunk) dd_n <<= 1;
-    int32_t *cand_rank = (BITMAP && adj_rank) ? cand + ((chunk + 3) & ~3) : nullptr;
-    uint32_t *dd_key = (uint32_t *)(cand + (cand_rank ? 2 : 1) * ((chunk + 3) & ~3));
-    uint32_t *dd_pos = dd_key + dd_n;
-    uint32_t *bk_key = dd_pos + dd_n;
-    uint32_t *bk_cnt = bk_key + dd_n;
-
-    if (walkers)
+    if (WALKERS)
         for (int i = threadIdx.x; i < W_max; i += BLK) best[i] = KEY_SENTINEL;
     if (threadIdx.x == 0) shared_i[0] = 0x7fffffff;  // rank of the first inserted entry
     __syncthreads();
@@ -446,7 +434,7 @@ round_kernel(const int32_t *__restrict__ adj, const int32_t *__restrict__ adj_ra
             key = make_key(scores[off + j], cand_q[j], 0u);
             keep = key < worst;
             // walkers: the best newly scored neighbour of each walker, whether it enters the list or not
-            if (walkers) atomicMin((unsigned long long *)&best[tag_q[j]], (unsigned long long)key);
+            if (WALKERS) atomicMin((unsigned long long *)&best[tag_q[j]], (unsigned long long)key);
         }
         int tot;
         int pos = block_excl_count<BLK>(keep, wave_sums, &tot);
@@ -521,9 +509,9 @@ round_kernel(const int32_t *__restrict__ adj, const int32_t *__restrict__ adj_ra
     // 2. termination test and choice of the parents
     int n_par = 0, n_live = 0;
     const bool capped = (st.cap > 0 && st.t >= st.cap);
-    const int lim = walkers ? 0 : min(st.L, n_list);
+    const int lim = WALKERS ? 0 : min(st.L, n_list);
     int first_open = min(st.first_open, shared_i[0]);
-    if (walkers && !capped) {
+    if (WALKERS && !capped) {
         // Paper-literal variant (Alg. 1 read as independent walkers): walker s moves to the best of the
         // neighbours it scored last round (round 0: to its seed); a walker without one is dead (-1) and
         // contributes R invalid candidates, so that candidate position / R keeps naming the walker.
@@ -537,7 +525,7 @@ round_kernel(const int32_t *__restrict__ adj, const int32_t *__restrict__ adj_ra
         }
         n_par = n_live > 0 ? st.W : 0;
     }
-    if (!capped && !walkers) {
+    if (!capped && !WALKERS) {
         int i0 = first_open;
         bool first_piece = true;
         while (i0 < lim && n_par < st.W) {
@@ -590,33 +578,51 @@ round_kernel(const int32_t *__restrict__ adj, const int32_t *__restrict__ adj_ra
         return;
     }
 
-    if (RESIDENT) __syncthreads();  // the LDS copies of the list are dead from here on; their space is reused
     // 3. neighbour gather: one adjacency row per parent, consecutive lanes read consecutive ids;
     // 4. visited filter, 5. survivors of this query for the next MLP launch.
-    // A round's candidates go through in pieces of at most `chunk` (what the dedupe tables in LDS hold).  An id
-    // that comes again in a later piece is dropped there because the earlier piece has entered it into the
-    // visited table: the first occurrence still wins, in candidate order.
     PHASE_MARK(3);  // selection
     const int n_cand = n_par * R;
+    uint32_t *table = hash + (size_t)q * (size_t)(BITMAP ? -hash_cap : hash_cap);
     int n_new = 0;
-    for (int c0 = 0; c0 < (PIECES ? n_cand : 1); c0 += chunk) {
-        const int nc = PIECES ? min(chunk, n_cand - c0) : n_cand;
-        if (PIECES && c0 > 0) {  // the table stores of the piece before must be seen by this piece's reads
-            __threadfence_block();
+    if (WALKERS) {
+        // In pieces of at most `chunk` (what the dedupe tables in LDS hold), which of equal candidates comes first
+        // decides whose it is.  An id that comes again in a later piece is dropped there because the earlier piece has
+        // entered it into the visited set.
+        if (RESIDENT) __syncthreads();  // the LDS copies of the list are dead from here on; their space is reused
+        int dd_n = 2;
+        while (dd_n < 2 * chunk) dd_n <<= 1;
+        int32_t *cand = (int32_t *)newk;  // [chunk], then their ranks where the bitmap goes by rank
+        int32_t *cand_rank = (BITMAP && adj_rank) ? cand + ((chunk + 3) & ~3) : nullptr;
+        uint32_t *dd_key = (uint32_t *)(cand + (cand_rank ? 2 : 1) * ((chunk + 3) & ~3));
+        uint32_t *dd_pos = dd_key + dd_n, *bk_key = dd_pos + dd_n, *bk_cnt = bk_key + dd_n;
+        for (int c0 = 0; c0 < n_cand; c0 += chunk) {
+            const int nc = min(chunk, n_cand - c0);
+            if (c0 > 0) {  // the table stores of the piece before must be seen by this piece's reads
+                __threadfence_block();
+                __syncthreads();
+            }
+            for (int j = threadIdx.x; j < nc; j += BLK) {
+                const int p = (c0 + j) / R, s = (c0 + j) - p * R;
+                cand[j] = parents[p] >= 0 ? adj[(size_t)parents[p] * R + s] : -1;
+                if (BITMAP && cand_rank) cand_rank[j] = parents[p] >= 0 ? adj_rank[(size_t)parents[p] * R + s] : -1;
+            }
             __syncthreads();
+            if (BITMAP)
+                n_new += filter_and_mark<BLK>(cand, cand_rank, nc, dd_key, dd_pos, bk_key, bk_cnt, dd_n, table, N,
+                                              cand_q + n_new, wave_sums, tag_q + n_new, R, c0);
+            else
+                n_new += filter_and_insert<BLK>(cand, nc, dd_key, dd_pos, bk_key, bk_cnt, dd_n, table, hash_cap, N,
+                                                cand_q + n_new, wave_sums, tag_q + n_new, R, c0);
         }
-        for (int j = threadIdx.x; j < nc; j += BLK) {
-            const int p = (c0 + j) / R, s = (c0 + j) - p * R;
-            cand[j] = parents[p] >= 0 ? adj[(size_t)parents[p] * R + s] : -1;
-            if (BITMAP && cand_rank) cand_rank[j] = parents[p] >= 0 ? adj_rank[(size_t)parents[p] * R + s] : -1;
-        }
-        __syncthreads();
-        if (BITMAP)
-            n_new += filter_and_mark<BLK>(cand, cand_rank, nc, dd_key, dd_pos, bk_key, bk_cnt, dd_n, hash + (size_t)q * (size_t)(-hash_cap),
-                                          N, cand_q + n_new, wave_sums, tag_q + n_new, R, PIECES ? c0 : 0);
-        else
-            n_new += filter_and_insert<BLK>(cand, nc, dd_key, dd_pos, bk_key, bk_cnt, dd_n, hash + (size_t)q * hash_cap,
-                                            hash_cap, N, cand_q + n_new, wave_sums, tag_q + n_new, R, PIECES ? c0 : 0);
+    } else {
+        auto neighbour = [&](int j, uint32_t *bit) {
+            const int p = j / R;
+            const size_t from = (size_t)parents[p] * R + (j - p * R);
+            const int32_t v = adj[from];
+            if (BITMAP) *bit = (uint32_t)(adj_rank ? adj_rank[from] : v);
+            return v;
+        };
+        n_new = visit<BLK, BITMAP, true, 4>(neighbour, n_cand, table, hash_cap, N, cand_q, wave_sums, Nothing{});
     }
     PHASE_MARK(5);  // adjacency gather, dedupe + visited table
     if (threadIdx.x == 0) {
@@ -624,7 +630,7 @@ round_kernel(const int32_t *__restrict__ adj, const int32_t *__restrict__ adj_ra
         state[q].first_open = first_open;
         state[q].t = st.t + 1;
         state[q].n_visited = st.n_visited + n_new;
-        state[q].n_expanded = st.n_expanded + (walkers ? n_live : n_par);
+        state[q].n_expanded = st.n_expanded + (WALKERS ? n_live : n_par);
         counts[q] = n_new;
     }
 }
@@ -678,28 +684,29 @@ static int tile_keys_of(const Plan &p) {
 // Does the visited bitmap of this search go by the graph's locality order?
 static bool ranked(const ann_graph *g, const Plan &p) { return p.bitmap_words > 0 && g->adj_rank != nullptr; }
 
-// Candidates that go through the visited filter together.  With ranks beside the ids the pieces are half as
-// large, so that the filter's LDS stays below what the merge needs anyway (the piece size does not show in the
-// kernel's time).
+// Walkers: candidates that go through the visited filter together.
 static int filter_chunk(const ann_graph *g, const Plan &p) {
     const int most = ranked(g, p) ? FILTER_CHUNK / 2 : FILTER_CHUNK;
     return p.slots < most ? p.slots : most;
 }
 
-// list_keys: list entries held in LDS (0: one tile)
-static size_t round_smem(const ann_graph *g, const Plan &p, int list_keys = 0) {
-    const int chunk = filter_chunk(g, p);
+// LDS of the walkers' filter over n candidates, dedupe tables included
+static size_t filter_smem(const ann_graph *g, const Plan &p, int n) {
     int dd_n = 2;
-    while (dd_n < 2 * chunk) dd_n <<= 1;
-    size_t lists = (size_t)(new_cap_of(p) + ((p.W_max + 1) & ~1) + (list_keys > 0 ? list_keys : tile_keys_of(p))) * 8;
-    size_t filt = (size_t)((chunk + 3) & ~3) * 4 * (ranked(g, p) ? 2 : 1) + (size_t)dd_n * 16;
+    while (dd_n < 2 * n) dd_n <<= 1;
+    return (size_t)((n + 3) & ~3) * 4 * (ranked(g, p) ? 2 : 1) + (size_t)dd_n * 16;
+}
+
+// list_keys: list entries held in LDS (0: one tile)
+static size_t round_smem(const SearchArgs &a, int list_keys = 0) {
+    const Plan &p = a.plan;
+    const size_t lists = (size_t)(new_cap_of(p) + ((p.W_max + 1) & ~1) + (list_keys > 0 ? list_keys : tile_keys_of(p))) * 8;
+    const size_t filt = a.walkers ? filter_smem(a.g, p, filter_chunk(a.g, p)) : 0;
     return (size_t)((p.W_max + 3) & ~3) * 4 + 24 * 4 + (lists > filt ? lists : filt);
 }
 
-static size_t seed_smem(const ann_graph *g, const Plan &p) {
-    int dd_n = 2;
-    while (dd_n < 2 * p.E) dd_n <<= 1;
-    return (size_t)((p.E + 3) & ~3) * 4 * (ranked(g, p) ? 2 : 1) + (size_t)dd_n * 16 + (WAVES + 1) * 4;
+static size_t seed_smem(const SearchArgs &a) {
+    return (WAVES + 1) * 4 + (a.walkers ? filter_smem(a.g, a.plan, a.plan.E) : 0);
 }
 
 int launch_zero_stats(const SearchArgs &a, int32_t one_launch) {
@@ -712,15 +719,14 @@ int launch_zero_stats(const SearchArgs &a, int32_t one_launch) {
 
 int launch_init(const SearchArgs &a) {
     const Plan &p = a.plan;
-    size_t smem = seed_smem(a.g, p);
-    int64_t *stats = (int64_t *)(a.ws + p.off_stats);
+    size_t smem = seed_smem(a);
     if (int rc = launch_zero_stats(a, 0); rc != ANN_OK) return rc;
     hipLaunchKernelGGL(init_kernel, dim3(p.Q), dim3(BLOCK), smem, a.stream, a.entries,
                        ranked(a.g, p) ? a.g->rank : nullptr, p.E, a.g->N,
                        (QState *)(a.ws + p.off_state), (uint32_t *)(a.ws + p.off_hash), table_cap_arg(p),
                        (int32_t *)(a.ws + p.off_cand), p.slots, (int32_t *)(a.ws + p.off_counts), a.W_q,
-                       a.L_q, a.cap_q, a.W, a.L, a.cap, p.W_max, p.L_max, p.max_iters_max, stats,
-                       (uint16_t *)(a.ws + p.off_tag));
+                       a.L_q, a.cap_q, a.W, a.L, a.cap, p.W_max, p.L_max, p.max_iters_max,
+                       a.walkers ? (uint16_t *)(a.ws + p.off_tag) : nullptr);
     ANN_HIP_TRY(hipGetLastError());
     return ANN_OK;
 }
@@ -745,13 +751,13 @@ int launch_stream_publish(const SearchArgs &a, int avail) {
 
 int launch_admit(const SearchArgs &a) {
     const Plan &p = a.plan;
-    hipLaunchKernelGGL(admit_kernel, dim3(p.Q), dim3(BLOCK), seed_smem(a.g, p), a.stream, a.entries,
+    hipLaunchKernelGGL(admit_kernel, dim3(p.Q), dim3(BLOCK), seed_smem(a), a.stream, a.entries,
                        ranked(a.g, p) ? a.g->rank : nullptr, p.E, a.g->N,
                        (QState *)(a.ws + p.off_state), (uint32_t *)(a.ws + p.off_hash), table_cap_arg(p),
                        (int32_t *)(a.ws + p.off_cand), p.slots, (int32_t *)(a.ws + p.off_counts), a.W_q, a.L_q,
                        a.cap_q, a.W, a.L, a.cap, p.W_max, p.L_max, p.max_iters_max, (int64_t *)(a.ws + p.off_stats),
                        (Ctrl *)(a.ws + p.off_ctrl), a.slot_query, a.Q_total, (const uint64_t *)(a.ws + p.off_pool), p.C,
-                       p.k, a.out_ids, a.out_scores, (uint16_t *)(a.ws + p.off_tag));
+                       p.k, a.out_ids, a.out_scores, a.walkers ? (uint16_t *)(a.ws + p.off_tag) : nullptr);
     ANN_HIP_TRY(hipGetLastError());
     return ANN_OK;
 }
@@ -773,38 +779,31 @@ int launch_scan_compact(const SearchArgs &a) {
 
 int launch_round(const SearchArgs &a) {
     const Plan &p = a.plan;
-    size_t smem = round_smem(a.g, p);
     // Workgroups of 128 threads when a round has at most 128 candidates per query and the batch is far larger
     // than what a chip holds at once (2,048 workgroups of 256): twice as many queries are then resident, and
     // the candidates still go through the visited filter in one pass.  (C4: 33 -> 28 ms per step; with few
     // queries the shorter path of the larger workgroup wins: C2 3.9 against 4.2 ms.)
-    // Workgroups of 1,024 threads when a round brings more than 512 candidates per query: the candidates pass the
-    // visited filter in one sweep, and the sort and the merge have a quarter of the work per thread.
-    const bool half = (p.slots <= 128 && p.Q >= 8192);
-    const bool big = p.slots > ROUND_BIG_FROM;  // several filter pieces only occur here: slots > FILTER_CHUNK / 2
+    // Workgroups of 512 threads when a round brings more than 512 candidates per query: the sort and the merge have half
+    // of the work per thread.
+    const bool big = p.slots > ROUND_BIG_FROM, half = p.slots <= 128 && p.Q >= 8192 && !a.walkers;
     const int which = half ? 1 : big ? 2 : 0;
     const int threads = half ? 128 : big ? ROUND_BIG_BLOCK : BLOCK;
     const bool bm = p.bitmap_words > 0;
-    const int chunk = filter_chunk(a.g, p);
-    const bool pieces = p.slots > chunk;
     const bool resident = !big && p.C <= tile_keys_of(p);
     const int tile_keys = resident ? ((p.C + 1) & ~1) : tile_keys_of(p);  // resident: the list itself, twice
-    if (resident) smem = round_smem(a.g, p, tile_keys + p.C);
+    const size_t smem = resident ? round_smem(a, tile_keys + p.C) : round_smem(a);
     using Fn = decltype(&round_kernel<BLOCK, false, false, false>);
     Fn fn;
-    if (big)
-        fn = pieces ? (bm ? round_kernel<ROUND_BIG_BLOCK, true, true, false> : round_kernel<ROUND_BIG_BLOCK, false, true, false>)
-                    : (bm ? round_kernel<ROUND_BIG_BLOCK, true, false, false> : round_kernel<ROUND_BIG_BLOCK, false, false, false>);
-    else if (half)
-        fn = resident ? (bm ? round_kernel<128, true, false, true> : round_kernel<128, false, false, true>)
-                      : (bm ? round_kernel<128, true, false, false> : round_kernel<128, false, false, false>);
-    else
-        fn = resident ? (bm ? round_kernel<BLOCK, true, false, true> : round_kernel<BLOCK, false, false, true>)
-                      : (bm ? round_kernel<BLOCK, true, false, false> : round_kernel<BLOCK, false, false, false>);
+#define ROUND_FN(BLK, RESIDENT, WALKERS) (bm ? round_kernel<BLK, true, RESIDENT, WALKERS> : round_kernel<BLK, false, RESIDENT, WALKERS>)
+    if (a.walkers) fn = big ? ROUND_FN(ROUND_BIG_BLOCK, false, true) : resident ? ROUND_FN(BLOCK, true, true) : ROUND_FN(BLOCK, false, true);
+    else if (big) fn = ROUND_FN(ROUND_BIG_BLOCK, false, false);
+    else if (half) fn = resident ? ROUND_FN(128, true, false) : ROUND_FN(128, false, false);
+    else fn = resident ? ROUND_FN(BLOCK, true, false) : ROUND_FN(BLOCK, false, false);
+#undef ROUND_FN
     if (smem > 48 * 1024) {
         static std::atomic<uint32_t> raised[24];
         if (int rc = raise_lds_limit((const void *)fn, 128 * 1024, a.m->device,
-                                     raised[8 * which + (bm ? 4 : 0) + (pieces ? 2 : 0) + (resident ? 1 : 0)]);
+                                     raised[8 * which + (bm ? 4 : 0) + (a.walkers ? 2 : 0) + (resident ? 1 : 0)]);
             rc != ANN_OK)
             return rc;
     }
@@ -814,8 +813,7 @@ int launch_round(const SearchArgs &a) {
                        (uint32_t *)(a.ws + p.off_hash), table_cap_arg(p), (int32_t *)(a.ws + p.off_cand), p.slots,
                        (int32_t *)(a.ws + p.off_counts), (const int32_t *)(a.ws + p.off_offsets),
                        (const float *)(a.ws + p.off_scores), new_cap_of(p), p.W_max,
-                       (int64_t *)(a.ws + p.off_stats), (uint16_t *)(a.ws + p.off_tag), a.walkers ? 1 : 0,
-                       tile_keys, chunk);
+                       (int64_t *)(a.ws + p.off_stats), (uint16_t *)(a.ws + p.off_tag), tile_keys, filter_chunk(a.g, p));
     ANN_HIP_TRY(hipGetLastError());
     return ANN_OK;
 }
