@@ -8,7 +8,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libgmpgr_ann.so")
-SOURCES = ["api.hip", "search_kernels.hip", "search_fused.hip", "mlp_alu.hip", "mlp_any.hip", "mlp_mfma.hip", "mlp_mfma_stream.hip", "mlp_mfma_f8.hip", "noise.hip", "noalloc.hip",
+SOURCES = ["api.hip", "search_kernels.hip", "search_fused.hip", "search_wave.hip", "mlp_alu.hip", "mlp_any.hip", "mlp_mfma.hip", "mlp_mfma_stream.hip", "mlp_mfma_f8.hip", "noise.hip", "noalloc.hip",
            "brute_force.hip"]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",

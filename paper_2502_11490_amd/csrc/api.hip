@@ -331,9 +331,10 @@ static int run_search(SearchArgs &a) {
     const int64_t round_limit = capped ? (int64_t)p.max_iters_max
                                        : (p.bitmap_words > 0 ? a.g->N : (int64_t)p.hash_cap / 2) + 1;
     // stage times are those of the separate kernels: a profiled search runs them
-    const bool fused = !g_prof.on && fused_serves(a);
-    if (fused) {
-        if ((rc = launch_fused(a, (int32_t)(round_limit < 0x7ffffffe ? round_limit : 0x7ffffffe), 0)) != ANN_OK) return rc;
+    const bool wave = !g_prof.on && wave_serves(a), fused = !g_prof.on && fused_serves(a);
+    if (wave || fused) {
+        const int32_t rounds_max = (int32_t)(round_limit < 0x7ffffffe ? round_limit : 0x7ffffffe);
+        if ((rc = wave ? launch_wave(a, rounds_max) : launch_fused(a, rounds_max, 0)) != ANN_OK) return rc;
         if (capped) return ANN_OK;
         const int g = box->gate(a.mail_tag, INT64_MAX, a.stream);
         if (g < 0) {

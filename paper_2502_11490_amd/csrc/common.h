@@ -51,6 +51,15 @@ __device__ __forceinline__ float sigmoid_hw(float z) {
     return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * z));
 }
 
+// ReLU, NaN gives 0, as fmaxf(x, 0).  The compiler makes two instructions of that, the first of which quiets a NaN that the
+// second drops; the median of x, 0 and infinity is one.  (Infinity passes through an empty statement, or the compiler
+// turns the median back into a maximum.)
+__device__ __forceinline__ float relu_f32(float x) {
+    float inf = __builtin_inff();
+    asm("" : "+s"(inf));
+    return __builtin_amdgcn_fmed3f(x, 0.f, inf);
+}
+
 // Layers of a metric as mlp_tile.h walks them: fragments of 1 KB, counts in units of the matrix instruction.
 struct TileNet {
     int32_t n_layers, J, d_user, d_item;
@@ -126,7 +135,8 @@ struct Ctrl {
     int32_t n_active;     // queries not finished
     int32_t next_query;   // continuous batching: queries admitted so far (a closed batch may overshoot its total)
     int32_t avail;        // open stream: queries that have arrived so far
-    int32_t pad[12];
+    int32_t ended;        // a search by waves: queries whose result is written
+    int32_t pad[11];
 };
 
 // Per-query state at off_state.
@@ -173,7 +183,8 @@ struct SearchArgs {
 };
 
 // search_kernels.hip
-int launch_zero_stats(const SearchArgs &a, int32_t one_launch);  // one_launch: queries that one launch will run
+// one_launch: queries that one launch will run, all of them at once; by_waves: queries that go to search_wave.hip
+int launch_zero_stats(const SearchArgs &a, int32_t one_launch, int32_t by_waves = 0);
 int launch_init(const SearchArgs &a);
 int launch_scan_compact(const SearchArgs &a);
 int launch_round(const SearchArgs &a);
@@ -188,6 +199,10 @@ constexpr size_t FUSED_LDS = 150 * 1024;
 bool fused_serves(const SearchArgs &a);
 int fused_tail(const SearchArgs &a);  // running queries from which on the tail goes there, 0 = never
 int launch_fused(const SearchArgs &a, int32_t rounds_max, int32_t tail);
+
+// search_wave.hip: all rounds of a query by one wave
+bool wave_serves(const SearchArgs &a);
+int launch_wave(const SearchArgs &a, int32_t rounds_max);
 
 // noise.hip: out = users + sigma * N(0, I), element-indexed counter-based draw (Eq. 5)
 int launch_users_add_noise(const void *users, void *out, int64_t n_elem, int dtype, double sigma, uint64_t seed,

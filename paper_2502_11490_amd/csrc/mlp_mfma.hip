@@ -95,7 +95,7 @@ template <bool F16>
 __device__ __forceinline__ bf16x8 relu_pack(const f32x16 &acc, int half) {
     f32x8 v;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) v[j] = fmaxf(acc[half * 8 + j], 0.f);
+    for (int j = 0; j < 8; ++j) v[j] = relu_f32(acc[half * 8 + j]);
     if constexpr (F16)
         return __builtin_bit_cast(bf16x8, __builtin_convertvector(v, f16x8));
     else

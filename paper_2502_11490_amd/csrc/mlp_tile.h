@@ -43,7 +43,7 @@ template <bool F16, bool INT_RELU>
 __device__ __forceinline__ uint4 tile_relu(const f32x16 &acc, int half) {
     f32x8 v;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) v[j] = INT_RELU ? acc[half * 8 + j] : fmaxf(acc[half * 8 + j], 0.f);
+    for (int j = 0; j < 8; ++j) v[j] = INT_RELU ? acc[half * 8 + j] : relu_f32(acc[half * 8 + j]);
     s16x8 r;
     if constexpr (F16) r = __builtin_bit_cast(s16x8, __builtin_convertvector(v, f16x8));
     else r = __builtin_bit_cast(s16x8, __builtin_convertvector(v, bf16x8));

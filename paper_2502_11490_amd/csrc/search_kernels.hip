@@ -66,10 +66,11 @@ constexpr int SCAN_WAVES = SCAN_BLOCK / 64;
 // stats[5], stats[6]: bytes of one adjacency row and of one item row, from which ann_search_stats derives the
 // algorithmic bytes of the gather stages.  stats[7]: queries that one launch ran to their end (search_fused.hip).
 __global__ void zero_stats_kernel(int64_t *stats, Ctrl *ctrl, int Q, int keep_stats, int adj_row_bytes,
-                                  int item_row_bytes, int one_launch) {
+                                  int item_row_bytes, int one_launch, int by_waves) {
     if (threadIdx.x < 16 && !keep_stats)
         stats[threadIdx.x] = threadIdx.x == 4 ? Q : threadIdx.x == 5 ? adj_row_bytes : threadIdx.x == 6 ? item_row_bytes : 0;
     if (threadIdx.x == 7) stats[7] += one_launch;  // the thread that has just cleared it
+    if (threadIdx.x == 8) stats[8] += by_waves;
     if (threadIdx.x < 16) ((int32_t *)ctrl)[threadIdx.x] = 0;
 }
 
@@ -709,10 +710,10 @@ static size_t seed_smem(const SearchArgs &a) {
     return (WAVES + 1) * 4 + (a.walkers ? filter_smem(a.g, a.plan, a.plan.E) : 0);
 }
 
-int launch_zero_stats(const SearchArgs &a, int32_t one_launch) {
+int launch_zero_stats(const SearchArgs &a, int32_t one_launch, int32_t by_waves) {
     const Plan &p = a.plan;
     hipLaunchKernelGGL(zero_stats_kernel, dim3(1), dim3(64), 0, a.stream, (int64_t *)(a.ws + p.off_stats),
-                       (Ctrl *)(a.ws + p.off_ctrl), p.Q, a.keep_stats ? 1 : 0, p.R * 4, item_row_bytes(a.g), one_launch);
+                       (Ctrl *)(a.ws + p.off_ctrl), p.Q, a.keep_stats ? 1 : 0, p.R * 4, item_row_bytes(a.g), one_launch, by_waves);
     ANN_HIP_TRY(hipGetLastError());
     return ANN_OK;
 }

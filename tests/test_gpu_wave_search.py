@@ -1,0 +1,87 @@
+"""Searches run by waves that take one query after the other (metrics with items of 64 and 256 hidden units, batches
+beyond what a workgroup per query is best at) against the same searches run stage by stage: id for id, relevance for
+relevance, counter for counter.  Enabling the stage timing selects the separate kernels.  The ninth word of the workspace's
+counters (at byte 256) says how many queries such a launch was given."""
+import pytest
+import torch
+
+import paper_2502_11490_amd as ann
+from test_gpu_fused_search import _handles
+
+pytestmark = pytest.mark.gpu
+TWO, ONE = (64, 64, (256, 128), 3), (64, 64, (256,), 4)
+
+
+def _both(call, ws):
+    runs = []
+    for staged in (True, False):
+        ann.ann_profile_enable(staged)
+        try:
+            ids, sc = call()
+        finally:
+            ann.ann_profile_enable(False)
+        st = ann.ann_search_stats(ws)
+        runs.append((ids.clone(), sc.clone(), (st.pairs_scored, st.nodes_expanded, st.max_query_iters, st.visited_overflow, st.queries)))
+        assert int(ws[256:384].view(torch.int64)[8]) == (0 if staged else st.queries)
+    assert torch.equal(runs[0][0], runs[1][0])
+    assert torch.equal(runs[0][1].view(torch.int32), runs[1][1].view(torch.int32))  # NaN too
+    assert runs[0][2] == runs[1][2]
+
+
+@pytest.mark.parametrize("visited", ["hash", "bitmap", "rank"])
+@pytest.mark.parametrize("dtype,shape", [("bf16", TWO), ("f16", TWO), ("bf16", ONE), ("f16", ONE)])
+def test_search_by_waves_is_the_staged_search(dtype, shape, visited, monkeypatch):
+    """Fewer and more queries than waves of the launch, one more than a multiple of a CU's; one neighbour an item; rounds of
+    one candidate, of a number that is no multiple of a wave, of one and several pieces of 128 and 256; lists of one entry
+    and lists that leave room for one to sixteen waves a CU; k above and below L; more seeds than candidates; with
+    and without a cap."""
+    monkeypatch.setenv("GMPGR_VISITED_SET", "hash" if visited == "hash" else "bitmap")
+    for Q, R, E, W, L, k, cap in [(2048, 32, 4, 4, 64, 100, 0), (2049, 16, 1, 1, 1, 5, 0), (2100, 1, 2, 3, 33, 7, 0),
+                                  (4097, 24, 3, 5, 100, 20, 0), (2050, 32, 300, 9, 200, 11, 0), (2048, 32, 2, 12, 250, 40, 9),
+                                  (9000, 17, 4, 2, 40, 10, 7), (2048, 16, 4, 4, 900, 30, 0), (2051, 16, 1024, 8, 2500, 30, 0),
+                                  (300, 32, 4, 4, 64, 100, 0), (777, 8, 5, 7, 131, 9, 0), (1024, 32, 4, 16, 300, 50, 5)]:
+        g, m, users, entries = _handles(dtype, *shape, 3001, R, Q, E)
+        if visited == "rank":
+            rank = torch.randperm(3001, generator=torch.Generator().manual_seed(1)).to(torch.int32).cuda()
+            ann.ann_graph_set_locality(g, rank)
+        ws = torch.empty(ann.ann_search_workspace_bytes(g, m, Q, E, W, L, k, cap), dtype=torch.uint8, device="cuda")
+        _both(lambda: ann.ann_search(g, m, users, entries, W, L, k, cap, workspace=ws), ws)
+
+
+@pytest.mark.parametrize("cap", [0, 24])
+@pytest.mark.parametrize("dtype,shape", [("bf16", TWO), ("f16", ONE)])
+def test_queries_with_their_own_parameters(dtype, shape, cap):
+    """Widths, lists and caps per query, some of them outside their range (they are taken to its ends)."""
+    Q = 3000
+    g, m, users, entries = _handles(dtype, *shape, 5000, 16, Q, 4)
+    gen = torch.Generator().manual_seed(Q)
+    own = [torch.randint(lo, hi, (Q,), generator=gen, dtype=torch.int32).cuda() for lo, hi in ((0, 14), (0, 190), (0, 30))]
+    ws = torch.empty(ann.ann_search_workspace_bytes(g, m, Q, 4, 12, 170, 20, cap), dtype=torch.uint8, device="cuda")
+    _both(lambda: ann.ann_search_ragged(g, m, users, entries, *own, 12, 170, 20, cap, workspace=ws), ws)
+
+
+@pytest.mark.parametrize("shape", [TWO, ONE])
+def test_items_that_are_not_finite(shape):
+    Q = 2200
+    g, m, users, entries = _handles("bf16", *shape, 400, 16, Q, 8)
+    emb = torch.randn(400, 64).bfloat16()
+    emb[::9, 1], emb[3::11, 0], emb[5::13, 2] = float("inf"), float("-inf"), float("nan")
+    g = ann.ann_graph_load(torch.randint(0, 400, (400, 16), dtype=torch.int32).cuda(), emb.cuda())
+    ws = torch.empty(ann.ann_search_workspace_bytes(g, m, Q, 8, 4, 64, 200, 0), dtype=torch.uint8, device="cuda")
+    _both(lambda: ann.ann_search(g, m, users, entries, 4, 64, 200, 0, workspace=ws), ws)
+
+
+def test_a_batch_by_waves_reports_its_progress():
+    """A batch that takes longer than the 20 ms after which the waiting thread asks, under a limit far below that."""
+    Q = 16384
+    g, m, users, entries = _handles("bf16", *TWO, 200_000, 32, Q, 4)
+    ws = torch.empty(ann.ann_search_workspace_bytes(g, m, Q, 4, 4, 512, 10, 0), dtype=torch.uint8, device="cuda")
+    want = ann.ann_search(g, m, users, entries, 4, 512, 10, 0, workspace=ws)
+    assert int(ws[256:384].view(torch.int64)[8]) == Q
+    ann.ann_set_progress_timeout(2e-3)
+    try:
+        got = ann.ann_search(g, m, users, entries, 4, 512, 10, 0, workspace=ws)
+    finally:
+        ann.ann_set_progress_timeout(600.0)
+        torch.cuda.synchronize()
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
