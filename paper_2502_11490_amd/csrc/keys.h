@@ -55,6 +55,52 @@ __device__ void bitonic_sort(uint64_t *keys, int n) {
     __syncthreads();
 }
 
+// c0 += (a < k) + (c < k), c1 += (b < k) + (d < k), the two halves of a key in the words of a 16-byte piece.  Three full-rate
+// instructions a comparison, where one on 64 bits is slow, and four carries at a time, so that none is waited for.
+__device__ __forceinline__ void count_less4(uint32_t &c0, uint32_t &c1, const uint4 &ab, const uint4 &cd, uint64_t k) {
+    uint32_t t0, t1, t2, t3;
+    uint64_t v0, v1, v2, v3;
+    asm("v_sub_co_u32 %2, %6, %10, %18\n\tv_sub_co_u32 %3, %7, %12, %18\n\t"
+        "v_sub_co_u32 %4, %8, %14, %18\n\tv_sub_co_u32 %5, %9, %16, %18\n\t"
+        "v_subb_co_u32 %2, %6, %11, %19, %6\n\tv_subb_co_u32 %3, %7, %13, %19, %7\n\t"
+        "v_subb_co_u32 %4, %8, %15, %19, %8\n\tv_subb_co_u32 %5, %9, %17, %19, %9\n\t"
+        "v_addc_co_u32 %0, %6, 0, %0, %6\n\tv_addc_co_u32 %1, %7, 0, %1, %7\n\t"
+        "v_addc_co_u32 %0, %8, 0, %0, %8\n\tv_addc_co_u32 %1, %9, 0, %1, %9"
+        : "+v"(c0), "+v"(c1), "=&v"(t0), "=&v"(t1), "=&v"(t2), "=&v"(t3), "=&s"(v0), "=&s"(v1), "=&s"(v2), "=&s"(v3)
+        : "v"(ab.x), "v"(ab.y), "v"(ab.z), "v"(ab.w), "v"(cd.x), "v"(cd.y), "v"(cd.z), "v"(cd.w), "v"((uint32_t)k),
+          "v"((uint32_t)(k >> 32)));
+}
+
+// smaller[u] = how many of keys[0..n) are below key[u].  The keys are read as LDS broadcasts, eight at a time and eight ahead of
+// their use.  keys: LDS, 16-byte aligned, sentinels behind it up to a multiple of eight, room for eight more to be read.
+template <int PER>
+__device__ __forceinline__ void count_smaller(const uint64_t *keys, int n, const uint64_t (&key)[PER], uint32_t (&smaller)[PER]) {
+    const uint4 *k = (const uint4 *)keys;
+    uint4 a[4];
+    uint32_t odd[PER];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) a[i] = k[i];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) smaller[u] = odd[u] = 0;
+#pragma unroll 1
+    for (int c = 0; c < n; c += 8) {
+        uint4 ahead[4];
+        k += 4;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) ahead[i] = k[i];
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            count_less4(smaller[u], odd[u], a[0], a[1], key[u]);
+            count_less4(smaller[u], odd[u], a[2], a[3], key[u]);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) a[i] = ahead[i];
+    }
+#pragma unroll
+    for (int u = 0; u < PER; ++u) smaller[u] += odd[u];
+}
+constexpr int KEYS_SLACK = 16;  // keys behind the last one that count_smaller may read
+
 // First index of the ascending a[0..n) whose key is not below `key`.
 __device__ __forceinline__ int lower_bound_keys(const uint64_t *a, int n, uint64_t key) {
     int lo = 0, hi = n;

@@ -113,7 +113,7 @@ __device__ __forceinline__ void tile_hidden(const uint4 *__restrict__ frag, int6
 // acc[c] += W-block (16 units) * slabs of column block c (16 pairs), KS inputs-of-16.  w: this lane's four weights of
 // the block's first fragment (unit lane % 16, inputs 16 k + 4 u + lane / 16); fragments follow one another.
 template <int CB>
-__device__ __forceinline__ void tile_contract64(f64x4 (&acc)[CB], const float4 *__restrict__ w, int KS, const f64x2 *in,
+__device__ __forceinline__ void tile_contract64(f64x4 (&acc)[CB], const float4 *w, int KS, const f64x2 *in,
                                                 int in_slabs) {
     const int lane = threadIdx.x & 63;
     float4 a = w[0];
@@ -133,32 +133,39 @@ __device__ __forceinline__ void tile_contract64(f64x4 (&acc)[CB], const float4 *
     }
 }
 
-// A hidden layer: NB blocks of 16 units over the workgroup's waves.  A lane's four results of a block (units lane / 16
-// + 4 i of its pair) are its four operands of the next layer's fragment.
+// A block of 16 units of a hidden layer for CB column blocks.  A lane's four results (units lane / 16 + 4 i of its pair) are
+// its four operands of the next layer's fragment.  `in`, `out`: the first of the column blocks.
+template <int CB>
+__device__ __forceinline__ void tile_block64(const float4 *w, int KS, int nb, const float *bias, const f64x2 *in, int in_slabs,
+                                             f64x2 *out, int out_slabs) {
+    const int lane = threadIdx.x & 63, g = lane >> 4;
+    f64x4 acc[CB];
+#pragma unroll
+    for (int c = 0; c < CB; ++c)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[c][i] = (double)bias[nb * 16 + g + 4 * i];
+    tile_contract64<CB>(acc, w, KS, in, in_slabs);
+#pragma unroll
+    for (int c = 0; c < CB; ++c) {
+        f64x2 lo, hi;
+        lo[0] = acc[c][0] > 0.0 ? acc[c][0] : 0.0;
+        lo[1] = acc[c][1] > 0.0 ? acc[c][1] : 0.0;
+        hi[0] = acc[c][2] > 0.0 ? acc[c][2] : 0.0;
+        hi[1] = acc[c][3] > 0.0 ? acc[c][3] : 0.0;
+        f64x2 *s = out + ((size_t)c * out_slabs + nb) * 128 + lane;
+        s[0] = lo;
+        s[64] = hi;
+    }
+}
+
+// A hidden layer: NB blocks of 16 units over the workgroup's waves.
 template <int CB>
 __device__ __forceinline__ void tile_hidden64(const float4 *__restrict__ frag, int64_t base, int KS, int NB,
                                               const float *__restrict__ bias, const f64x2 *in, int in_slabs, f64x2 *out,
                                               int out_slabs, int n_waves) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g = lane >> 4;
-    for (int nb = wave; nb < NB; nb += n_waves) {
-        f64x4 acc[CB];
-#pragma unroll
-        for (int c = 0; c < CB; ++c)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) acc[c][i] = (double)bias[nb * 16 + g + 4 * i];
-        tile_contract64<CB>(acc, frag + (base + (int64_t)nb * KS) * 64 + lane, KS, in, in_slabs);
-#pragma unroll
-        for (int c = 0; c < CB; ++c) {
-            f64x2 lo, hi;
-            lo[0] = acc[c][0] > 0.0 ? acc[c][0] : 0.0;
-            lo[1] = acc[c][1] > 0.0 ? acc[c][1] : 0.0;
-            hi[0] = acc[c][2] > 0.0 ? acc[c][2] : 0.0;
-            hi[1] = acc[c][3] > 0.0 ? acc[c][3] : 0.0;
-            f64x2 *s = out + ((size_t)c * out_slabs + nb) * 128 + lane;
-            s[0] = lo;
-            s[64] = hi;
-        }
-    }
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (int nb = wave; nb < NB; nb += n_waves)
+        tile_block64<CB>(frag + (base + (int64_t)nb * KS) * 64 + lane, KS, nb, bias, in, in_slabs, out, out_slabs);
 }
 
 }  // namespace gmpgr

@@ -46,18 +46,14 @@ struct WaveArgs {
 template <int PER>
 __device__ __forceinline__ void wave_rank_sort(uint64_t *keys, int m, int lane) {
     uint64_t key[PER];
-    int rank[PER];
+    uint32_t rank[PER];
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
         key[u] = lane + 64 * u < m ? keys[lane + 64 * u] : KEY_SENTINEL;
-        rank[u] = 0;
     }
-#pragma unroll 8
-    for (int i = 0; i < m; ++i) {
-        const uint64_t x = keys[i];
-#pragma unroll
-        for (int u = 0; u < PER; ++u) rank[u] += x < key[u] ? 1 : 0;
-    }
+    if (lane < 8) keys[m + lane] = KEY_SENTINEL;
+    wave_lds_fence();
+    count_smaller<PER>(keys, m, key, rank);
     wave_lds_fence();
 #pragma unroll
     for (int u = 0; u < PER; ++u)
@@ -487,7 +483,7 @@ static bool wave_plan(const SearchArgs &a, int *nw, int *piece, WaveArgs *A, siz
     const size_t weights = two ? 104 * 1024 + 576 : 48 * 1024 + 64;
     *piece = wide > 128 ? 256 : 128;
     auto up16 = [](size_t v) { return (v + 15) & ~(size_t)15; };
-    const size_t at_keys = up16((size_t)p.C * 8), at_taken = at_keys + (size_t)*piece * 8, at_ut = at_taken + up16((size_t)((p.C + 63) >> 6) * 8),
+    const size_t at_keys = up16((size_t)p.C * 8), at_taken = at_keys + (size_t)(*piece + KEYS_SLACK) * 8, at_ut = at_taken + up16((size_t)((p.C + 63) >> 6) * 8),
                  at_parents = at_ut + 1024, bytes = at_parents + up16((size_t)p.W_max * 4);
     *nw = 0;
     const int fit = (int)((160 * 1024 - weights) / bytes), most = two ? 8 : 16, want = (p.Q + 255) / 256;
