@@ -165,7 +165,7 @@ struct Mailbox {
         }
         host = (volatile uint64_t *)h;
         dev = (uint64_t *)d;
-        for (int i = 0; i < 3; ++i) host[i] = 0;
+        for (int i = 0; i < 4; ++i) host[i] = 0;
         ok = true;
         return true;
     }
@@ -295,18 +295,20 @@ static int score_batch(const SearchArgs &a) {
 static const char NO_PROGRESS[] = "no progress report from the search's kernels within the time limit (ann_set_progress_timeout)";
 static const char RAN_DRY[] = "the stream failed or ran dry without the search's progress report";
 
+static int filled_error(const SearchArgs &a, int64_t filled) {
+    if (filled <= 0) return ANN_OK;
+    set_error("%lld queries filled their visited table (sized for %d rounds) and stopped early", (long long)filled,
+              a.plan.rounds_assumed);
+    return ANN_EWORKSPACE;
+}
+
 // Waits for the search and reports queries that stopped because their visited table was full.
 static int report_overflow(const SearchArgs &a) {
     const Plan &p = a.plan;
     int64_t stats[8];
     ANN_HIP_TRY(hipMemcpyAsync(stats, a.ws + p.off_stats, sizeof(stats), hipMemcpyDeviceToHost, a.stream));
     ANN_HIP_TRY(hipStreamSynchronize(a.stream));
-    if (stats[3] > 0) {
-        set_error("%lld queries filled their visited table (sized for %d rounds) and stopped early",
-                  (long long)stats[3], p.rounds_assumed);
-        return ANN_EWORKSPACE;
-    }
-    return ANN_OK;
+    return filled_error(a, stats[3]);
 }
 
 static int run_search(SearchArgs &a) {
@@ -341,7 +343,9 @@ static int run_search(SearchArgs &a) {
             set_error(g == -3 ? NO_PROGRESS : RAN_DRY);
             return ANN_EDEVICE;
         }
-        return report_overflow(a);
+        // the kernel has said how many queries stopped early: nothing is copied, the stream is about to be idle
+        ANN_HIP_TRY(hipStreamSynchronize(a.stream));
+        return filled_error(a, (int64_t)(box->host[MAIL_FILLED] & 0xFFFFFFFFFFull));
     }
     {
         StageTimer timer(ANN_STAGE_ROUND, a.stream);

@@ -113,8 +113,9 @@ struct ann_mlp {
 namespace gmpgr {
 
 // Words of the progress mailbox in pinned host memory (all carry the search's tag): rounds packed and finished,
-// queries still running (written once none is waiting), a sign of life of a search in one launch.
-enum { MAIL_ROUNDS = 0, MAIL_RUNNING = 1, MAIL_SIGN = 2 };
+// queries still running (written once none is waiting), a sign of life of a search in one launch, and in front of that
+// search's finished bit how many of its queries filled their visited table.
+enum { MAIL_ROUNDS = 0, MAIL_RUNNING = 1, MAIL_SIGN = 2, MAIL_FILLED = 3 };
 
 // Device workspace layout; every offset is in bytes from the workspace base, 256-aligned.
 struct Plan {

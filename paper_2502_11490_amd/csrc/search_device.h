@@ -418,4 +418,13 @@ __device__ __forceinline__ void add_to_totals(int64_t *stats, long long scored, 
     if (overflowed) atomicAdd((unsigned long long *)&stats[3], (unsigned long long)overflowed);
 }
 
+// The end of a search in one launch, by one thread once all queries have joined the totals: the number of those that filled
+// their visited table, then the finished bit.
+__device__ __forceinline__ void report_end(int64_t *stats, uint64_t *mailbox, uint64_t tag) {
+    const uint64_t filled = atomicAdd((unsigned long long *)&stats[3], 0ull);
+    __hip_atomic_store(mailbox + MAIL_FILLED, tag | filled, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __threadfence_system();
+    __hip_atomic_store(mailbox + MAIL_ROUNDS, tag | 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 }  // namespace gmpgr

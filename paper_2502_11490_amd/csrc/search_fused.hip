@@ -663,9 +663,7 @@ __global__ void __launch_bounds__(BLK, CB == 4 ? 2 : 4) fused_search_kernel(Fuse
         if (A.mailbox) {
             // the last query to end reports
             __threadfence_system();
-            if (atomicAdd(&A.ctrl->next_query, 1) == A.Q - 1) {
-                __hip_atomic_store(A.mailbox, A.mail_tag | 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-            }
+            if (atomicAdd(&A.ctrl->next_query, 1) == A.Q - 1) report_end(A.stats, A.mailbox, A.mail_tag);
         }
     }
 }

@@ -429,8 +429,7 @@ __global__ void __launch_bounds__(64 * MOST) wave_search_kernel(WaveArgs A) {
         add_to_totals(A.stats, scored, expanded, longest, overflowed);
         if (A.mailbox) {  // the last wave to end reports
             __threadfence_system();
-            if (atomicAdd(&A.ctrl->ended, ended) + ended == A.Q)
-                __hip_atomic_store(A.mailbox, A.mail_tag | 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            if (atomicAdd(&A.ctrl->ended, ended) + ended == A.Q) report_end(A.stats, A.mailbox, A.mail_tag);
         }
     }
 }
