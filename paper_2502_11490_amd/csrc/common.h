@@ -137,7 +137,8 @@ struct Ctrl {
     int32_t next_query;   // continuous batching: queries admitted so far (a closed batch may overshoot its total)
     int32_t avail;        // open stream: queries that have arrived so far
     int32_t ended;        // a search by waves: queries whose result is written
-    int32_t pad[11];
+    int32_t handed;       // ... queries that its last launch goes on with
+    int32_t pad[10];
 };
 
 // Per-query state at off_state.
@@ -200,6 +201,9 @@ constexpr size_t FUSED_LDS = 150 * 1024;
 bool fused_serves(const SearchArgs &a);
 int fused_tail(const SearchArgs &a);  // running queries from which on the tail goes there, 0 = never
 int launch_fused(const SearchArgs &a, int32_t rounds_max, int32_t tail);
+// the last queries of a search by waves, whose numbers (ctrl->handed of them, at most `most`) lie in the offsets' region
+bool fused_goes_on(const SearchArgs &a, int32_t most);
+int launch_fused_rest(const SearchArgs &a, int32_t rounds_max, int32_t most);
 
 // search_wave.hip: all rounds of a query by one wave
 bool wave_serves(const SearchArgs &a);

@@ -45,6 +45,7 @@ struct FusedArgs {
     uint64_t *pool;
     int32_t *counts;
     const int32_t *cand, *slot_query;
+    const int32_t *handed;      // searches that waves began: their numbers, ctrl->handed of them; results are written here
     int64_t N;
     int32_t seen_words, seen_bits;   // visited set in LDS (0: in memory): one bit per item, or slots of one id
     int32_t frag_words, bias_words;  // a metric kept in LDS, 0 = read from L2
@@ -421,7 +422,12 @@ __host__ __device__ inline void fused_lds(int C, int slots, int W_max, int seen_
 template <int BLK, bool BITMAP, int METRIC, int CB, bool RESUME>
 __global__ void __launch_bounds__(BLK, CB == 4 ? 2 : 4) fused_search_kernel(FusedArgs A) {  // waves a SIMD: see fused_plan
     extern __shared__ __align__(16) unsigned char smem[];
-    const int q = blockIdx.x, tid = threadIdx.x;
+    const int tid = threadIdx.x;
+    int q = blockIdx.x;
+    if (RESUME && A.handed) {
+        if (q >= __builtin_amdgcn_readfirstlane(A.ctrl->handed)) return;
+        q = __builtin_amdgcn_readfirstlane(A.handed[q]);
+    }
     FusedLds at;
     fused_lds(A.C, A.slots, A.W_max, A.seen_words, A.frag_words + A.bias_words, &at);
     uint64_t *cur = (uint64_t *)smem, *taken = (uint64_t *)(smem + at.taken);
@@ -438,10 +444,12 @@ __global__ void __launch_bounds__(BLK, CB == 4 ? 2 : 4) fused_search_kernel(Fuse
 
     int n_list = 0, n_visited = 0, n_expanded = 0, first_open = 0, t = 0, n_cand = A.E, user = q, pending = 0;
     if (RESUME) {
-        pending = __builtin_amdgcn_readfirstlane(A.counts[q]);
-        if (pending < 0) return;
         const QState *st = A.state + q;
-        if (__builtin_amdgcn_readfirstlane(st->done)) return;
+        if (!A.handed) {
+            pending = __builtin_amdgcn_readfirstlane(A.counts[q]);
+            if (pending < 0) return;
+            if (__builtin_amdgcn_readfirstlane(st->done)) return;
+        }
         n_list = __builtin_amdgcn_readfirstlane(st->n_list);
         n_visited = __builtin_amdgcn_readfirstlane(st->n_visited);
         n_expanded = __builtin_amdgcn_readfirstlane(st->n_expanded);
@@ -637,7 +645,7 @@ __global__ void __launch_bounds__(BLK, CB == 4 ? 2 : 4) fused_search_kernel(Fuse
         __syncthreads();
     }
     __syncthreads();
-    if (RESUME) {
+    if (RESUME && !A.handed) {
         for (int i = tid; i < n_list; i += BLK) A.pool[(size_t)q * A.C + i] = cur[i];
         if (tid == 0) {
             QState *st = A.state + q;
@@ -663,7 +671,7 @@ __global__ void __launch_bounds__(BLK, CB == 4 ? 2 : 4) fused_search_kernel(Fuse
         if (A.mailbox) {
             // the last query to end reports
             __threadfence_system();
-            if (atomicAdd(&A.ctrl->next_query, 1) == A.Q - 1) report_end(A.stats, A.mailbox, A.mail_tag);
+            if (atomicAdd(RESUME ? &A.ctrl->ended : &A.ctrl->next_query, 1) == A.Q - 1) report_end(A.stats, A.mailbox, A.mail_tag);
         }
     }
 }
@@ -707,12 +715,12 @@ static size_t fused_smem(const SearchArgs &a, const TileNet &T, bool f64, int cb
 }
 
 template <int BLK, int METRIC, int CB, bool RESUME>
-static int fused_launch(const SearchArgs &a, const FusedArgs &A, size_t smem) {
+static int fused_launch(const SearchArgs &a, const FusedArgs &A, size_t smem, int grid) {
     const bool bm = a.plan.bitmap_words > 0;
     auto fn = bm ? fused_search_kernel<BLK, true, METRIC, CB, RESUME> : fused_search_kernel<BLK, false, METRIC, CB, RESUME>;
     static std::atomic<uint32_t> raised[2];
     if (int rc = raise_lds_limit((const void *)fn, FUSED_LDS, a.m->device, raised[bm ? 1 : 0]); rc != ANN_OK) return rc;
-    hipLaunchKernelGGL(fn, dim3(a.plan.Q), dim3(BLK), smem, a.stream, A);
+    hipLaunchKernelGGL(fn, dim3(grid), dim3(BLK), smem, a.stream, A);
     ANN_HIP_TRY(hipGetLastError());
     return ANN_OK;
 }
@@ -818,16 +826,14 @@ int fused_tail(const SearchArgs &a) {
     return fused_takes(a, 512) ? 512 : fused_takes(a, 256) ? 256 : 0;
 }
 
-int launch_fused(const SearchArgs &a, int32_t rounds_max, int32_t tail) {
+static FusedArgs fused_args(const SearchArgs &a, const FusedPlan &f, int32_t rounds_max, bool resume) {
     const Plan &p = a.plan;
     const ann_mlp *m = a.m;
     FusedArgs A{};
-    FusedPlan f;
-    if (!fused_plan(a, tail > 0 ? tail : p.Q, &f)) return ANN_EINVAL;
     A.T = f.T;
     A.new_cap = f.new_cap;
     A.frag_words = f.frag_words, A.bias_words = f.bias_words;
-    A.seen_words = tail > 0 ? 0 : f.seen_words, A.seen_bits = tail > 0 ? 0 : f.seen_bits;
+    A.seen_words = resume ? 0 : f.seen_words, A.seen_bits = resume ? 0 : f.seen_bits;
     const bool built_in = m->kernel == MLP_MFMA2, f64 = m->dtype == ANN_F32, bm = p.bitmap_words > 0;
     A.frag = built_in ? m->frag_dev : m->any_dev;
     A.b = m->b_dev;
@@ -862,21 +868,47 @@ int launch_fused(const SearchArgs &a, int32_t rounds_max, int32_t tail) {
     A.int_relu = built_in && m->n_layers == 3 && mfma_stream_supported(m->d_item, m->dims[1], m->dims[2]);
     A.wide_loads = ((uintptr_t)a.g->emb & 15) == 0 && (m->d_item & 7) == 0 &&
                    (built_in || ((m->d_user & 7) == 0 && ((uintptr_t)a.queries & 15) == 0));
+    return A;
+}
+
+int launch_fused(const SearchArgs &a, int32_t rounds_max, int32_t tail) {
+    const Plan &p = a.plan;
+    const ann_mlp *m = a.m;
+    FusedPlan f;
+    if (!fused_plan(a, tail > 0 ? tail : p.Q, &f)) return ANN_EINVAL;
+    const FusedArgs A = fused_args(a, f, rounds_max, tail > 0);
+    const bool f64 = m->dtype == ANN_F32;
     if (tail <= 0)
         if (int rc = launch_zero_stats(a, p.Q); rc != ANN_OK) return rc;
 #define FUSED_PICK(METRIC, RESUME)                                \
-    (f.cb == 4   ? fused_launch<512, METRIC, 4, RESUME>(a, A, f.smem)  \
-     : f.cb == 2 ? fused_launch<512, METRIC, 2, RESUME>(a, A, f.smem)  \
-               : fused_launch<256, METRIC, 1, RESUME>(a, A, f.smem))
+    (f.cb == 4   ? fused_launch<512, METRIC, 4, RESUME>(a, A, f.smem, p.Q)  \
+     : f.cb == 2 ? fused_launch<512, METRIC, 2, RESUME>(a, A, f.smem, p.Q)  \
+               : fused_launch<256, METRIC, 1, RESUME>(a, A, f.smem, p.Q))
     if (tail > 0)
         return f64                     ? FUSED_PICK(FUSED_F64, true)
                : m->dtype == ANN_F16   ? FUSED_PICK(FUSED_F16, true)
                                        : FUSED_PICK(FUSED_BF16, true);
     if (f.held && m->n_layers == 3)
-        return m->dtype == ANN_F16 ? fused_launch<512, FUSED_TWO + 1, 4, false>(a, A, f.smem) : fused_launch<512, FUSED_TWO, 4, false>(a, A, f.smem);
-    if (f.held) return m->dtype == ANN_F16 ? fused_launch<512, FUSED_ONE + 1, 4, false>(a, A, f.smem) : fused_launch<512, FUSED_ONE, 4, false>(a, A, f.smem);
+        return m->dtype == ANN_F16 ? fused_launch<512, FUSED_TWO + 1, 4, false>(a, A, f.smem, p.Q) : fused_launch<512, FUSED_TWO, 4, false>(a, A, f.smem, p.Q);
+    if (f.held) return m->dtype == ANN_F16 ? fused_launch<512, FUSED_ONE + 1, 4, false>(a, A, f.smem, p.Q) : fused_launch<512, FUSED_ONE, 4, false>(a, A, f.smem, p.Q);
     return f64 ? FUSED_PICK(FUSED_F64, false) : m->dtype == ANN_F16 ? FUSED_PICK(FUSED_F16, false) : FUSED_PICK(FUSED_BF16, false);
 #undef FUSED_PICK
+}
+
+bool fused_goes_on(const SearchArgs &a, int32_t most) {
+    FusedPlan f;
+    return fused_plan(a, most, &f) && f.held;
+}
+
+int launch_fused_rest(const SearchArgs &a, int32_t rounds_max, int32_t most) {
+    const ann_mlp *m = a.m;
+    FusedPlan f;
+    if (!fused_plan(a, most, &f) || !f.held) return ANN_EINVAL;
+    FusedArgs A = fused_args(a, f, rounds_max, true);
+    A.handed = (const int32_t *)(a.ws + a.plan.off_offsets);
+    if (m->n_layers == 3)
+        return m->dtype == ANN_F16 ? fused_launch<512, FUSED_TWO + 1, 4, true>(a, A, f.smem, most) : fused_launch<512, FUSED_TWO, 4, true>(a, A, f.smem, most);
+    return m->dtype == ANN_F16 ? fused_launch<512, FUSED_ONE + 1, 4, true>(a, A, f.smem, most) : fused_launch<512, FUSED_ONE, 4, true>(a, A, f.smem, most);
 }
 
 }  // namespace gmpgr

@@ -14,13 +14,19 @@
 // take 22 us a round, and the scattered accesses of a round (128 visited words, 75 item rows, 75 dirty lines) share
 // the memory's bandwidth.
 // Against the batch path and, up to 1,024 queries, the search by workgroups: 1,024 queries of 10^6 items, lists of 512
-// 6.1 -> 3.7 ms; 16,384 queries of 2 10^7 items, one hidden layer, lists of 64 8.3 -> 4.7; 8,192 ragged capped queries
+// 6.1 -> 3.3 ms; 16,384 queries of 2 10^7 items, one hidden layer, lists of 64 8.3 -> 4.7; 8,192 ragged capped queries
 // 7.4 -> 4.6.
 #include "mlp_tile.h"
 #include "search_device.h"
 
 namespace gmpgr {
 
+
+// Running queries from which on a workgroup per query goes on with them (search_fused.hip): it takes half the time for a
+// round, and the longest searches run half as many rounds again as the average one.  Both sides measured, ms: 1,024 queries
+// with lists of 512 3.70 -> 3.26, 300 with W = 4, L = 64 1.02 -> 0.81, 2,048 with W = 16, L = 256 4.5 -> 3.9, 8,192 with
+// W = 4, L = 512 17.3 -> 16.2; 16,384 with lists of 64 the same.
+constexpr int WAVE_HAND = 256;
 
 struct WaveArgs {
     const uint4 *frag;
@@ -29,6 +35,11 @@ struct WaveArgs {
     const uint16_t *emb;
     const int32_t *adj, *adj_rank, *rank, *entries;
     const int32_t *W_q, *L_q, *cap_q, *order;
+    // from `hand_at` running queries on (0: never) a query's list and state go to memory and its number to `handed`
+    QState *state;
+    uint64_t *pool;
+    int32_t *handed;
+    int32_t hand_at;
     uint32_t *table;
     int64_t *stats;
     Ctrl *ctrl;
@@ -287,9 +298,14 @@ __global__ void __launch_bounds__(64 * MOST) wave_search_kernel(WaveArgs A) {
             wave_lds_fence();
         }
         int n_list = 0, n_visited = 0, n_expanded = 0, first_open = 0, t = 0, n_cand = A.E;
-        bool seeding = true, overflow = false;
+        bool seeding = true, overflow = false, handed = false;
+        // among the last queries: nothing waits any more when few are left
+        const bool may_hand = A.hand_at > 0 && turn + slots >= A.Q;
         // bounded: a search cannot run more rounds than its cap or than ids fit its visited set
         for (int round = 0; round <= A.rounds_max; ++round) {
+            int gone = 0;  // queries that have ended; looked at after the round's work
+            if (may_hand && (round & 3) == 3)
+                gone = __hip_atomic_load(&A.ctrl->next_query, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             // the candidates (the seeds, later one adjacency row per parent) piece by piece through the visited set, the
             // metric and into the list; which of them the list keeps does not depend on how they are cut
             for (int p0 = 0; p0 < n_cand; p0 += 64 * U) {
@@ -370,6 +386,11 @@ __global__ void __launch_bounds__(64 * MOST) wave_search_kernel(WaveArgs A) {
                 }
             }
 
+            if (A.Q - __builtin_amdgcn_readfirstlane(gone) <= A.hand_at && may_hand && (round & 3) == 3) {
+                handed = true;
+                break;
+            }
+
             // termination test and choice of the parents: the first <= W unexpanded entries among the first L ranks
             int n_par = 0;
             if (!(cap > 0 && t >= cap)) {
@@ -408,6 +429,19 @@ __global__ void __launch_bounds__(64 * MOST) wave_search_kernel(WaveArgs A) {
             if (A.mailbox && (t & 7) == 7 && ((q + (t >> 3)) & 31) == 0 && lane == 0)
                 __hip_atomic_store(A.mailbox + MAIL_SIGN, A.mail_tag | ((uint32_t)q << 8 ^ (uint32_t)t), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         }
+        if (handed) {
+            for (int i = lane; i < n_list; i += 64) A.pool[(size_t)q * A.C + i] = list[i];
+            if (lane == 0) {
+                QState *st = A.state + q;
+                st->t = t;
+                st->n_list = n_list;
+                st->n_visited = n_visited;
+                st->n_expanded = n_expanded;
+                st->first_open = first_open;
+                A.handed[atomicAdd(&A.ctrl->handed, 1)] = q;
+            }
+            break;  // nothing waits
+        }
         for (int i = lane; i < A.k; i += 64) {
             const bool held = i < n_list;
             const uint64_t key = held ? list[i] : 0;
@@ -420,7 +454,7 @@ __global__ void __launch_bounds__(64 * MOST) wave_search_kernel(WaveArgs A) {
         overflowed += overflow ? 1 : 0;
         ++ended;
         wave_lds_fence();
-        if (A.Q <= slots) break;
+        if (A.Q <= slots && A.hand_at == 0) break;
         int next = 0;
         if (lane == 0) next = atomicAdd(&A.ctrl->next_query, 1);
         turn = slots + __builtin_amdgcn_readfirstlane(next);
@@ -552,6 +586,10 @@ int launch_wave(const SearchArgs &a, int32_t rounds_max) {
     A.hash_cap = p.hash_cap;
     A.Q = p.Q;
     A.rounds_max = rounds_max;
+    A.state = (QState *)(a.ws + p.off_state);
+    A.pool = (uint64_t *)(a.ws + p.off_pool);
+    A.handed = (int32_t *)(a.ws + p.off_offsets);  // [Q], unused by this path otherwise
+    A.hand_at = p.max_iters_max == 0 && fused_goes_on(a, WAVE_HAND) ? WAVE_HAND : 0;
     if (int rc = launch_zero_stats(a, p.Q <= 1024 ? p.Q : 0, p.Q); rc != ANN_OK) return rc;
     if (a.W_q || a.L_q || a.cap_q) {
         int32_t *order = (int32_t *)(a.ws + p.off_counts);  // [Q], unused by this path otherwise
@@ -560,10 +598,13 @@ int launch_wave(const SearchArgs &a, int32_t rounds_max) {
         A.order = order;
     }
 #define WAVE_PICK(TWO, F16, MOST) (piece > 128 ? wave_launch<TWO, F16, MOST, 4>(a, A, nw, smem) : wave_launch<TWO, F16, MOST, 2>(a, A, nw, smem))
-    if (two && f16) return nw <= 4 ? WAVE_PICK(true, true, 4) : WAVE_PICK(true, true, 8);
-    if (two) return nw <= 4 ? WAVE_PICK(true, false, 4) : WAVE_PICK(true, false, 8);
-    if (f16) return nw <= 4 ? WAVE_PICK(false, true, 4) : nw <= 8 ? WAVE_PICK(false, true, 8) : WAVE_PICK(false, true, 16);
-    return nw <= 4 ? WAVE_PICK(false, false, 4) : nw <= 8 ? WAVE_PICK(false, false, 8) : WAVE_PICK(false, false, 16);
+    int rc = ANN_OK;
+    if (two && f16) rc = nw <= 4 ? WAVE_PICK(true, true, 4) : WAVE_PICK(true, true, 8);
+    else if (two) rc = nw <= 4 ? WAVE_PICK(true, false, 4) : WAVE_PICK(true, false, 8);
+    else if (f16) rc = nw <= 4 ? WAVE_PICK(false, true, 4) : nw <= 8 ? WAVE_PICK(false, true, 8) : WAVE_PICK(false, true, 16);
+    else rc = nw <= 4 ? WAVE_PICK(false, false, 4) : nw <= 8 ? WAVE_PICK(false, false, 8) : WAVE_PICK(false, false, 16);
+    if (rc != ANN_OK || A.hand_at == 0) return rc;
+    return launch_fused_rest(a, rounds_max, WAVE_HAND);
 #undef WAVE_PICK
 }
 

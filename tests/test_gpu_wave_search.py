@@ -26,6 +26,7 @@ def _both(call, ws):
     assert torch.equal(runs[0][0], runs[1][0])
     assert torch.equal(runs[0][1].view(torch.int32), runs[1][1].view(torch.int32))  # NaN too
     assert runs[0][2] == runs[1][2]
+    return runs[1]
 
 
 @pytest.mark.parametrize("visited", ["hash", "bitmap", "rank"])
@@ -85,3 +86,41 @@ def test_a_batch_by_waves_reports_its_progress():
         ann.ann_set_progress_timeout(600.0)
         torch.cuda.synchronize()
     assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+
+
+@pytest.mark.parametrize("far", [100, 900])
+@pytest.mark.parametrize("hidden", [(256, 128), (256,)])
+def test_visited_table_that_fills_up(hidden, far, monkeypatch):
+    """Items whose relevance rises with their id (id / 64 and id % 64 are two exact coordinates), each joined to the next 16: a
+    table of 2,048 slots takes 1,024 ids, and queries that start far from the last item stop when it is full.  100 of them
+    are all that run when the waves hand the last 256 queries over, of 900 many end before."""
+    monkeypatch.setenv("GMPGR_VISITED_SET", "hash")
+    N, R, k, Q, d = 8000, 16, 3, 2100, 64
+    i = torch.arange(N, device="cuda")
+    emb = torch.zeros(N, d, device="cuda")
+    emb[:, 0], emb[:, 1] = (i // 64).float(), (i % 64).float()
+    adj = i[:, None] + 1 + torch.arange(R, device="cuda")
+    adj = torch.where(adj < N, adj, -1).int()
+    dims = [2 * d, *hidden, 1]
+    Ws = [torch.zeros(o, n) for n, o in zip(dims, dims[1:])]
+    Ws[0][0, d], Ws[0][1, d + 1] = 1, 1
+    for w in Ws[1:-1]:
+        w[0, 0], w[1, 1] = 1, 1
+    Ws[-1][0, 0], Ws[-1][0, 1] = 2.0 ** -4, 2.0 ** -10
+    bs = [torch.zeros(o) for o in dims[1:-1]] + [torch.tensor([-4.0])]
+    g = ann.ann_graph_load(adj, emb.bfloat16())
+    m = ann.ann_mlp_load([w.bfloat16() for w in Ws], bs, torch.ones(1), d, ann.ANN_BF16)
+    start = torch.full((Q,), N - 30, dtype=torch.int32)
+    start[torch.arange(far) * Q // far] = torch.linspace(0, N - 1100, far).int()
+    entries, users = start[:, None].contiguous().cuda(), torch.zeros(Q, d, device="cuda").bfloat16()
+    ws = torch.empty(ann.ann_search_workspace_bytes(g, m, Q, 1, 1, 1, k, 0), dtype=torch.uint8, device="cuda")
+    out = torch.empty(Q, k, dtype=torch.int32, device="cuda"), torch.empty(Q, k, device="cuda")
+
+    def call():
+        with pytest.raises(ann.AnnError) as e:
+            ann.ann_search(g, m, users, entries, 1, 1, k, 0, workspace=ws, out_ids=out[0].fill_(-7), out_scores=out[1])
+        assert e.value.code == -5 and "visited table" in str(e.value)
+        return out
+    ids, _, counters = _both(call, ws)
+    assert torch.equal(ids[:, 0].cpu(), (start + 16 * 63).clamp(max=N - 1))  # 1 + 16 * 63 ids fit, 16 more do not
+    assert counters[3] == far
