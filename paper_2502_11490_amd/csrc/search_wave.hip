@@ -502,14 +502,15 @@ __global__ void __launch_bounds__(1024) wave_order_kernel(WaveArgs A, int32_t *o
 //     7.6 -> 4.5.
 // So: a wave per query from 257 queries on (below, a workgroup per query has a CU to itself), unless a round's pairs are
 // many for the number of queries (a wave scores them alone) or long lists leave room for four waves only and rounds are
-// wide.  Batches of 1,025 to 2,047 queries stay with the batch path, whose last queries end in one launch.
+// wide.  1,025 to 2,000 queries: W = 4, L = 64 1.9 -> 1.1, W = 1, L = 256 12.1 -> 5.3, W = 16, L = 1,200 11.5 -> 9.7, W = 32,
+// L = 1,000 8.3 either way; one hidden layer, W = 4, L = 300 5.5 -> 2.7.
 static bool wave_plan(const SearchArgs &a, int *nw, int *piece, WaveArgs *A, size_t *smem) {
     const Plan &p = a.plan;
     const ann_mlp *m = a.m;
     if (a.walkers || a.Q_total != 0 || m->kernel != MLP_MFMA2 || (m->dtype != ANN_BF16 && m->dtype != ANN_F16)) return false;
     if (m->d_item != 64 || m->dims[1] != 256 || (m->n_layers == 3 && m->dims[2] != 128)) return false;
     const int wide = p.W_max * p.R;  // candidates of a round
-    if (p.Q <= 256 || (p.Q > 1024 && p.Q < 2048)) return false;
+    if (p.Q <= 256) return false;
     if (p.Q <= 1024 && p.Q <= 2 * wide && (p.Q <= 768 || wide > 512)) return false;
     if (((uintptr_t)a.g->emb & 15) != 0) return false;
     const bool two = m->n_layers == 3;

@@ -40,7 +40,7 @@ def test_search_by_waves_is_the_staged_search(dtype, shape, visited, monkeypatch
     for Q, R, E, W, L, k, cap in [(2048, 32, 4, 4, 64, 100, 0), (2049, 16, 1, 1, 1, 5, 0), (2100, 1, 2, 3, 33, 7, 0),
                                   (4097, 24, 3, 5, 100, 20, 0), (2050, 32, 300, 9, 200, 11, 0), (2048, 32, 2, 12, 250, 40, 9),
                                   (9000, 17, 4, 2, 40, 10, 7), (2048, 16, 4, 4, 900, 30, 0), (2051, 16, 1024, 8, 2500, 30, 0),
-                                  (300, 32, 4, 4, 64, 100, 0), (777, 8, 5, 7, 131, 9, 0), (1024, 32, 4, 16, 300, 50, 5)]:
+                                  (1025, 32, 4, 4, 64, 100, 0), (1300, 16, 4, 16, 500, 30, 6), (300, 32, 4, 4, 64, 100, 0), (777, 8, 5, 7, 131, 9, 0), (1024, 32, 4, 16, 300, 50, 5)]:
         g, m, users, entries = _handles(dtype, *shape, 3001, R, Q, E)
         if visited == "rank":
             rank = torch.randperm(3001, generator=torch.Generator().manual_seed(1)).to(torch.int32).cuda()
