@@ -427,7 +427,7 @@ int ann_search_stats(const void *workspace_dev, ann_stats *out_host, void *strea
  * stream.  Stages: ANN_STAGE_SCORE = the MLP relevance kernel (Sec. 3.1), ANN_STAGE_ROUND =
  * seeding and the per-query round kernel (merge, choice of parents, neighbour gather, visited
  * filter; Algorithm 1), ANN_STAGE_PACK = prefix sum + packing of the ragged groups (Algorithm 2).
- * Small batches, which otherwise run as one launch for the whole search, run stage by stage meanwhile, with the
+ * Searches that otherwise run as one or two launches (small batches; the metrics of 64-wide items), run stage by stage meanwhile, with the
  * same results.
  * ann_profile_read waits for the recorded events, writes per stage the summed elapsed
  * milliseconds and the number of launches since the last read (arrays of ANN_STAGE_COUNT),

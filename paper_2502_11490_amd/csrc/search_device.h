@@ -55,8 +55,8 @@ __device__ void rank_sort(uint64_t *keys, int m, uint32_t *cnt) {
     __syncthreads();
 }
 
-// The visited filters of the walkers, which need the first of equal candidates to win: whose neighbour it is decides where a
-// walker goes next.
+// The ordered visited filters: the first of equal candidates wins.  The walkers need that (whose neighbour it is decides where
+// a walker goes next); the bitmap's serves the batch path's rounds too where it is the faster one.
 //
 // Drops ids that are out of range, repeated inside cand[0..n_cand) (first occurrence kept)
 // or already in this query's visited table; inserts the rest into the table and writes them,

@@ -29,7 +29,7 @@ constexpr int WAVES = BLOCK / 64;
 #define ROUND_BIG_FROM 512   // candidates per query and round above which the round kernel runs larger workgroups
 #endif
 #ifndef FILTER_CHUNK
-#define FILTER_CHUNK 1024   // walkers: candidates of a round that pass the visited filter together
+#define FILTER_CHUNK 1024   // candidates of a round that pass an ordered visited filter together
 #endif
 #ifndef ROUND_TILE_MAX
 #define ROUND_TILE_MAX 4096   // most list entries held in LDS at a time during the merge
@@ -367,14 +367,16 @@ scan_compact_kernel(const int32_t *__restrict__ counts, int Q, const int32_t *__
 // BITMAP: the visited set is one bit per item (hash_cap < 0), else the hash table.  RESIDENT: the whole list fits one tile
 // (C <= tile_keys); it is then requested at the very start, together with the state, merged into a second LDS copy, and
 // the parents are chosen from that copy: two dependent trips to memory fewer per round than the tiled walk, which is what
-// short lists are bound by.  WALKERS: the paper-literal rule, whose visited filter keeps the first of equal candidates.
-template <int BLK, bool BITMAP, bool RESIDENT, bool WALKERS>
+// short lists are bound by.  FILTER: see filter_of.
+enum { FILTER_ATOMIC = 0, FILTER_ORDERED = 1, FILTER_WALKERS = 2 };
+template <int BLK, bool BITMAP, bool RESIDENT, int FILTER>
 __global__ void __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(ROUND_WAVES_MIN, 8)))
 round_kernel(const int32_t *__restrict__ adj, const int32_t *__restrict__ adj_rank, int R, int64_t N, QState *state,
              uint64_t *pool_g, int C,
              uint32_t *hash, int hash_cap, int32_t *cand_g, int slots, int32_t *counts,
              const int32_t *__restrict__ offsets, const float *__restrict__ scores, int new_cap,
              int W_max, int64_t *stats, uint16_t *tag_g, int tile_keys, int chunk) {
+    constexpr bool WALKERS = FILTER == FILTER_WALKERS;
     extern __shared__ __align__(16) unsigned char smem[];
     const int q = blockIdx.x;
     PHASE_START
@@ -585,9 +587,8 @@ round_kernel(const int32_t *__restrict__ adj, const int32_t *__restrict__ adj_ra
     const int n_cand = n_par * R;
     uint32_t *table = hash + (size_t)q * (size_t)(BITMAP ? -hash_cap : hash_cap);
     int n_new = 0;
-    if (WALKERS) {
-        // In pieces of at most `chunk` (what the dedupe tables in LDS hold), which of equal candidates comes first
-        // decides whose it is.  An id that comes again in a later piece is dropped there because the earlier piece has
+    if (FILTER != FILTER_ATOMIC) {
+        // In pieces of at most `chunk` (what the dedupe tables in LDS hold); the first of equal candidates is kept.  An id that comes again in a later piece is dropped there because the earlier piece has
         // entered it into the visited set.
         if (RESIDENT) __syncthreads();  // the LDS copies of the list are dead from here on; their space is reused
         int dd_n = 2;
@@ -610,10 +611,10 @@ round_kernel(const int32_t *__restrict__ adj, const int32_t *__restrict__ adj_ra
             __syncthreads();
             if (BITMAP)
                 n_new += filter_and_mark<BLK>(cand, cand_rank, nc, dd_key, dd_pos, bk_key, bk_cnt, dd_n, table, N,
-                                              cand_q + n_new, wave_sums, tag_q + n_new, R, c0);
+                                              cand_q + n_new, wave_sums, WALKERS ? tag_q + n_new : nullptr, R, c0);
             else
                 n_new += filter_and_insert<BLK>(cand, nc, dd_key, dd_pos, bk_key, bk_cnt, dd_n, table, hash_cap, N,
-                                                cand_q + n_new, wave_sums, tag_q + n_new, R, c0);
+                                                cand_q + n_new, wave_sums, WALKERS ? tag_q + n_new : nullptr, R, c0);
         }
     } else {
         auto neighbour = [&](int j, uint32_t *bit) {
@@ -685,24 +686,35 @@ static int tile_keys_of(const Plan &p) {
 // Does the visited bitmap of this search go by the graph's locality order?
 static bool ranked(const ann_graph *g, const Plan &p) { return p.bitmap_words > 0 && g->adj_rank != nullptr; }
 
-// Walkers: candidates that go through the visited filter together.
+// Candidates that go through an ordered filter together.
 static int filter_chunk(const ann_graph *g, const Plan &p) {
     const int most = ranked(g, p) ? FILTER_CHUNK / 2 : FILTER_CHUNK;
     return p.slots < most ? p.slots : most;
 }
 
-// LDS of the walkers' filter over n candidates, dedupe tables included
+// LDS of an ordered filter over n candidates, dedupe tables included
 static size_t filter_smem(const ann_graph *g, const Plan &p, int n) {
     int dd_n = 2;
     while (dd_n < 2 * n) dd_n <<= 1;
     return (size_t)((n + 3) & ~3) * 4 * (ranked(g, p) ? 2 : 1) + (size_t)dd_n * 16;
 }
 
+// Which visited filter a round uses.  Atomics, one a candidate, with a hash table (16,384 queries 8.3 -> 8.1 ms, 6,001 in slots
+// 30.0 -> 29.1).  On a bitmap they are ahead where every thread has two candidates, which then go through in one pass (2,048
+// 8-bit queries of 512 candidates 29.5 -> 28.2 ms); with one a thread, and with 2,048 candidates in pieces of 512, the
+// ordered filter's loads and plain stores are (4,096 queries, 256 candidates 47.7 against 48.5 ms; 2,048 254 against 255).
+// The walkers' rule needs the first of equal candidates.
+static int filter_of(const SearchArgs &a, int threads) {
+    const Plan &p = a.plan;
+    if (a.walkers) return FILTER_WALKERS;
+    return p.bitmap_words > 0 && (p.slots <= threads || p.slots > 2 * threads) ? FILTER_ORDERED : FILTER_ATOMIC;
+}
+
 // list_keys: list entries held in LDS (0: one tile)
-static size_t round_smem(const SearchArgs &a, int list_keys = 0) {
+static size_t round_smem(const SearchArgs &a, int filter, int list_keys = 0) {
     const Plan &p = a.plan;
     const size_t lists = (size_t)(new_cap_of(p) + ((p.W_max + 1) & ~1) + (list_keys > 0 ? list_keys : tile_keys_of(p))) * 8;
-    const size_t filt = a.walkers ? filter_smem(a.g, p, filter_chunk(a.g, p)) : 0;
+    const size_t filt = filter != FILTER_ATOMIC ? filter_smem(a.g, p, filter_chunk(a.g, p)) : 0;
     return (size_t)((p.W_max + 3) & ~3) * 4 + 24 * 4 + (lists > filt ? lists : filt);
 }
 
@@ -792,19 +804,22 @@ int launch_round(const SearchArgs &a) {
     const bool bm = p.bitmap_words > 0;
     const bool resident = !big && p.C <= tile_keys_of(p);
     const int tile_keys = resident ? ((p.C + 1) & ~1) : tile_keys_of(p);  // resident: the list itself, twice
-    const size_t smem = resident ? round_smem(a, tile_keys + p.C) : round_smem(a);
-    using Fn = decltype(&round_kernel<BLOCK, false, false, false>);
+    const int filter = filter_of(a, threads);
+    const size_t smem = resident ? round_smem(a, filter, tile_keys + p.C) : round_smem(a, filter);
+    using Fn = decltype(&round_kernel<BLOCK, false, false, FILTER_ATOMIC>);
     Fn fn;
-#define ROUND_FN(BLK, RESIDENT, WALKERS) (bm ? round_kernel<BLK, true, RESIDENT, WALKERS> : round_kernel<BLK, false, RESIDENT, WALKERS>)
-    if (a.walkers) fn = big ? ROUND_FN(ROUND_BIG_BLOCK, false, true) : resident ? ROUND_FN(BLOCK, true, true) : ROUND_FN(BLOCK, false, true);
-    else if (big) fn = ROUND_FN(ROUND_BIG_BLOCK, false, false);
-    else if (half) fn = resident ? ROUND_FN(128, true, false) : ROUND_FN(128, false, false);
-    else fn = resident ? ROUND_FN(BLOCK, true, false) : ROUND_FN(BLOCK, false, false);
+#define ROUND_FN(BLK, RESIDENT)                                                                                                \
+    (filter == FILTER_WALKERS ? (bm ? round_kernel<BLK, true, RESIDENT, FILTER_WALKERS> : round_kernel<BLK, false, RESIDENT, FILTER_WALKERS>) \
+     : filter == FILTER_ORDERED ? round_kernel<BLK, true, RESIDENT, FILTER_ORDERED>                                             \
+                                : (bm ? round_kernel<BLK, true, RESIDENT, FILTER_ATOMIC> : round_kernel<BLK, false, RESIDENT, FILTER_ATOMIC>))
+    if (big) fn = ROUND_FN(ROUND_BIG_BLOCK, false);
+    else if (half) fn = resident ? ROUND_FN(128, true) : ROUND_FN(128, false);
+    else fn = resident ? ROUND_FN(BLOCK, true) : ROUND_FN(BLOCK, false);
 #undef ROUND_FN
     if (smem > 48 * 1024) {
-        static std::atomic<uint32_t> raised[24];
+        static std::atomic<uint32_t> raised[36];
         if (int rc = raise_lds_limit((const void *)fn, 128 * 1024, a.m->device,
-                                     raised[8 * which + (bm ? 4 : 0) + (a.walkers ? 2 : 0) + (resident ? 1 : 0)]);
+                                     raised[12 * which + (bm ? 6 : 0) + 2 * filter + (resident ? 1 : 0)]);
             rc != ANN_OK)
             return rc;
     }
