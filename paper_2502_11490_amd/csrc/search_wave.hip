@@ -491,19 +491,56 @@ __global__ void __launch_bounds__(1024) wave_order_kernel(WaveArgs A, int32_t *o
     for (int q = threadIdx.x; q < A.Q; q += 1024) order[atomicAdd(&start[bin(q)], 1)] = q;
 }
 
+// Long lists leave room for nw waves a CU where the batch wants more: is it still ahead of the batch path (up to 1,024
+// queries: of the workgroup per query, where that serves the call)?  Rounds of a wave get hardly faster when it has its CU to
+// itself, so the batch goes through in turns of 256 nw queries, while the batch path spreads every round over the chip;
+// that one pays three launches for every round, also for those in which few queries or none are left.  Measured on
+// 2 10^6 items with 32 neighbours, without / here, > 1 is a gain; "two", "one": hidden layers:
+//   nw = 4  8,192 queries, W = 4, L = 1,024 1.21 (L = 1,200 1.10 at 16,384), W = 8, L = 1,000 1.16, W = 16, L = 1,024 1.07; one
+//           8,192, W = 4, L = 3,000 1.27, W = 16 1.09.  With a cap that ends most searches: two 8,192, W = 4, L = 1,200 0.98
+//           (2,048 1.40, 4,096 1.18), W = 8, L = 1,000 1.01 (2,048 1.18), but W = 16, L = 1,000 0.91 (4,096 0.92; 2,048 0.97;
+//           1,024 1.18, where all are resident; own parameters 1.07); nw = 5, W = 16, L = 900 1.05 (4,096 0.95)
+//   nw = 3  two 1,024, W = 4, L = 2,048 1.52, L = 1,300 1.56, W = 8, L = 1,500 1.16, W = 16 1.02; 2,048, W = 4 1.14, W = 8 0.96, W = 16
+//           0.86; 4,096, W = 1 1.19, W = 2 1.16, W = 4 0.95; 8,192, W = 1 0.91, W = 2 0.91, W = 4 0.84, W = 16 0.82 (L = 64 with
+//           k = 2,000 0.94); one 1,024, W = 4, L = 4,096 1.70; 2,048, W = 4 1.13, W = 8 0.99, W = 16 0.83; 4,096, W = 2 1.24, W = 4 1.04,
+//           W = 8 0.97; 8,192, W = 2 1.10, W = 4 1.02, W = 16 0.83; 16,384, W = 1 0.95.  Capped: 1,024, W = 4, L = 2,000 1.07,
+//           W = 8, L = 1,500 0.83; 2,048, W = 4 0.98, W = 16 0.71; 4,096, W = 4 0.79; 8,192 0.75; one 2,048, W = 8 0.96; 8,192, W = 16 0.82
+//   nw = 2  two 600 and 768, W = 4, L = 3,000 0.87 and 0.89 (W = 2 0.88, W = 8 0.95); 1,024, W = 4 1.19, W = 8 1.00; 2,048, W = 1 1.13,
+//           W = 2 0.99, W = 4 0.81, W = 16 0.60; 8,192, W = 8 0.63; one 768, W = 4, L = 6,000 1.55, W = 8 1.24; 1,024, W = 2 1.68, W = 4
+//           1.26, W = 8 1.01; 2,048, W = 2 1.06, W = 4 0.84; 8,192, W = 8 0.72.  Capped: two 768 0.68; 1,024, W = 8 0.89; 2,048 0.53 to 0.64
+//   nw = 1  two 300 and 512, W = 4, L = 5,000 0.72; 2,048, W = 8 0.37; 8,192 0.34; one 300, W = 4, L = 9,000 1.00, W = 2 1.34; 512,
+//           W = 1 1.78, W = 4 1.04; 768 0.75
+// Queries with parameters of their own and no cap (the batch path runs all their rounds at the pace of the longest): nw = 3 two
+// 4,096 and 8,192, W = 4, L = 2,000 1.74 and 1.43, one 8,192, W = 8, L = 4,000 1.61; nw = 2 two 768, W = 4, L = 3,000 1.06, 1,024, W = 8
+// 1.35, 2,048, W = 4 1.48, W = 8 and 16, L = 2,000 1.43, 4,096, W = 8 1.18, 8,192 1.01, W = 16 0.95; nw = 1 512 0.95, 1,024, W = 8, L = 5,000 1.02,
+// 2,048, W = 4 0.74.  A cap far beyond the list (the batch path launches all its rounds): nw = 3 two 1,024, W = 16, L = 1,500 1.30,
+// 2,048, W = 4 1.44 to 1.70, 8,192, W = 4 1.00; nw = 2 1,024, W = 8, L = 2,000 1.82, 2,048, W = 4, L = 3,000 1.04, 4,096, W = 16 0.70, 8,192,
+// W = 8 0.69.
+static bool few_waves_ahead(const SearchArgs &a, int nw, int wide, bool two) {
+    const Plan &p = a.plan;
+    const bool own = a.W_q || a.L_q || a.cap_q, capped = p.max_iters_max > 0;
+    const bool far_cap = capped && (int64_t)p.max_iters_max * p.W_max >= 2 * (int64_t)p.C, near_cap = capped && !far_cap;
+    const int64_t work = (int64_t)p.Q * wide;  // candidates of a round of all queries
+    if (nw >= 4) return !(nw == 4 && two && near_cap && !own && wide > 256 && p.Q > 1024);
+    if (far_cap || (own && !capped)) return nw >= 2 && work <= (capped ? 1 << 19 : 1 << 21);
+    if (nw <= 2 && (near_cap || fused_serves(a))) return false;
+    const int more = nw == 3 && !two ? 2 : 1;
+    return p.Q <= 512 * nw * nw * more && work <= (int64_t)(near_cap ? 256 : 384) * 256 * nw * more;
+}
+
 // Which searches run here, with how many waves a CU.  Both sides measured on 2 10^6 items with 32 neighbours, without ->
 // here, ms; beyond 1,024 queries without is the batch path, up to there a workgroup per query (search_fused.hip):
 //   64 -> 256 -> 128: 300 queries, W = 4, L = 64 0.94 -> 0.88; 512, W = 4 1.09 -> 0.90, W = 8, L = 512 3.53 -> 3.64; 1,024,
-//     W = 1, L = 64 2.1 -> 1.7, W = 16, L = 1,024 6.6 -> 5.8, W = 32 6.4 -> 7.6; 2,048, W = 4, L = 64 2.4 -> 1.4, L = 1,024
-//     15.1 -> 11.2, W = 16, L = 256 5.5 -> 4.5, W = 32, L = 1,024 10.4 -> 11.2; 4,096, W = 8, L = 600 13.6 -> 11.0; 8,192,
-//     W = 4, L = 512 22.9 -> 17.0, W = 16, L = 1,200 38.4 -> 38.3;
+//     W = 1, L = 64 2.1 -> 1.7, W = 16, L = 1,024 6.6 -> 5.8, W = 32 6.4 -> 7.6; 2,048, W = 4, L = 64 2.4 -> 1.4, W = 16, L = 256
+//     5.5 -> 4.5, W = 32, L = 1,024 10.4 -> 11.2; 4,096, W = 8, L = 600 13.6 -> 11.0; 8,192, W = 4, L = 512 22.9 -> 17.0;
 //   64 -> 256: 512 queries, W = 8, L = 512 2.6 -> 2.8; 1,024, W = 4, L = 64 1.24 -> 0.85; 2,048, W = 4, L = 512 8.3 -> 4.3,
 //     W = 8, L = 2,000 17.7 -> 12.4, W = 32 13.9 -> 12.6; 8,192, W = 32, L = 2,000 46.6 -> 42.0; 16,384, W = 4, L = 64
-//     7.6 -> 4.5.
+//     7.6 -> 4.5;
+//   1,025 to 2,000 queries: W = 4, L = 64 1.9 -> 1.1, W = 1, L = 256 12.1 -> 5.3, W = 16, L = 1,200 11.5 -> 9.7, W = 32, L = 1,000 8.3
+//     either way; one hidden layer, W = 4, L = 300 5.5 -> 2.7.
 // So: a wave per query from 257 queries on (below, a workgroup per query has a CU to itself), unless a round's pairs are
-// many for the number of queries (a wave scores them alone) or long lists leave room for four waves only and rounds are
-// wide.  1,025 to 2,000 queries: W = 4, L = 64 1.9 -> 1.1, W = 1, L = 256 12.1 -> 5.3, W = 16, L = 1,200 11.5 -> 9.7, W = 32,
-// L = 1,000 8.3 either way; one hidden layer, W = 4, L = 300 5.5 -> 2.7.
+// many for the number of queries (a wave scores them alone), or long lists leave room for four waves only and rounds are
+// wide, or for fewer than the batch wants (few_waves_ahead).
 static bool wave_plan(const SearchArgs &a, int *nw, int *piece, WaveArgs *A, size_t *smem) {
     const Plan &p = a.plan;
     const ann_mlp *m = a.m;
@@ -524,6 +561,7 @@ static bool wave_plan(const SearchArgs &a, int *nw, int *piece, WaveArgs *A, siz
     *nw = fit < most ? fit : most;
     if (*nw > want) *nw = want;
     if (*nw < 1 || (*nw <= 4 && wide > 512)) return false;
+    if (*nw < want && *nw < most && !few_waves_ahead(a, *nw, wide, two)) return false;
     A->wave_off = (int32_t)weights;
     A->wave_bytes = (int32_t)bytes;
     A->at_keys = (int32_t)at_keys;

@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 TWO, ONE = (64, 64, (256, 128), 3), (64, 64, (256,), 4)
 
 
-def _both(call, ws):
+def _both(call, ws, waves=True):
     runs = []
     for staged in (True, False):
         ann.ann_profile_enable(staged)
@@ -22,7 +22,7 @@ def _both(call, ws):
             ann.ann_profile_enable(False)
         st = ann.ann_search_stats(ws)
         runs.append((ids.clone(), sc.clone(), (st.pairs_scored, st.nodes_expanded, st.max_query_iters, st.visited_overflow, st.queries)))
-        assert int(ws[256:384].view(torch.int64)[8]) == (0 if staged else st.queries)
+        assert int(ws[256:384].view(torch.int64)[8]) == (st.queries if waves and not staged else 0)
     assert torch.equal(runs[0][0], runs[1][0])
     assert torch.equal(runs[0][1].view(torch.int32), runs[1][1].view(torch.int32))  # NaN too
     assert runs[0][2] == runs[1][2]
@@ -39,7 +39,8 @@ def test_search_by_waves_is_the_staged_search(dtype, shape, visited, monkeypatch
     monkeypatch.setenv("GMPGR_VISITED_SET", "hash" if visited == "hash" else "bitmap")
     for Q, R, E, W, L, k, cap in [(2048, 32, 4, 4, 64, 100, 0), (2049, 16, 1, 1, 1, 5, 0), (2100, 1, 2, 3, 33, 7, 0),
                                   (4097, 24, 3, 5, 100, 20, 0), (2050, 32, 300, 9, 200, 11, 0), (2048, 32, 2, 12, 250, 40, 9),
-                                  (9000, 17, 4, 2, 40, 10, 7), (2048, 16, 4, 4, 900, 30, 0), (2051, 16, 1024, 8, 2500, 30, 0),
+                                  (9000, 17, 4, 2, 40, 10, 7), (2048, 16, 4, 4, 900, 30, 0), (2040, 16, 1024, 4, 2500, 30, 0),
+                                  (300, 16, 1024, 1, 6690, 30, 0),
                                   (1025, 32, 4, 4, 64, 100, 0), (1300, 16, 4, 16, 500, 30, 6), (300, 32, 4, 4, 64, 100, 0), (777, 8, 5, 7, 131, 9, 0), (1024, 32, 4, 16, 300, 50, 5)]:
         g, m, users, entries = _handles(dtype, *shape, 3001, R, Q, E)
         if visited == "rank":
@@ -47,6 +48,31 @@ def test_search_by_waves_is_the_staged_search(dtype, shape, visited, monkeypatch
             ann.ann_graph_set_locality(g, rank)
         ws = torch.empty(ann.ann_search_workspace_bytes(g, m, Q, E, W, L, k, cap), dtype=torch.uint8, device="cuda")
         _both(lambda: ann.ann_search(g, m, users, entries, W, L, k, cap, workspace=ws), ws)
+
+
+@pytest.mark.parametrize("shape,Q,W,L,cap,waves", [
+    (TWO, 8192, 4, 1024, 0, True), (TWO, 8192, 4, 1500, 0, False), (TWO, 2048, 4, 2000, 0, True), (TWO, 2048, 8, 2000, 0, False),
+    (TWO, 4096, 2, 1500, 0, True), (TWO, 4096, 4, 1500, 0, False), (TWO, 1024, 4, 3000, 0, True), (TWO, 1024, 8, 3000, 0, False),
+    (TWO, 768, 4, 3000, 0, False), (TWO, 8192, 8, 5000, 0, False), (TWO, 4096, 16, 1000, 0, True), (TWO, 4096, 16, 1000, 60, False),
+    (TWO, 1024, 8, 2000, 1000, True), (TWO, 1024, 8, 2000, 250, False), (ONE, 1024, 4, 6000, 0, True), (ONE, 2048, 4, 6000, 0, False),
+    (ONE, 768, 8, 6000, 0, True), (ONE, 8192, 2, 4000, 0, True), (ONE, 8192, 16, 4096, 0, False), (ONE, 512, 4, 9000, 0, True),
+    (ONE, 768, 4, 9000, 0, False)])
+def test_long_lists_that_leave_room_for_few_waves(shape, Q, W, L, cap, waves):
+    """Both sides of the lines from which on a wave per query falls behind: a batch of many queries whose lists leave room for
+    one to four waves a CU goes to the other paths (8,192 queries, W = 8, L = 5,000 took three times as long by waves)."""
+    g, m, users, entries = _handles("bf16", *shape, 3001, 32, Q, 4)
+    ws = torch.empty(ann.ann_search_workspace_bytes(g, m, Q, 4, W, L, 100, cap), dtype=torch.uint8, device="cuda")
+    _both(lambda: ann.ann_search(g, m, users, entries, W, L, 100, cap, workspace=ws), ws, waves)
+
+
+@pytest.mark.parametrize("waves,Q,W,L", [(True, 4096, 8, 2000), (False, 8192, 16, 2000), (False, 600, 4, 5000)])
+def test_long_lists_of_their_own(waves, Q, W, L):
+    """Without a cap and with lists of every length the batch path runs all rounds at the pace of the longest query."""
+    g, m, users, entries = _handles("bf16", *TWO, 3001, 32, Q, 4)
+    gen = torch.Generator().manual_seed(Q)
+    own = [torch.randint(1, hi + 1, (Q,), generator=gen, dtype=torch.int32).cuda() for hi in (W, L)] + [torch.zeros(Q, dtype=torch.int32).cuda()]
+    ws = torch.empty(ann.ann_search_workspace_bytes(g, m, Q, 4, W, L, 100, 0), dtype=torch.uint8, device="cuda")
+    _both(lambda: ann.ann_search_ragged(g, m, users, entries, *own, W, L, 100, 0, workspace=ws), ws, waves)
 
 
 @pytest.mark.parametrize("cap", [0, 24])
