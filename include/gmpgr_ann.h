@@ -409,9 +409,11 @@ int ann_score_pairs_noalloc(const ann_graph *g, const ann_mlp *m, const void *qu
  * Searches that run until every query has converged (ann_search / ann_search_layers with max_iters = 0,
  * ann_search_stream) follow the progress their kernels report to pinned host memory: every round of the batch, and
  * where the search of a small batch, or that of the last queries of a large one, is a single launch, after the first
- * and every eighth round of a query (rounds take microseconds to a few hundred of them).  This sets,
+ * and every eighth round of a query (rounds take microseconds to a few hundred of them).  Where one launch takes the
+ * queries of a large batch one after the other (metrics of 64-wide items), each of them reports at its end or after its next
+ * eighth round once 4 ms have gone by since the last report from the same place (4 to 8 ms since the start).  This sets,
  * for the whole process, how long such a call waits for the NEXT report while `stream` stays busy before it gives
- * up with ANN_EDEVICE (default 600 s, 0 = wait for ever).  The limit counts from the last report seen, so work
+ * up with ANN_EDEVICE (default 600 s, 0 = wait for ever; a wait is looked at after 20 ms at the earliest).  The limit counts from the last report seen, so work
  * the caller enqueued on the stream ahead of the search must finish within it too.  A call that gives up has
  * enqueued only complete rounds or the whole search; its kernels end by themselves, nothing is left waiting on the device, and the
  * results are undefined.  While it waits the calling thread yields the core between looks at the word.

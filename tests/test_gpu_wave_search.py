@@ -2,6 +2,8 @@
 beyond what a workgroup per query is best at) against the same searches run stage by stage: id for id, relevance for
 relevance, counter for counter.  Enabling the stage timing selects the separate kernels.  The ninth word of the workspace's
 counters (at byte 256) says how many queries such a launch was given."""
+import time
+
 import pytest
 import torch
 
@@ -98,20 +100,74 @@ def test_items_that_are_not_finite(shape):
     _both(lambda: ann.ann_search(g, m, users, entries, 4, 64, 200, 0, workspace=ws), ws)
 
 
-def test_a_batch_by_waves_reports_its_progress():
-    """A batch that takes longer than the 20 ms after which the waiting thread asks, under a limit far below that."""
-    Q = 16384
-    g, m, users, entries = _handles("bf16", *TWO, 200_000, 32, Q, 4)
-    ws = torch.empty(ann.ann_search_workspace_bytes(g, m, Q, 4, 4, 512, 10, 0), dtype=torch.uint8, device="cuda")
-    want = ann.ann_search(g, m, users, entries, 4, 512, 10, 0, workspace=ws)
+def _under_a_limit(call, ws, Q, at_least):
+    """The call by waves, again under a limit far below the 20 ms after which the waiting thread asks; it has to take longer than
+    that for the reports to be needed."""
+    call()
+    torch.cuda.synchronize()
+    start = time.perf_counter()
+    ids, sc = [t.clone() for t in call()]
+    torch.cuda.synchronize()
+    assert time.perf_counter() - start > at_least
     assert int(ws[256:384].view(torch.int64)[8]) == Q
-    ann.ann_set_progress_timeout(2e-3)
+    ann.ann_set_progress_timeout(1e-3)
     try:
-        got = ann.ann_search(g, m, users, entries, 4, 512, 10, 0, workspace=ws)
+        got = call()
     finally:
         ann.ann_set_progress_timeout(600.0)
         torch.cuda.synchronize()
-    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+    assert torch.equal(got[0], ids) and torch.equal(got[1], sc)
+
+
+def test_a_batch_by_waves_reports_its_progress():
+    Q = 16384
+    g, m, users, entries = _handles("bf16", *TWO, 200_000, 32, Q, 4)
+    ws = torch.empty(ann.ann_search_workspace_bytes(g, m, Q, 4, 4, 512, 10, 0), dtype=torch.uint8, device="cuda")
+    _under_a_limit(lambda: ann.ann_search(g, m, users, entries, 4, 512, 10, 0, workspace=ws), ws, Q, 0.025)
+
+
+def test_many_short_searches_report_their_progress():
+    """Every query ends within seven rounds."""
+    Q = 2_500_000
+    g, m, users, entries = _handles("bf16", *TWO, 16, 16, Q, 4)
+    ws = torch.empty(ann.ann_search_workspace_bytes(g, m, Q, 4, 4, 16, 8, 0), dtype=torch.uint8, device="cuda")
+    _under_a_limit(lambda: ann.ann_search(g, m, users, entries, 4, 16, 8, 0, workspace=ws), ws, Q, 0.03)
+    assert ann.ann_search_stats(ws).max_query_iters < 7
+
+
+def _rising_metric(hidden):
+    """Relevance rises with the items' first two coordinates, 2 ** -4 and 2 ** -10 of them (small whole numbers: exact)."""
+    d = 64
+    dims = [2 * d, *hidden, 1]
+    Ws = [torch.zeros(o, n) for n, o in zip(dims, dims[1:])]
+    Ws[0][0, d], Ws[0][1, d + 1] = 1, 1
+    for w in Ws[1:-1]:
+        w[0, 0], w[1, 1] = 1, 1
+    Ws[-1][0, 0], Ws[-1][0, 1] = 2.0 ** -4, 2.0 ** -10
+    bs = [torch.zeros(o) for o in dims[1:-1]] + [torch.tensor([-4.0])]
+    return ann.ann_mlp_load([w.bfloat16() for w in Ws], bs, torch.ones(1), d, ann.ANN_BF16)
+
+
+def test_a_long_search_of_wide_rounds_reports_its_progress(monkeypatch):
+    """One query that runs 500 rounds of 1,152 new items while the others end at once; rounds that wide are not handed over, so
+    its wave scores them alone, some 40 ms in 256 rounds.  18 nodes a layer, each joined to one of the next and to 63 of its own."""
+    monkeypatch.setenv("GMPGR_VISITED_SET", "bitmap")
+    R, W, layers, Q, q = 64, 18, 500, 1100, 5
+    N = layers * W * R
+    i = torch.arange(N, device="cuda").view(layers, W, R)
+    adj = torch.full((layers, W, R, R), -1, dtype=torch.int32, device="cuda")
+    adj[:-1, :, 0, 0] = i[1:, :, 0]
+    adj[:, :, 0, 1:] = i[:, :, 1:]
+    emb = torch.zeros(layers, W, R, 64, device="cuda")
+    rank = torch.arange(1, layers + 1, device="cuda")[:, None]
+    emb[:, :, 0, 0], emb[:, :, 0, 1] = (rank // 64).float(), (rank % 64).float()
+    g, m = ann.ann_graph_load(adj.view(N, R), emb.view(N, 64).bfloat16()), _rising_metric((256, 128))
+    entries = torch.full((Q, W), -1, dtype=torch.int32, device="cuda")
+    entries[q] = i[0, :, 0]
+    users = torch.zeros(Q, 64, device="cuda").bfloat16()
+    ws = torch.empty(ann.ann_search_workspace_bytes(g, m, Q, W, W, W, W, 0), dtype=torch.uint8, device="cuda")
+    _under_a_limit(lambda: ann.ann_search(g, m, users, entries, W, W, W, 0, workspace=ws), ws, Q, 0.04)
+    assert ann.ann_search_stats(ws).max_query_iters == layers
 
 
 @pytest.mark.parametrize("far", [100, 900])
@@ -127,15 +183,8 @@ def test_visited_table_that_fills_up(hidden, far, monkeypatch):
     emb[:, 0], emb[:, 1] = (i // 64).float(), (i % 64).float()
     adj = i[:, None] + 1 + torch.arange(R, device="cuda")
     adj = torch.where(adj < N, adj, -1).int()
-    dims = [2 * d, *hidden, 1]
-    Ws = [torch.zeros(o, n) for n, o in zip(dims, dims[1:])]
-    Ws[0][0, d], Ws[0][1, d + 1] = 1, 1
-    for w in Ws[1:-1]:
-        w[0, 0], w[1, 1] = 1, 1
-    Ws[-1][0, 0], Ws[-1][0, 1] = 2.0 ** -4, 2.0 ** -10
-    bs = [torch.zeros(o) for o in dims[1:-1]] + [torch.tensor([-4.0])]
     g = ann.ann_graph_load(adj, emb.bfloat16())
-    m = ann.ann_mlp_load([w.bfloat16() for w in Ws], bs, torch.ones(1), d, ann.ANN_BF16)
+    m = _rising_metric(hidden)
     start = torch.full((Q,), N - 30, dtype=torch.int32)
     start[torch.arange(far) * Q // far] = torch.linspace(0, N - 1100, far).int()
     entries, users = start[:, None].contiguous().cuda(), torch.zeros(Q, d, device="cuda").bfloat16()
