@@ -795,10 +795,12 @@ int launch_round(const SearchArgs &a) {
     // Workgroups of 128 threads when a round has at most 128 candidates per query and the batch is far larger
     // than what a chip holds at once (2,048 workgroups of 256): twice as many queries are then resident, and
     // the candidates still go through the visited filter in one pass.  (C4: 33 -> 28 ms per step; with few
-    // queries the shorter path of the larger workgroup wins: C2 3.9 against 4.2 ms.)
+    // queries the shorter path of the larger workgroup wins: C2 3.9 against 4.2 ms.)  Walkers merge every survivor: with lists
+    // of up to 768 entries (8,192 queries, 64 hops, k = 100, 300, 500, 700 and 1,000: 128 threads 9.9, 19.3, 19.7, 20.3 and 21.6 ms,
+    // the first one with 32 hops; 256 threads 10.3, 19.7, 19.9, 20.3 and 20.8).
     // Workgroups of 512 threads when a round brings more than 512 candidates per query: the sort and the merge have half
     // of the work per thread.
-    const bool big = p.slots > ROUND_BIG_FROM, half = p.slots <= 128 && p.Q >= 8192 && !a.walkers;
+    const bool big = p.slots > ROUND_BIG_FROM, half = p.slots <= 128 && p.Q >= 8192 && (!a.walkers || p.C <= 768);
     const int which = half ? 1 : big ? 2 : 0;
     const int threads = half ? 128 : big ? ROUND_BIG_BLOCK : BLOCK;
     const bool bm = p.bitmap_words > 0;
@@ -808,14 +810,17 @@ int launch_round(const SearchArgs &a) {
     const size_t smem = resident ? round_smem(a, filter, tile_keys + p.C) : round_smem(a, filter);
     using Fn = decltype(&round_kernel<BLOCK, false, false, FILTER_ATOMIC>);
     Fn fn;
+#define ROUND_SHARED(BLK, RESIDENT)                                                \
+    (filter == FILTER_ORDERED ? round_kernel<BLK, true, RESIDENT, FILTER_ORDERED>  \
+                              : (bm ? round_kernel<BLK, true, RESIDENT, FILTER_ATOMIC> : round_kernel<BLK, false, RESIDENT, FILTER_ATOMIC>))
 #define ROUND_FN(BLK, RESIDENT)                                                                                                \
     (filter == FILTER_WALKERS ? (bm ? round_kernel<BLK, true, RESIDENT, FILTER_WALKERS> : round_kernel<BLK, false, RESIDENT, FILTER_WALKERS>) \
-     : filter == FILTER_ORDERED ? round_kernel<BLK, true, RESIDENT, FILTER_ORDERED>                                             \
-                                : (bm ? round_kernel<BLK, true, RESIDENT, FILTER_ATOMIC> : round_kernel<BLK, false, RESIDENT, FILTER_ATOMIC>))
+                              : ROUND_SHARED(BLK, RESIDENT))
     if (big) fn = ROUND_FN(ROUND_BIG_BLOCK, false);
-    else if (half) fn = resident ? ROUND_FN(128, true) : ROUND_FN(128, false);
+    else if (half) fn = resident ? ROUND_FN(128, true) : ROUND_SHARED(128, false);  // walkers: up to 768 entries, resident
     else fn = resident ? ROUND_FN(BLOCK, true) : ROUND_FN(BLOCK, false);
 #undef ROUND_FN
+#undef ROUND_SHARED
     if (smem > 48 * 1024) {
         static std::atomic<uint32_t> raised[36];
         if (int rc = raise_lds_limit((const void *)fn, 128 * 1024, a.m->device,

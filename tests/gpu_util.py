@@ -42,10 +42,11 @@ class _KernelNode(ctypes.Structure):  # hipKernelNodeParams
                 ("grid", ctypes.c_uint * 3), ("params", ctypes.c_void_p), ("lds", ctypes.c_uint)]
 
 
-def captured_launches(call):
-    """The kernel launches that `call` enqueues, recorded into a HIP graph: (workgroups, threads of one) each."""
+def captured_kernels(call):
+    """The kernel launches that `call` enqueues, recorded into a HIP graph: (mangled name, workgroups, threads of one) each."""
     with open("/proc/self/maps") as f:  # the runtime that is loaded already
         hip = ctypes.CDLL(next(line.split()[-1] for line in f if "libamdhip64.so" in line))
+    hip.hipKernelNameRefByPtr.restype = ctypes.c_char_p
     torch.cuda.synchronize()
     graph = torch.cuda.CUDAGraph(keep_graph=True)
     with torch.cuda.graph(graph):
@@ -58,5 +59,11 @@ def captured_launches(call):
         assert hip.hipGraphNodeGetType(ctypes.c_void_p(node), ctypes.byref(kind)) == 0
         assert kind.value == 0, "a node that is not a kernel"
         assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(p)) == 0
-        out.append((p.grid[0], p.block[0]))
+        name = hip.hipKernelNameRefByPtr(ctypes.c_void_p(p.func), None)
+        out.append((name.decode() if name else "", p.grid[0], p.block[0]))
     return out
+
+
+def captured_launches(call):
+    """(workgroups, threads of one) of each of them."""
+    return [launch[1:] for launch in captured_kernels(call)]
