@@ -699,15 +699,10 @@ static size_t filter_smem(const ann_graph *g, const Plan &p, int n) {
     return (size_t)((n + 3) & ~3) * 4 * (ranked(g, p) ? 2 : 1) + (size_t)dd_n * 16;
 }
 
-// Which visited filter a round uses.  Atomics, one a candidate, with a hash table (16,384 queries 8.3 -> 8.1 ms, 6,001 in slots
-// 30.0 -> 29.1).  On a bitmap they are ahead where every thread has two candidates, which then go through in one pass (2,048
-// 8-bit queries of 512 candidates 29.5 -> 28.2 ms); with one a thread, and with 2,048 candidates in pieces of 512, the
-// ordered filter's loads and plain stores are (4,096 queries, 256 candidates 47.7 against 48.5 ms; 2,048 254 against 255).
-// The walkers' rule needs the first of equal candidates.
-static int filter_of(const SearchArgs &a, int threads) {
-    const Plan &p = a.plan;
-    if (a.walkers) return FILTER_WALKERS;
-    return p.bitmap_words > 0 && (p.slots <= threads || p.slots > 2 * threads) ? FILTER_ORDERED : FILTER_ATOMIC;
+// Workgroups of the round kernel on a CU: its LDS, eight waves a SIMD.
+static int groups_of(size_t smem, int threads) {
+    const int by_lds = (int)(160 * 1024 / smem), by_waves = 2048 / threads;
+    return by_lds < by_waves ? by_lds : by_waves;
 }
 
 // list_keys: list entries held in LDS (0: one tile)
@@ -716,6 +711,24 @@ static size_t round_smem(const SearchArgs &a, int filter, int list_keys = 0) {
     const size_t lists = (size_t)(new_cap_of(p) + ((p.W_max + 1) & ~1) + (list_keys > 0 ? list_keys : tile_keys_of(p))) * 8;
     const size_t filt = filter != FILTER_ATOMIC ? filter_smem(a.g, p, filter_chunk(a.g, p)) : 0;
     return (size_t)((p.W_max + 3) & ~3) * 4 + 24 * 4 + (lists > filt ? lists : filt);
+}
+
+// Which visited filter a round uses.  The walkers' rule needs the first of equal candidates.  Atomics, one a candidate, with a
+// hash table (time in the round kernel: 2,048 queries of 2 10^6 items, 64 to 2,048 candidates 3 to 17 % less, 16,384 queries
+// 8.3 -> 8.1 ms a call, 6,001 in slots 30.0 -> 29.1).  On a bitmap the ordered filter's loads and plain stores against them, time of
+// the ordered one / of the atomics in the round kernel, bitmaps of 0.5, 2, 4 and 10 million items, by id (by rank within 0.02
+// of it), lists of 1,024: 2,048 queries, 64 candidates 1.16, -, 1.12, 1.11; 128 candidates 1.10, 1.04, 1.05, 1.05; 160 1.01, -, 1.00, 1.00;
+// 192 0.99, 0.98, 0.99, 0.99; 256 0.99, 0.97, 0.99, 1.00; 384 0.97, 1.00, 1.01, 1.02; 512 0.95, 0.97, 0.99, 1.00; 544 -, 0.96, -, -;
+// 768 0.92, 0.93, 0.96, 0.98; 1,024 0.88, 0.91, 0.95, 0.97; 1,056 0.92 and 2,048 0.82 (2 million items).  8,192 queries with 128 threads, 32
+// candidates 1.06, 64 1.03, 96 0.98, 128 0.99.  So: atomics for up to half a candidate a thread; beyond that the ordered filter, unless
+// its tables in LDS cost a workgroup on the CU (512 candidates by rank, lists of 2,048, 4 and 10 million items: 2,048 queries,
+// which are then all resident, 1.12 and 1.13, 4,096 1.04, 8,192 0.99, 1,024 1.00).
+static int filter_of(const SearchArgs &a, int threads, int list_keys) {
+    const Plan &p = a.plan;
+    if (a.walkers) return FILTER_WALKERS;
+    if (p.bitmap_words == 0 || 2 * p.slots <= threads) return FILTER_ATOMIC;
+    return groups_of(round_smem(a, FILTER_ORDERED, list_keys), threads) < groups_of(round_smem(a, FILTER_ATOMIC, list_keys), threads)
+               ? FILTER_ATOMIC : FILTER_ORDERED;
 }
 
 static size_t seed_smem(const SearchArgs &a) {
@@ -806,8 +819,8 @@ int launch_round(const SearchArgs &a) {
     const bool bm = p.bitmap_words > 0;
     const bool resident = !big && p.C <= tile_keys_of(p);
     const int tile_keys = resident ? ((p.C + 1) & ~1) : tile_keys_of(p);  // resident: the list itself, twice
-    const int filter = filter_of(a, threads);
-    const size_t smem = resident ? round_smem(a, filter, tile_keys + p.C) : round_smem(a, filter);
+    const int list_keys = resident ? tile_keys + p.C : 0, filter = filter_of(a, threads, list_keys);
+    const size_t smem = round_smem(a, filter, list_keys);
     using Fn = decltype(&round_kernel<BLOCK, false, false, FILTER_ATOMIC>);
     Fn fn;
 #define ROUND_SHARED(BLK, RESIDENT)                                                \

@@ -10,12 +10,12 @@ from gpu_util import captured_kernels
 from workloads import random_mlp
 
 pytestmark = pytest.mark.gpu
-WALKERS = 2
+ATOMIC, ORDERED, WALKERS = 0, 1, 2
 
 
 def _handles(N, R, Q, E, f8=False):
     gen = torch.Generator().manual_seed(N + R)
-    dims = [128, 512, 256, 2] if f8 else [64, 32, 2]
+    dims = [256, 512, 256, 2] if f8 else [64, 32, 2]
     d = dims[0] // 2
     Ws, bs = random_mlp(dims, 5, "bf16", bias_scale=0.2)
     emb = torch.randn(N, d, generator=gen).bfloat16().cuda()
@@ -49,3 +49,27 @@ def test_walkers_of_a_large_batch(Q, R, E, k, threads, visited, monkeypatch):
     assert _round_kernel(call) == (threads, int(visited == "bitmap"), 1, WALKERS)
     few = ann.ann_search_walkers(g, m, users[:64].contiguous(), entries[:64].contiguous(), 6, k)
     assert torch.equal(ids[:64], few[0]) and torch.equal(sc[:64], few[1])
+
+
+@pytest.mark.parametrize("Q,R,W,L,ranked,threads,which", [
+    (300, 32, 4, 100, False, 256, ATOMIC), (300, 43, 3, 100, False, 256, ORDERED), (300, 32, 9, 100, True, 256, ORDERED),
+    (300, 32, 16, 1024, False, 256, ORDERED), (300, 32, 16, 1024, True, 256, ORDERED), (300, 32, 16, 1500, True, 256, ATOMIC),
+    (300, 32, 16, 1500, False, 256, ORDERED), (300, 32, 17, 300, True, 512, ORDERED), (300, 32, 32, 1500, False, 512, ORDERED),
+    (300, 32, 33, 300, True, 512, ORDERED), (8192, 32, 2, 60, False, 128, ATOMIC), (8192, 13, 5, 60, True, 128, ORDERED)])
+def test_visited_filter_on_a_bitmap(Q, R, W, L, ranked, threads, which, monkeypatch):
+    """On either side of the lines; the searches with the hash table, which always takes the atomics, are the reference."""
+    N, E, k, cap = 4001, 5, 50, 12
+    g, m, users, entries = _handles(N, R, Q, E, f8=True)
+    out = dict(out_ids=torch.empty(Q, k, dtype=torch.int32, device="cuda"), out_scores=torch.empty(Q, k, device="cuda"))
+    found = []
+    for form in ("hash", "bitmap"):
+        monkeypatch.setenv("GMPGR_VISITED_SET", form)
+        if ranked and form == "bitmap":
+            ann.ann_graph_set_locality(g, torch.randperm(N, generator=torch.Generator().manual_seed(1)).to(torch.int32).cuda())
+        ws = torch.empty(ann.ann_search_workspace_bytes(g, m, Q, E, W, L, k, cap), dtype=torch.uint8, device="cuda")
+        call = lambda: ann.ann_search(g, m, users, entries, W, L, k, cap, workspace=ws, **out)
+        call()
+        found.append((out["out_ids"].clone(), out["out_scores"].clone()))
+        t, bitmap, _, picked = _round_kernel(call)
+        assert (t, bitmap, picked) == (threads, int(form == "bitmap"), which if form == "bitmap" else ATOMIC)
+    assert torch.equal(found[0][0], found[1][0]) and torch.equal(found[0][1], found[1][1])
