@@ -42,8 +42,15 @@ class _KernelNode(ctypes.Structure):  # hipKernelNodeParams
                 ("grid", ctypes.c_uint * 3), ("params", ctypes.c_void_p), ("lds", ctypes.c_uint)]
 
 
+class _FuncAttributes(ctypes.Structure):  # hipFuncAttributes
+    _fields_ = [("version", ctypes.c_int), ("ca", ctypes.c_int), ("const", ctypes.c_size_t), ("scratch", ctypes.c_size_t),
+                ("dynamic", ctypes.c_int), ("threads", ctypes.c_int), ("registers", ctypes.c_int), ("carveout", ctypes.c_int),
+                ("ptx", ctypes.c_int), ("lds", ctypes.c_size_t)]
+
+
 def captured_kernels(call):
-    """The kernel launches that `call` enqueues, recorded into a HIP graph: (mangled name, workgroups, threads of one) each."""
+    """The kernel launches that `call` enqueues, recorded into a HIP graph: (mangled name, workgroups, threads of one,
+    registers and scratch bytes of a lane) each."""
     with open("/proc/self/maps") as f:  # the runtime that is loaded already
         hip = ctypes.CDLL(next(line.split()[-1] for line in f if "libamdhip64.so" in line))
     hip.hipKernelNameRefByPtr.restype = ctypes.c_char_p
@@ -60,10 +67,12 @@ def captured_kernels(call):
         assert kind.value == 0, "a node that is not a kernel"
         assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(p)) == 0
         name = hip.hipKernelNameRefByPtr(ctypes.c_void_p(p.func), None)
-        out.append((name.decode() if name else "", p.grid[0], p.block[0]))
+        attr = _FuncAttributes()
+        assert hip.hipFuncGetAttributes(ctypes.byref(attr), ctypes.c_void_p(p.func)) == 0
+        out.append((name.decode() if name else "", p.grid[0], p.block[0], attr.registers, attr.scratch))
     return out
 
 
 def captured_launches(call):
     """(workgroups, threads of one) of each of them."""
-    return [launch[1:] for launch in captured_kernels(call)]
+    return [launch[1:3] for launch in captured_kernels(call)]

@@ -29,10 +29,16 @@ def _handles(N, R, Q, E, f8=False):
 
 def _round_kernel(call):
     """(threads, bitmap, list resident, filter)"""
-    found = {tuple(int(x) for x in t.groups()) for name, _, _ in captured_kernels(call)
+    found = {tuple(int(x) for x in t.groups()) for name, *_ in captured_kernels(call)
              if (t := re.search(r"round_kernelILi(\d+)ELb([01])ELb([01])ELi(\d)E", name))}
     assert len(found) == 1, found
     return found.pop()
+
+
+def _seeds_by_eight_waves(call):
+    """The seeding kernel leaves room for eight waves a SIMD (64 registers a lane) and keeps nothing in scratch memory."""
+    (registers, scratch), = {k[3:] for k in captured_kernels(call) if "init_kernel" in k[0]}
+    assert 0 < registers <= 64 and scratch == 0
 
 
 @pytest.mark.parametrize("visited", ["hash", "bitmap"])
@@ -47,6 +53,7 @@ def test_walkers_of_a_large_batch(Q, R, E, k, threads, visited, monkeypatch):
     call()
     ids, sc = out["out_ids"].clone(), out["out_scores"].clone()
     assert _round_kernel(call) == (threads, int(visited == "bitmap"), 1, WALKERS)
+    _seeds_by_eight_waves(call)
     few = ann.ann_search_walkers(g, m, users[:64].contiguous(), entries[:64].contiguous(), 6, k)
     assert torch.equal(ids[:64], few[0]) and torch.equal(sc[:64], few[1])
 
@@ -70,6 +77,7 @@ def test_visited_filter_on_a_bitmap(Q, R, W, L, ranked, threads, which, monkeypa
         call = lambda: ann.ann_search(g, m, users, entries, W, L, k, cap, workspace=ws, **out)
         call()
         found.append((out["out_ids"].clone(), out["out_scores"].clone()))
+        _seeds_by_eight_waves(call)
         t, bitmap, _, picked = _round_kernel(call)
         assert (t, bitmap, picked) == (threads, int(form == "bitmap"), which if form == "bitmap" else ATOMIC)
     assert torch.equal(found[0][0], found[1][0]) and torch.equal(found[0][1], found[1][1])
