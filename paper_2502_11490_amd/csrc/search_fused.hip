@@ -668,7 +668,7 @@ __global__ void __launch_bounds__(BLK, CB == 4 ? 2 : 4) fused_search_kernel(Fuse
     }
     if (tid == 0) {
         add_to_totals(A.stats, n_visited, n_expanded, t, overflow ? 1 : 0);
-        if (RESUME && A.Q > 1024) atomicAdd((unsigned long long *)&A.stats[7], 1ull);  // up to there all have been counted
+        if (RESUME) atomicAdd((unsigned long long *)&A.stats[7], 1ull);  // a batch that begins here has been counted
         if (A.mailbox) {
             // the last query to end reports
             __threadfence_system();

@@ -64,7 +64,8 @@ constexpr int SCAN_WAVES = SCAN_BLOCK / 64;
 // Counters and control block start at zero (a kernel, not a memset, so that a caller may
 // capture the launch sequence into a HIP graph).
 // stats[5], stats[6]: bytes of one adjacency row and of one item row, from which ann_search_stats derives the
-// algorithmic bytes of the gather stages.  stats[7]: queries that one launch ran to their end (search_fused.hip).
+// algorithmic bytes of the gather stages.  stats[7]: queries that a workgroup ran to their end (search_fused.hip), stats[8]:
+// queries that waves were given (search_wave.hip; the last ones of a batch may count in both).
 __global__ void zero_stats_kernel(int64_t *stats, Ctrl *ctrl, int Q, int keep_stats, int adj_row_bytes,
                                   int item_row_bytes, int one_launch, int by_waves) {
     if (threadIdx.x < 16 && !keep_stats)

@@ -641,7 +641,7 @@ int launch_wave(const SearchArgs &a, int32_t rounds_max) {
     A.pool = (uint64_t *)(a.ws + p.off_pool);
     A.handed = (int32_t *)(a.ws + p.off_offsets);  // [Q], unused by this path otherwise
     A.hand_at = p.max_iters_max == 0 && fused_goes_on(a, WAVE_HAND) ? WAVE_HAND : 0;
-    if (int rc = launch_zero_stats(a, p.Q <= 1024 ? p.Q : 0, p.Q); rc != ANN_OK) return rc;
+    if (int rc = launch_zero_stats(a, 0, p.Q); rc != ANN_OK) return rc;
     if (a.W_q || a.L_q || a.cap_q) {
         int32_t *order = (int32_t *)(a.ws + p.off_counts);  // [Q], unused by this path otherwise
         hipLaunchKernelGGL(wave_order_kernel, dim3(1), dim3(1024), 0, a.stream, A, order);

@@ -1,7 +1,7 @@
 """Searches that run as one launch (small batches) against the same searches run stage by stage: id for id, relevance for
 relevance, counter for counter.  Enabling the stage timing selects the separate kernels, whose parity with the oracle
-the other tests hold.  Every case also says which path it takes: the queries that one launch runs to their end
-are counted in the eighth word of the workspace's counters (at byte 256)."""
+the other tests hold.  Every case also says which path it takes: the queries that a workgroup runs to their end
+are counted in the eighth word of the workspace's counters (at byte 256), those that waves are given in the ninth."""
 import pytest
 import torch
 
@@ -34,8 +34,14 @@ def _ended_in_one_launch(ws):
     return int(ws[256:320].view(torch.int64)[7])
 
 
+def _given_to_waves(ws):
+    torch.cuda.synchronize()
+    return int(ws[256:384].view(torch.int64)[8])
+
+
 def _both(g, m, call, ws, path, overflow=None):
-    """path: "one" = the whole batch in one launch, "staged" = no query, "tail" = the last ones.  overflow: the arrays
+    """path: "one" = the whole batch in one launch, a workgroup a query, "staged" = no query, "tail" = the last ones, "waves" = the
+    batch by waves (test_gpu_wave_search.py), the last ones of it perhaps by workgroups.  overflow: the arrays
     that a call writes which ends with ANN_EWORKSPACE (-5)."""
     runs = []
     for staged in (True, False):
@@ -54,8 +60,11 @@ def _both(g, m, call, ws, path, overflow=None):
         st = ann.ann_search_stats(ws)
         runs.append((ids.clone(), sc.clone(), (st.pairs_scored, st.nodes_expanded, st.max_query_iters, st.visited_overflow, st.queries)))
         ended = _ended_in_one_launch(ws)
+        assert _given_to_waves(ws) == (st.queries if path == "waves" and not staged else 0)
         if staged or path == "staged":
             assert ended == 0
+        elif path == "waves":
+            assert ended <= 256
         else:
             assert ended == st.queries if path == "one" else 0 < ended < st.queries
     assert torch.equal(runs[0][0], runs[1][0])
@@ -99,7 +108,21 @@ def test_batch_sizes_around_the_lines(dtype, du, d, hidden, J, Q):
     own = [torch.randint(lo, hi, (Q,), generator=gen, dtype=torch.int32).cuda() for lo, hi in ((0, 10), (0, 140), (0, 30))]
     ws = torch.empty(ann.ann_search_workspace_bytes(g, m, Q, 4, 8, 128, 20, 24), dtype=torch.uint8, device="cuda")
     _both(g, m, lambda: ann.ann_search_ragged(g, m, users, entries, *own, 8, 128, 20, 24, workspace=ws), ws,
-          "one" if Q <= (1024 if dtype == "bf16" else 768) else "staged")
+          ("one" if Q == 256 else "waves") if dtype == "bf16" else "one" if Q <= 768 else "staged")
+
+
+@pytest.mark.parametrize("dtype,du,d,hidden,J,Q,R,W", [
+    (*SHAPES[0], 257, 16, 16), (*SHAPES[0], 512, 16, 16), (*SHAPES[0], 600, 20, 16), ("f16", *SHAPES[0][1:], 512, 31, 9),
+    (*SHAPES[2], 512, 16, 16), (*SHAPES[2], 768, 16, 24), (*SHAPES[2], 1024, 16, 33), (*SHAPES[2], 1025, 16, 33)])
+def test_wide_rounds_of_middle_batches(dtype, du, d, hidden, J, Q, R, W):
+    """The metrics of 64-wide items beyond 256 queries, where rounds that are wide for the number of queries stay with a workgroup
+    a query (tiles of one, two and four column blocks) instead of a wave."""
+    g, m, users, entries = _handles(dtype, du, d, hidden, J, 5000, R, Q, 4)
+    gen = torch.Generator().manual_seed(Q)
+    own = [torch.randint(lo, hi, (Q,), generator=gen, dtype=torch.int32).cuda() for lo, hi in ((0, W + 3), (0, 140), (0, 30))]
+    ws = torch.empty(ann.ann_search_workspace_bytes(g, m, Q, 4, W, 128, 20, 24), dtype=torch.uint8, device="cuda")
+    _both(g, m, lambda: ann.ann_search_ragged(g, m, users, entries, *own, W, 128, 20, 24, workspace=ws), ws,
+          "one" if Q <= 1024 else "waves")
 
 
 @pytest.mark.parametrize("dtype,du,d,hidden,J", SHAPES[:4])
@@ -128,7 +151,7 @@ def test_last_queries_of_a_large_batch(dtype, du, d, hidden, J, visited, monkeyp
     own = [o.cuda() for o in own]
     ws = torch.empty(ann.ann_search_workspace_bytes(g, m, Q, E, W, L, k, 0), dtype=torch.uint8, device="cuda")
     _both(g, m, lambda: ann.ann_search_ragged(g, m, users, entries, *own, W, L, k, 0, workspace=ws), ws,
-          "tail")
+          "waves" if d == 64 else "tail")
     few = entries.clone()
     few[torch.arange(Q, device="cuda") % 7 != 0] = -1
     for seeds in (entries, few):

@@ -24,7 +24,9 @@ def _both(call, ws, waves=True):
             ann.ann_profile_enable(False)
         st = ann.ann_search_stats(ws)
         runs.append((ids.clone(), sc.clone(), (st.pairs_scored, st.nodes_expanded, st.max_query_iters, st.visited_overflow, st.queries)))
-        assert int(ws[256:384].view(torch.int64)[8]) == (st.queries if waves and not staged else 0)
+        ended, given = ws[256:384].view(torch.int64)[7:9].tolist()
+        assert given == (st.queries if waves and not staged else 0)
+        assert not waves or ended <= (0 if staged else 256)  # by workgroups: at most those that were handed over
     assert torch.equal(runs[0][0], runs[1][0])
     assert torch.equal(runs[0][1].view(torch.int32), runs[1][1].view(torch.int32))  # NaN too
     assert runs[0][2] == runs[1][2]
