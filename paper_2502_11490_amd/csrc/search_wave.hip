@@ -25,7 +25,7 @@ namespace gmpgr {
 // Running queries from which on a workgroup per query goes on with them (search_fused.hip): it takes half the time for a
 // round, and the longest searches run half as many rounds again as the average one.  Both sides measured, ms: 1,024 queries
 // with lists of 512 3.70 -> 3.26, 300 with W = 4, L = 64 1.02 -> 0.81, 2,048 with W = 16, L = 256 4.5 -> 3.9, 8,192 with
-// W = 4, L = 512 17.3 -> 16.2; 16,384 with lists of 64 the same.
+// W = 4, L = 512 17.3 -> 16.2; 16,384 with lists of 64 the same.  No more than there are waves.
 constexpr int WAVE_HAND = 256;
 
 // Ticks of the 100 MHz clock after which a wave of a search that is waited for says again that it goes on (4 ms): a store over
@@ -312,12 +312,13 @@ __global__ void __launch_bounds__(64 * MOST) wave_search_kernel(WaveArgs A) {
         }
         int n_list = 0, n_visited = 0, n_expanded = 0, first_open = 0, t = 0, n_cand = A.E;
         bool seeding = true, overflow = false, handed = false;
-        // among the last queries: nothing waits any more when few are left
-        const bool may_hand = A.hand_at > 0 && turn + slots >= A.Q;
+        // Rounds after which the number of ended queries is looked at: 4 once all queries have been taken, 32 before that (every
+        // 4: 16,384 queries of some 20 rounds 4.38 -> 4.66 ms).  When hand_at <= slots are left, none waits.
+        int poll = turn + slots >= A.Q ? 3 : 31;
         // bounded: a search cannot run more rounds than its cap or than ids fit its visited set
         for (int round = 0; round <= A.rounds_max; ++round) {
             int gone = 0;  // queries that have ended; looked at after the round's work
-            if (may_hand && (round & 3) == 3)
+            if (A.hand_at > 0 && (round & poll) == poll)
                 gone = __hip_atomic_load(&A.ctrl->next_query, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             // the candidates (the seeds, later one adjacency row per parent) piece by piece through the visited set, the
             // metric and into the list; which of them the list keeps does not depend on how they are cut
@@ -399,9 +400,13 @@ __global__ void __launch_bounds__(64 * MOST) wave_search_kernel(WaveArgs A) {
                 }
             }
 
-            if (A.Q - __builtin_amdgcn_readfirstlane(gone) <= A.hand_at && may_hand && (round & 3) == 3) {
-                handed = true;
-                break;
+            if (A.hand_at > 0 && (round & poll) == poll) {
+                const int left = A.Q - __builtin_amdgcn_readfirstlane(gone);
+                if (left <= A.hand_at) {
+                    handed = true;
+                    break;
+                }
+                if (left <= slots) poll = 3;
             }
 
             // termination test and choice of the parents: the first <= W unexpanded entries among the first L ranks

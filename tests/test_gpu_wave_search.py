@@ -91,6 +91,18 @@ def test_queries_with_their_own_parameters(dtype, shape, cap):
     _both(lambda: ann.ann_search_ragged(g, m, users, entries, *own, 12, 170, 20, cap, workspace=ws), ws)
 
 
+@pytest.mark.parametrize("shape,Q", [(TWO, 3000), (TWO, 2000), (ONE, 5000)])
+def test_the_longest_query_is_handed_over(shape, Q):
+    """The only query that has a seed: with more queries than waves it is taken first, among the last it would not be seen."""
+    g, m, users, entries = _handles("bf16", *shape, 5000, 16, Q, 4)
+    entries[torch.arange(Q) != 7] = -1
+    own = [torch.full((Q,), v, dtype=torch.int32, device="cuda") for v in (1, 20, 0)]
+    own[1][7] = 170
+    ws = torch.empty(ann.ann_search_workspace_bytes(g, m, Q, 4, 4, 170, 20, 0), dtype=torch.uint8, device="cuda")
+    _, _, counters = _both(lambda: ann.ann_search_ragged(g, m, users, entries, *own, 4, 170, 20, 0, workspace=ws), ws)
+    assert counters[2] > 100 and int(ws[256:384].view(torch.int64)[7]) == 1
+
+
 @pytest.mark.parametrize("shape", [TWO, ONE])
 def test_items_that_are_not_finite(shape):
     Q = 2200
