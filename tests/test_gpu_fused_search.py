@@ -2,6 +2,8 @@
 relevance, counter for counter.  Enabling the stage timing selects the separate kernels, whose parity with the oracle
 the other tests hold.  Every case also says which path it takes: the queries that a workgroup runs to their end
 are counted in the eighth word of the workspace's counters (at byte 256), those that waves are given in the ninth."""
+import time
+
 import pytest
 import torch
 
@@ -164,35 +166,40 @@ def test_last_queries_of_a_large_batch(dtype, du, d, hidden, J, visited, monkeyp
                 assert 0 < _ended_in_one_launch(ws) < Q
 
 
-def slow_rounds(W):
-    """A search of one query with slow rounds: every parent's row is one item of the next layer and 63 filler items, all
-    ids multiples of 1,024, which fall on one slot of the filter's table in LDS and walk through it one by one.  W items a
-    layer, 60 layers; relevance grows from layer to layer, the fillers have the least."""
-    R, layers, groups, step = 64, 60, 8, 1024
-    n_fill = groups * (R - 1)
-    N = (n_fill + (layers + 1) * W) * step
-    adj = torch.full((N, R), -1, dtype=torch.int32, device="cuda")
-    fill = torch.arange(n_fill, dtype=torch.int32, device="cuda").view(groups, R - 1) * step
-    node = lambda layer: (n_fill + layer * W + torch.arange(W, device="cuda")) * step
-    for layer in range(layers):
-        adj[node(layer), 0] = node(layer + 1).int()
-        adj[node(layer), 1:] = fill.repeat(-(-W // groups), 1)[:W]
-    emb = torch.full((N, 1), -4.0, device="cuda")
-    emb[torch.arange(n_fill, N // step, device="cuda") * step, 0] = torch.linspace(-3, 3, (layers + 1) * W, device="cuda")
-    m = ann.ann_mlp_load([torch.tensor([[0.0, 1.0]])], [torch.zeros(1)], torch.ones(1), 1, ann.ANN_F32)
-    return ann.ann_graph_load(adj, emb), m, torch.zeros(1, 1, device="cuda"), node(0).int()[None].contiguous(), W, W, W, layers
+def slow_rounds():
+    """A search of one query with slow rounds: 64 nodes a layer, each joined to one of the next layer and to 63 items of its own,
+    so that every round brings 4,096 new pairs; an fp32 metric of eight layers, whose passes over 64 pairs wait for each other
+    at every layer.  Relevance grows from layer to layer, the other items have the least."""
+    R, W, layers = 64, 64, 60
+    N = layers * W * R
+    i = torch.arange(N, device="cuda").view(layers, W, R)
+    adj = torch.full((layers, W, R, R), -1, dtype=torch.int32, device="cuda")
+    adj[:-1, :, 0, 0] = i[1:, :, 0]
+    adj[:, :, 0, 1:] = i[:, :, 1:]
+    emb = torch.zeros(layers, W, R, 1, device="cuda")
+    emb[:, :, 0, 0] = torch.linspace(0.5, 3, layers * W, device="cuda").view(layers, W)
+    first = torch.zeros(7, 2)
+    first[0, 1] = 1
+    between = torch.eye(7)
+    Ws = [first] + [between.clone() for _ in range(6)] + [between[:1].clone()]
+    m = ann.ann_mlp_load(Ws, [torch.zeros(7) for _ in range(7)] + [torch.zeros(1)], torch.ones(1), 1, ann.ANN_F32)
+    return ann.ann_graph_load(adj.view(N, R), emb.view(N, 1)), m, torch.zeros(1, 1, device="cuda"), i[:1, :, 0].int().contiguous(), W, layers
 
 
 def test_a_search_in_one_launch_reports_its_progress():
-    """36 ms of one query's rounds, 0.6 ms each and fewer than 64, under a limit far below that (a wait is looked at after
-    20 ms without a report): the kernel reports often enough for the call to see that it goes on."""
-    g, m, users, entries, W, L, k, layers = slow_rounds(32)
-    ws = torch.empty(ann.ann_search_workspace_bytes(g, m, 1, W, W, L, k, 0), dtype=torch.uint8, device="cuda")
-    want = ann.ann_search(g, m, users, entries, W, L, k, 0, workspace=ws)
-    assert ann.ann_search_stats(ws).max_query_iters == layers + 1
+    """60 rounds of one query, 0.5 ms each, under a limit far below the 20 ms after which the waiting thread asks: the kernel
+    reports often enough (every eighth round) for the call to see that it goes on.  One report in 64 rounds would not do."""
+    g, m, users, entries, W, layers = slow_rounds()
+    ws = torch.empty(ann.ann_search_workspace_bytes(g, m, 1, W, W, W, W, 0), dtype=torch.uint8, device="cuda")
+    want = ann.ann_search(g, m, users, entries, W, W, W, 0, workspace=ws)
+    assert ann.ann_search_stats(ws).max_query_iters == layers and _ended_in_one_launch(ws) == 1
+    start = time.perf_counter()
+    ann.ann_search(g, m, users, entries, W, W, W, 0, workspace=ws)
+    torch.cuda.synchronize()
+    assert time.perf_counter() - start > 0.025
     ann.ann_set_progress_timeout(1e-3)
     try:
-        got = ann.ann_search(g, m, users, entries, W, L, k, 0, workspace=ws)
+        got = ann.ann_search(g, m, users, entries, W, W, W, 0, workspace=ws)
     finally:
         ann.ann_set_progress_timeout(600.0)
         torch.cuda.synchronize()
