@@ -86,7 +86,8 @@ MOST = {SHAPES[0]: 1110, SHAPES[1]: 278, SHAPES[2]: 3206, SHAPES[3]: 400, SHAPES
 @pytest.mark.parametrize("dtype,du,d,hidden,J", SHAPES)
 def test_one_launch_is_the_staged_search(dtype, du, d, hidden, J, visited, monkeypatch):
     """One query and a few; one candidate a round up to several pieces of the filter; more seeds than a piece; odd
-    lists, k above and below L, lists longer than a workgroup; with and without a cap.  The widest metric and the fp32
+    lists, k above and below L, lists longer than a workgroup; with and without a cap.  (So few items have a bit each in LDS whatever
+    the form; test_gpu_fused_close.py and test_gpu_visited.py have larger tables.)  The widest metric and the fp32
     one take the staged path at 600 candidates and more, and one launch at the sizes just below their lines."""
     monkeypatch.setenv("GMPGR_VISITED_SET", "hash" if visited == "hash" else "bitmap")
     for Q, R, E, W, L, k, cap in [(1, 16, 1, 1, 1, 5, 0), (3, 1, 2, 1, 33, 7, 0), (65, 32, 3, 4, 257, 30, 0),
