@@ -577,31 +577,23 @@ __global__ void __launch_bounds__(BLK, CB == 4 ? 2 : 4) fused_search_kernel(Fuse
         int n_par = 0;
         if (!(cap > 0 && t >= cap)) {
             const int lim = min(L, n_list);
-            if (lim - first_open <= 1024) {  // one wave, four entries a lane at a time, no barrier on the way
+            // One entry a lane of one wave where that is enough, with no barrier on the way (one query, W = 4, L = 64 276 -> 269 us); a
+            // wave that walks on, 256 entries a step, is behind (256 queries, W = 8, L = 512 1,389 -> 1,447, one, W = 16, L = 1,000
+            // 1,446 -> 1,519).
+            if (lim - first_open <= 64) {
                 if (tid < 64) {
-                    int i0 = first_open;
-                    bool filled = false;
-                    while (i0 < lim && !filled) {
-                        uint64_t e[4];
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) e[u] = i0 + 64 * u + tid < lim ? cur[i0 + 64 * u + tid] : 1ull;
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) {
-                            if (filled) break;
-                            const bool open = !key_expanded(e[u]);
-                            const unsigned long long b = __ballot(open);
-                            const int pos = n_par + __popcll(b & ((1ull << tid) - 1ull)), tot = __popcll(b);
-                            const bool take = open && pos < W;
-                            if (take) {
-                                parents[pos] = key_id(e[u]);
-                                cur[i0 + tid] = e[u] | 1ull;
-                            }
-                            filled = n_par + tot >= W;
-                            n_par = min(W, n_par + tot);
-                            i0 = filled ? i0 + __ffsll(__ballot(take && pos == W - 1)) : min(i0 + 64, lim);
-                        }
+                    const int i = first_open + tid;
+                    const uint64_t e = i < lim ? cur[i] : 1ull;
+                    const bool open = !key_expanded(e);
+                    const unsigned long long b = __ballot(open);
+                    const int pos = __popcll(b & ((1ull << tid) - 1ull)), tot = __popcll(b);
+                    const bool take = open && pos < W;
+                    if (take) {
+                        parents[pos] = key_id(e);
+                        cur[i] = e | 1ull;
                     }
-                    if (tid == 0) shared_i[1] = i0, shared_i[3] = n_par;
+                    const int behind = __ffsll(__ballot(take && pos == W - 1));  // the last parent's lane + 1
+                    if (tid == 0) shared_i[1] = tot >= W ? first_open + behind : lim, shared_i[3] = min(W, tot);
                 }
                 __syncthreads();
                 first_open = __builtin_amdgcn_readfirstlane(shared_i[1]);
