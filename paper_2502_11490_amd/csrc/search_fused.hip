@@ -16,8 +16,10 @@
 // the instructions between them, one after the other.  For the widest metric scoring is 77 %: its weights come from L2.
 //
 // Measured against the batch path of its time: one query on a million items (lists of 64) 0.88 -> 0.46 ms, 64 fp32 queries
-// with lists of 32 and 4,096 0.78 -> 0.33 and 7.9 -> 4.2 ms; weights and visited set brought closer 0.40 -> 0.27, 0.27 ->
-// 0.24 and 3.57 -> 2.77 ms, 64 queries of the metric with two layers and lists of 256 2.15 -> 1.58.
+// with lists of 32 and 4,096 0.78 -> 0.33 and 7.9 -> 4.2 ms.  Each part that came closer, without it -> with it, us: weights in registers
+// 385 -> 275 (64 queries, lists of 256, two layers 1,741 -> 1,220; 256, W = 8, lists of 512 2,213 -> 1,448); a small metric in LDS
+// 340 -> 312 (64 fp32 queries, lists of 32; 16 with lists of 512 1,765 -> 1,620); the visited set in LDS 295 -> 275 and 327 -> 312 (the same
+// for lists of 256 and more); the merge of short lists by binary search 300 -> 275 (1,394 -> 1,220, 1,574 -> 1,448).
 //
 // A pair's relevance is computed in the order of the batch path's kernels (same fragments, same sequence of MFMAs,
 // same start values), so which path serves a call does not show in its results.
@@ -577,10 +579,10 @@ __global__ void __launch_bounds__(BLK, CB == 4 ? 2 : 4) fused_search_kernel(Fuse
         int n_par = 0;
         if (!(cap > 0 && t >= cap)) {
             const int lim = min(L, n_list);
-            // One entry a lane of one wave where that is enough, with no barrier on the way (one query, W = 4, L = 64 276 -> 269 us); a
-            // wave that walks on, 256 entries a step, is behind (256 queries, W = 8, L = 512 1,389 -> 1,447, one, W = 16, L = 1,000
-            // 1,446 -> 1,519).
-            if (lim - first_open <= 64) {
+            // First an entry a lane of one wave, with no barrier on the way, where that is mostly enough (one query, W = 4, L = 64 271 ->
+            // 267 us, 64 with W = 1, L = 1,000 6,850 -> 6,671, W = 2, L = 300 1,766 -> 1,723); with W = 4, L = 1,000 it is behind, 2,567 -> 2,608,
+            // and a wave that walks on, 256 entries a step, more so (2,624; 256 queries, W = 8, L = 512 1,385 -> 1,448).
+            if (lim - first_open <= 64 || W <= 2) {
                 if (tid < 64) {
                     const int i = first_open + tid;
                     const uint64_t e = i < lim ? cur[i] : 1ull;
@@ -593,12 +595,13 @@ __global__ void __launch_bounds__(BLK, CB == 4 ? 2 : 4) fused_search_kernel(Fuse
                         cur[i] = e | 1ull;
                     }
                     const int behind = __ffsll(__ballot(take && pos == W - 1));  // the last parent's lane + 1
-                    if (tid == 0) shared_i[1] = tot >= W ? first_open + behind : lim, shared_i[3] = min(W, tot);
+                    if (tid == 0) shared_i[1] = tot >= W ? first_open + behind : min(first_open + 64, lim), shared_i[3] = min(W, tot);
                 }
                 __syncthreads();
                 first_open = __builtin_amdgcn_readfirstlane(shared_i[1]);
                 n_par = __builtin_amdgcn_readfirstlane(shared_i[3]);
-            } else {
+            }
+            if (first_open < lim && n_par < W) {
                 int i0 = first_open;
                 bool filled = false;
                 while (i0 < lim && !filled) {

@@ -21,6 +21,8 @@ pytestmark = pytest.mark.gpu
     (1, 33, 4, 4, 300, 9, 0),     # 132 candidates a round: up to a pass of 128 pairs, and a few in a second one
     (256, 32, 2, 2, 30, 40, 0),   # the most queries; up to two column blocks
     (5, 32, 70, 3, 90, 10, 0),    # three column blocks
+    (3, 32, 270, 1, 400, 9, 0),   # one and two parents a round among more entries than a wave has lanes
+    (2, 33, 4, 2, 300, 9, 0),
     (4, 48, 200, 5, 120, 30, 25)])
 def test_one_launch_close_to_its_data(dtype, du, d, hidden, J, Q, R, E, W, L, k, cap, visited, monkeypatch):
     monkeypatch.setenv("GMPGR_VISITED_SET", "hash" if visited == "hash" else "bitmap")
