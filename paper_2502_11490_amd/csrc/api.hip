@@ -32,7 +32,7 @@ static inline int next_pow2(int64_t x) {
     return (int)p;
 }
 
-constexpr size_t STATS_OFFSET = 256;  // bytes from the workspace base: int64[8] counters
+constexpr size_t STATS_OFFSET = 256;  // bytes from the workspace base: int64[16] counters
 
 bool make_plan(const ann_graph *g, const ann_mlp *m, int32_t Q, int32_t E, int32_t W_max, int32_t L_max,
                int32_t k, int32_t max_iters_max, Plan *p) {

@@ -287,14 +287,15 @@ __device__ int filter_and_mark(const int32_t *cand, const int32_t *cand_rank, in
 // survivors).  The UNROLL atomics of a thread are in flight together.
 //   at[u] : BITMAP: the bit that stands for the candidate; else scratch
 //   table : BITMAP: one bit per item; else hash_cap slots of one id each, EMPTY_SLOT = free, an id lies in the first free
-//           slot from its home on.  The caller guarantees n_visited + n_cand <= hash_cap / 2.
+//           slot from its home on.  The caller guarantees that slots stay free: n_visited + n_cand is at most hash_cap / 2 of a
+//           table in memory, five eighths of one in LDS.
 //   PEEK  : the word is read first, and the atomic left out where it shows the id, or another one in its slot: an atomic
 //           makes its line dirty whatever it finds, and full batches are bound by that traffic.  (What was read may be
 //           older than the set; it only ever grows, so the atomic has the last word.)
 // A query's set belongs to one workgroup, so the atomics need no more than workgroup scope: they are carried out in
 // the L2 slice, like a load or a store.  (At device scope, the default of atomicCAS, they go to the memory side and
 // cost several times as much.)
-// Against the filters below, which sort out repetitions in LDS tables first (five barriers, 16 KB of tables for 512
+// Against the filters above, which sort out repetitions in LDS tables first (five barriers, 16 KB of tables for 512
 // candidates, 64-byte buckets read whole): one query in one launch 473 -> 412 us, 64 fp32 queries 335 -> 270 us (lists of
 // 4,096: 4.18 -> 3.63 ms).  In full batches, with PEEK: 2,048 8-bit queries with lists of 2,048 29.7 -> 28.3 ms, 6,001 fp16
 // queries in slots 30.0 -> 29.1, 8,192 ragged ones 7.39 -> 7.05; without it 31.9, 29.7 and 7.50, and 16,384 queries of a
@@ -355,7 +356,7 @@ __device__ __forceinline__ void visited_enter(const int32_t (&v)[UNROLL], uint32
     for (int u = 0; u < UNROLL; ++u) meanwhile(u, v[u], maybe[u]);
 #pragma unroll
     for (int u = 0; u < UNROLL; ++u) {
-        // another id in the slot: on to the next one.  Ends: at least half of the slots are free
+        // another id in the slot: on to the next one.  Ends: some slots are free (see above)
         bool open = fresh[u] && old[u] != EMPTY_SLOT && old[u] != (uint32_t)v[u];
         fresh[u] = fresh[u] && old[u] == EMPTY_SLOT;
         while (open) {

@@ -44,14 +44,14 @@ constexpr int SCAN_BLOCK = 256;
 constexpr int SCAN_WAVES = SCAN_BLOCK / 64;
 
 // Phase timing of the round kernel for measurement builds (-DROUND_TIMING): thread 0 of every
-// 64th workgroup adds the shader-clock ticks of each phase to counters 8..15 of the stats block
+// 64th workgroup adds the shader-clock ticks of each phase to counters 9..15 of the stats block
 // (every workgroup doing so would serialise on those few addresses and distort what is measured).
 #ifdef ROUND_TIMING
 #define PHASE_MARK(k)                                                                          \
     do {                                                                                       \
         if (threadIdx.x == 0 && (blockIdx.x & 63) == 0) {                                      \
             long long now_ = clock64();                                                        \
-            atomicAdd((unsigned long long *)&stats[8 + (k)], (unsigned long long)(now_ - t_)); \
+            atomicAdd((unsigned long long *)&stats[9 + (k)], (unsigned long long)(now_ - t_)); \
             t_ = now_;                                                                         \
         }                                                                                      \
     } while (0)
@@ -592,8 +592,8 @@ round_kernel(const int32_t *__restrict__ adj, const int32_t *__restrict__ adj_ra
     uint32_t *table = hash + (size_t)q * (size_t)(BITMAP ? -hash_cap : hash_cap);
     int n_new = 0;
     if (FILTER != FILTER_ATOMIC) {
-        // In pieces of at most `chunk` (what the dedupe tables in LDS hold); the first of equal candidates is kept.  An id that comes again in a later piece is dropped there because the earlier piece has
-        // entered it into the visited set.
+        // In pieces of at most `chunk` (what the dedupe tables in LDS hold); the first of equal candidates is kept.  An id that
+        // comes again in a later piece is dropped there because the earlier piece has entered it into the visited set.
         if (RESIDENT) __syncthreads();  // the LDS copies of the list are dead from here on; their space is reused
         int dd_n = 2;
         while (dd_n < 2 * chunk) dd_n <<= 1;

@@ -12,7 +12,8 @@
 // which the matrix instructions are half, a fifth the way to the neighbours and through the visited set, a seventh the
 // merge; and the slowest search, which runs half as many rounds again as the average one.  Full batches: two waves a SIMD
 // take 22 us a round, and the scattered accesses of a round (128 visited words, 75 item rows, 75 dirty lines) share
-// the memory's bandwidth.
+// the memory's bandwidth.  The builds of eight waves for two hidden layers take all 256 registers and spill 10 to 18 of them
+// (60 to 76 bytes of scratch; bitmaps 44 to 60); scalar registers spill to vector ones in all of them.
 // Against the batch path and, up to 1,024 queries, the search by workgroups: 1,024 queries of 10^6 items, lists of 512
 // 6.1 -> 3.3 ms; 16,384 queries of 2 10^7 items, one hidden layer, lists of 64 8.3 -> 4.7; 8,192 ragged capped queries
 // 7.4 -> 4.6.
@@ -20,7 +21,6 @@
 #include "search_device.h"
 
 namespace gmpgr {
-
 
 // Running queries from which on a workgroup per query goes on with them (search_fused.hip): it takes half the time for a
 // round, and the longest searches run half as many rounds again as the average one.  Both sides measured, ms: 1,024 queries
@@ -602,7 +602,7 @@ static int wave_launch(const SearchArgs &a, const WaveArgs &A, int nw, size_t sm
     auto fn = bm ? wave_search_kernel<TWO, F16, true, MOST, U> : wave_search_kernel<TWO, F16, false, MOST, U>;
     static std::atomic<uint32_t> raised[2];
     if (int rc = raise_lds_limit((const void *)fn, 160 * 1024, a.m->device, raised[bm ? 1 : 0]); rc != ANN_OK) return rc;
-    hipLaunchKernelGGL(fn, dim3(a.plan.Q < 256 ? a.plan.Q : 256), dim3(64 * nw), smem, a.stream, A);
+    hipLaunchKernelGGL(fn, dim3(256), dim3(64 * nw), smem, a.stream, A);
     ANN_HIP_TRY(hipGetLastError());
     return ANN_OK;
 }
