@@ -719,18 +719,22 @@ static size_t round_smem(const SearchArgs &a, int filter, int list_keys = 0) {
 
 // Which visited filter a round uses.  The walkers' rule needs the first of equal candidates.  Atomics, one a candidate, with a
 // hash table (time in the round kernel: 2,048 queries of 2 10^6 items, 64 to 2,048 candidates 3 to 17 % less, 16,384 queries
-// 8.3 -> 8.1 ms a call, 6,001 in slots 30.0 -> 29.1).  On a bitmap the ordered filter's loads and plain stores against them, time of
-// the ordered one / of the atomics in the round kernel, bitmaps of 0.5, 2, 4 and 10 million items, by id (by rank within 0.02
-// of it), lists of 1,024: 2,048 queries, 64 candidates 1.16, -, 1.12, 1.11; 128 candidates 1.10, 1.04, 1.05, 1.05; 160 1.01, -, 1.00, 1.00;
-// 192 0.99, 0.98, 0.99, 0.99; 256 0.99, 0.97, 0.99, 1.00; 384 0.97, 1.00, 1.01, 1.02; 512 0.95, 0.97, 0.99, 1.00; 544 -, 0.96, -, -;
-// 768 0.92, 0.93, 0.96, 0.98; 1,024 0.88, 0.91, 0.95, 0.97; 1,056 0.92 and 2,048 0.82 (2 million items).  8,192 queries with 128 threads, 32
-// candidates 1.06, 64 1.03, 96 0.98, 128 0.99.  So: atomics for up to half a candidate a thread; beyond that the ordered filter, unless
-// its tables in LDS cost a workgroup on the CU (512 candidates by rank, lists of 2,048, 4 and 10 million items: 2,048 queries,
-// which are then all resident, 1.12 and 1.13, 4,096 1.04, 8,192 0.99, 1,024 1.00).
+// 8.3 -> 8.1 ms a call, 6,001 in slots 30.0 -> 29.1).  On a bitmap the ordered filter, whose barriers a few queries wait for, but whose
+// loads and plain stores are less traffic when the chip is full.  Time in the round kernel, ordered / atomics, bitmaps of 0.1 to 10
+// million items by id or by rank, candidates of a round in brackets:
+//   16 and 64 queries 1.13 to 1.29 throughout; 256 (512) 1.16 to 1.22, (2,048) 1.06; 300 (512) 1.12 to 1.18, (2,048) 1.02; 384 (1,024) 1.00
+//   to 1.04, (2,048) 0.98; 512 (512) 1.06 to 1.17, (768) 0.99 to 1.03, (1,024) 0.95 to 1.01, (2,048) 0.90 to 1.02; 700 (512) 1.01 to
+//   1.06, (768) 0.97; 1,024 (256) 1.02 to 1.11, (320) 1.00, (384) 0.99 to 1.04, (512) 0.97 to 1.01, (2,048) 0.77 to 0.92; 1,500 (256) 1.00;
+//   2,048 (64) 1.11 to 1.16, (128) 1.04 to 1.14, (160) 1.00, (192) 0.98, (256) 0.96 to 1.00, (512) 0.84 to 1.00, (1,024) 0.86 to 0.98;
+//   4,096 and 6,000 (64) 1.08 to 1.17, (128) 1.01 to 1.05; 8,192 and 16,384 with 128 threads (32) 1.05 to 1.09, (64) 1.01 to 1.05, (96)
+//   and (128) 0.94 to 0.98.
+// So: atomics for up to half a candidate a thread, for 256 queries or fewer, for fewer than 393,216 candidates of all queries, and where
+// the ordered filter's tables in LDS cost a workgroup on the CU (512 candidates by rank, lists of 2,048: 2,048 queries, which
+// are then all resident, 1.12, 4,096 1.04, 8,192 0.99, 1,024 1.00).
 static int filter_of(const SearchArgs &a, int threads, int list_keys) {
     const Plan &p = a.plan;
     if (a.walkers) return FILTER_WALKERS;
-    if (p.bitmap_words == 0 || 2 * p.slots <= threads) return FILTER_ATOMIC;
+    if (p.bitmap_words == 0 || 2 * p.slots <= threads || p.Q <= 256 || (int64_t)p.Q * p.slots < 3 << 17) return FILTER_ATOMIC;
     return groups_of(round_smem(a, FILTER_ORDERED, list_keys), threads) < groups_of(round_smem(a, FILTER_ATOMIC, list_keys), threads)
                ? FILTER_ATOMIC : FILTER_ORDERED;
 }

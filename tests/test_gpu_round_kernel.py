@@ -59,10 +59,11 @@ def test_walkers_of_a_large_batch(Q, R, E, k, threads, visited, monkeypatch):
 
 
 @pytest.mark.parametrize("Q,R,W,L,ranked,threads,which", [
-    (300, 32, 4, 100, False, 256, ATOMIC), (300, 43, 3, 100, False, 256, ORDERED), (300, 32, 9, 100, True, 256, ORDERED),
-    (300, 32, 16, 1024, False, 256, ORDERED), (300, 32, 16, 1024, True, 256, ORDERED), (300, 32, 16, 1500, True, 256, ATOMIC),
-    (300, 32, 16, 1500, False, 256, ORDERED), (300, 32, 17, 300, True, 512, ORDERED), (300, 32, 32, 1500, False, 512, ORDERED),
-    (300, 32, 33, 300, True, 512, ORDERED), (8192, 32, 2, 60, False, 128, ATOMIC), (8192, 13, 5, 60, True, 128, ORDERED)])
+    (4096, 32, 4, 100, False, 256, ATOMIC), (4096, 43, 3, 100, False, 256, ORDERED), (1024, 32, 11, 100, True, 256, ATOMIC),
+    (1024, 32, 12, 100, True, 256, ORDERED), (256, 32, 64, 300, False, 512, ATOMIC), (257, 32, 64, 300, False, 512, ORDERED),
+    (1024, 32, 16, 1024, False, 256, ORDERED), (1024, 32, 16, 1024, True, 256, ORDERED), (1024, 32, 16, 1500, True, 256, ATOMIC),
+    (1024, 32, 16, 1500, False, 256, ORDERED), (1024, 32, 17, 300, True, 512, ORDERED), (1024, 32, 32, 1500, False, 512, ORDERED),
+    (1024, 32, 33, 300, True, 512, ORDERED), (8192, 32, 2, 60, False, 128, ATOMIC), (8192, 13, 5, 60, True, 128, ORDERED)])
 def test_visited_filter_on_a_bitmap(Q, R, W, L, ranked, threads, which, monkeypatch):
     """On either side of the lines; the searches with the hash table, which always takes the atomics, are the reference."""
     N, E, k, cap = 4001, 5, 50, 12
